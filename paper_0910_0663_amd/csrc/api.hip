@@ -159,6 +159,13 @@ struct vtm_handle_s {
     DevBuf<int64_t> nofs;
     DevBuf<double> N64, N64T;  // T: transposed, for the adjoint of an unsymmetric A
     DevBuf<float> N32, N32T;
+    // several right-hand sides (column-group handles): the same K^-1[N, N] as MFMA
+    // tiles (T: transposed, for the adjoint of an unsymmetric A)
+    bool ppt = false;
+    std::vector<int64_t> ntofs_host;
+    DevBuf<int64_t> ntofs;
+    DevBuf<double> Nt64, Nt64T;
+    DevBuf<float> Nt32, Nt32T;
     DevBuf<int32_t> pn_off, pn_node, pn_pfirst;
     // tearing at interfacial nodes: maps between plan rows and the caller's nodes, the
     // caller's A, and right-hand side / residual / solution in the caller's node order
@@ -305,6 +312,20 @@ vtm_status port_residual_launch(vtm_handle h, bool low, int cur, int nrhs) {
     return VTM_OK;
 }
 
+// Whether a solve of nrhs right-hand sides has port-to-port sweeps: one right-hand
+// side in any of the forms, several in the batched (MFMA tile) form, on the
+// port-node tiles, or on M when the handle keeps M.  The adjoint of an
+// unsymmetric A needs a form with a transposed operator.
+bool has_pp(vtm_handle h, int nrhs, bool adjoint) {
+    const bool same = !adjoint || h->plan.symmetric;
+    if (h->ppb) return same;
+    if (!h->pp) return false;
+    if (nrhs == 1) return same || h->ppn;
+    if (h->pps || h->ppn) return h->ppt;
+    const size_t tv = h->opt.precision == VTM_FP64 ? 8 : 4;
+    return same && size_t(h->plan.max_ports) * 2 * tv <= 65536;  // M: two staged right-hand sides in LDS
+}
+
 struct IterOut {
     int64_t sweeps = 0;
     int checks = 0;
@@ -427,6 +448,21 @@ vtm_status sweep_once(vtm_handle h, bool low, int nrhs, const void* b, void* x, 
                                                       h->lds_limit, h->Mbt.p, h->qmofs.p, h->port_off.p,
                                                       h->port_twin.p, h->h32.p, h->a32[cur].p, h->a32[cur ^ 1].p,
                                                       cur, h->stream));
+    } else if (pp && nrhs > 1 && (h->pps || h->ppn)) {
+        const vtm::Plan& P = h->plan;
+        const bool kt = adjoint && !P.symmetric;
+        if (!low)
+            VTM_HIP(vtm::launch_sweep_ppt<double>(int(P.S), P.max_npn, P.max_ports, nrhs, h->lds_limit,
+                                                  kt ? h->Nt64T.p : h->Nt64.p, h->ntofs.p, h->pn_off.p,
+                                                  h->pn_pfirst.p, h->port_off.p, h->port_twin.p, h->c64.p,
+                                                  h->beta64.p, h->gamma64.p, h->h64.p, h->a64[cur].p,
+                                                  h->a64[cur ^ 1].p, cur, h->stream));
+        else
+            VTM_HIP(vtm::launch_sweep_ppt<float>(int(P.S), P.max_npn, P.max_ports, nrhs, h->lds_limit,
+                                                 kt ? h->Nt32T.p : h->Nt32.p, h->ntofs.p, h->pn_off.p,
+                                                 h->pn_pfirst.p, h->port_off.p, h->port_twin.p, h->c32.p, h->beta32.p,
+                                                 h->gamma32.p, h->h32.p, h->a32[cur].p, h->a32[cur ^ 1].p, cur,
+                                                 h->stream));
     } else if (pp && h->ppn) {
         const vtm::Plan& P = h->plan;
         if (!low)
@@ -457,11 +493,11 @@ vtm_status sweep_once(vtm_handle h, bool low, int nrhs, const void* b, void* x, 
     } else if (pp) {
         const vtm::Plan& P = h->plan;
         if (!low)
-            VTM_HIP((vtm::launch_sweep_pp<double, double>(int(P.S), P.max_ports, h->M64.p, h->pofs.p, h->port_off.p,
+            VTM_HIP((vtm::launch_sweep_pp<double, double>(int(P.S), P.max_ports, nrhs, h->M64.p, h->pofs.p, h->port_off.p,
                                                           h->port_twin.p, h->h64.p, h->a64[cur].p, h->a64[cur ^ 1].p,
                                                           h->stream)));
         else
-            VTM_HIP((vtm::launch_sweep_pp<float, float>(int(P.S), P.max_ports, h->M32.p, h->pofs.p, h->port_off.p,
+            VTM_HIP((vtm::launch_sweep_pp<float, float>(int(P.S), P.max_ports, nrhs, h->M32.p, h->pofs.p, h->port_off.p,
                                                         h->port_twin.p, h->h32.p, h->a32[cur].p, h->a32[cur ^ 1].p,
                                                         h->stream)));
     } else {
@@ -765,7 +801,7 @@ vtm_status run_fp64(vtm_handle h, int nrhs, double tol, bool adjoint, bool resum
     if (!resume) cad.record(0, max_of(out.rel));
     std::vector<double> bb(nrhs);  // ||b||^2 per right-hand side, for the port-residual checks
     for (int r = 0; r < nrhs; ++r) bb[r] = h->h_norms[2 * r + 1];
-    const bool pp = ((h->pp && nrhs == 1) || h->ppb) && (!adjoint || P.symmetric || h->ppn) && !resume;
+    const bool pp = has_pp(h, nrhs, adjoint) && !resume;
     // port-to-port sweeps check the residual from port quantities; once it passes
     // (and at the end), x^k is rebuilt by a full sweep from the same waves and
     // the residual on A decides
@@ -864,15 +900,19 @@ vtm_status run_refine(vtm_handle h, int nrhs, double tol, bool adjoint, IterOut&
     if (!(drop > 0.0)) drop = h->opt.precision == VTM_BF16_REFINE ? 1e-2 : 1e-5;
     VTM_HIP(vtm::launch_fill<double>(nv, 0.0, h->xp.p, h->stream));
     std::vector<double> rel, e, target(nrhs);
-    const bool pp = ((h->pp && nrhs == 1) || h->ppb) && (!adjoint || P.symmetric || h->ppn);
+    const bool pp = has_pp(h, nrhs, adjoint);
     auto all_le = [](const std::vector<double>& v, const std::vector<double>& t) {
         for (size_t i = 0; i < v.size(); ++i)
             if (!(v[i] <= t[i])) return false;
         return true;
     };
     // the inner checks: ||r - A d|| from port quantities (then r itself is not read
-    // again), else on A with the FP64 r kept by the outer residual
-    const bool iface = pp && !P.vertex;
+    // again), else on A with the FP64 r kept by the outer residual.  Several right-hand
+    // sides on FP32 column groups check on A: near an inner target of 1e-5 the rounding
+    // of the interior rows, which port quantities leave out, is part of the value that
+    // has always ended their inner solves
+    const bool ports_check = pp && (nrhs == 1 || h->ppb);
+    const bool iface = ports_check && !P.vertex;
     for (int outer = 0;; ++outer) {
         // r = b - A x (FP64) and its BF16 or FP32 copy (the inner right-hand side),
         // written by the same pass
@@ -900,7 +940,7 @@ vtm_status run_refine(vtm_handle h, int nrhs, double tol, bool adjoint, IterOut&
         Cadence cad;
         cad.m = h->opt.check_every;
         cad.adaptive = h->opt.adaptive_checks != 0;
-        cad.reach = inner_reach(h, nrhs, pp);
+        cad.reach = inner_reach(h, nrhs, ports_check);
         cad.cap = 4;
         cad.record(0, 1.0);
         double goal = 1.0;
@@ -938,7 +978,7 @@ vtm_status run_refine(vtm_handle h, int nrhs, double tol, bool adjoint, IterOut&
             cad.record(inner, max_of(e));
         }
         out.sweeps += inner;
-        if (pp && !P.vertex) {  // d from the last sweep's waves, by a full sweep
+        if (iface) {  // d from the last sweep's waves, by a full sweep
             const void* bl = h->tiles ? static_cast<const void*>(h->b16.p) : static_cast<const void*>(h->b32.p);
             if ((st = sweep_once(h, true, nrhs, bl, h->d32.p, cur ^ 1, adjoint, true, false)) != VTM_OK)
                 return st;
@@ -1251,6 +1291,39 @@ static vtm_status build_values(vtm_handle_s* h) {
         }
         VTM_HIP(hipStreamSynchronize(s));
     }
+    if (h->ppt) {
+        const int64_t nt = h->ntofs_host[P.S];
+        const bool fp64 = o.precision == VTM_FP64;
+        auto build = [&](bool transpose) -> hipError_t {
+            if (fp64)
+                return vtm::launch_port_node_tiles<double>(int(P.S), h->sub_off.p, h->kofs.p, h->pn_off.p, h->pn_node.p,
+                                                           h->K64.p, h->ntofs.p,
+                                                           transpose ? h->Nt64T.p : h->Nt64.p, transpose, s);
+            return vtm::launch_port_node_tiles<float>(int(P.S), h->sub_off.p, h->kofs.p, h->pn_off.p, h->pn_node.p,
+                                                      h->K32.p, h->ntofs.p, transpose ? h->Nt32T.p : h->Nt32.p,
+                                                      transpose, s);
+        };
+        auto room = [&]() -> hipError_t {
+            hipError_t e = fp64 ? h->Nt64.alloc(nt) : h->Nt32.alloc(nt);
+            if (e == hipSuccess && !P.symmetric) e = fp64 ? h->Nt64T.alloc(nt) : h->Nt32T.alloc(nt);
+            return e;
+        };
+        const hipError_t e = room();
+        if (e == hipErrorOutOfMemory) {
+            // no room for a second copy of the operators: several right-hand sides keep
+            // the full form
+            (void)hipGetLastError();
+            h->ppt = false;
+            h->Nt64.reset();
+            h->Nt64T.reset();
+            h->Nt32.reset();
+            h->Nt32T.reset();
+        } else {
+            VTM_HIP(e);
+            VTM_HIP(build(false));
+            if (!P.symmetric) VTM_HIP(build(true));
+        }
+    }
     if (h->ppn) {
         const int64_t nn = P.nofs[P.S];
         if (o.precision == VTM_FP64) {
@@ -1414,7 +1487,21 @@ static vtm_status setup_from_plan(std::unique_ptr<vtm_handle_s> h, vtm_handle* o
     } else if (h->pp) {
         VTM_HIP(h->pofs.upload(P.pofs, s));
     }
-    if (h->pp) VTM_HIP(fp64 ? h->h64.alloc(P.nports) : h->h32.alloc(P.nports));
+    if (h->pp) VTM_HIP(fp64 ? h->h64.alloc(P.nports * nr) : h->h32.alloc(P.nports * nr));
+    // several right-hand sides: the port-node operators also as MFMA tiles
+    const int npt = vtm::node_tile_pad(P.max_npn);
+    h->ppt = (h->pps || h->ppn) && nr > 1 &&
+             (fp64 ? vtm::ppt_lds_bytes<double>(npt, P.max_ports, 1) : vtm::ppt_lds_bytes<float>(npt, P.max_ports, 1)) <=
+                 h->lds_limit;
+    if (h->ppt) {
+        h->ntofs_host.resize(P.S + 1);
+        h->ntofs_host[0] = 0;
+        for (int64_t k = 0; k < P.S; ++k) {
+            const int64_t np = vtm::node_tile_pad(P.pn_off[k + 1] - P.pn_off[k]);
+            h->ntofs_host[k + 1] = h->ntofs_host[k] + np * np;
+        }
+        VTM_HIP(h->ntofs.upload(h->ntofs_host, s));
+    }
 
     if ((st = build_values(h.get())) != VTM_OK) return st;
     if (h->tiles) {

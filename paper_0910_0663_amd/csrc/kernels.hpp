@@ -149,9 +149,9 @@ hipError_t launch_port_h(int S, int nrhs, const int32_t* sub_off, const int32_t*
 template <typename TV>
 hipError_t launch_wave_coupled(int n_ports, int nrhs, Coupling<TV> B, const int32_t* port_row, const TV* pgamma,
                                const int32_t* port_twin, const TV* x, const TV* a_cur, TV* a_next, hipStream_t st);
-// a_next[twin(p)] = h_p + (M_s a_cur)_p for every port (one right-hand side)
+// a_next[twin(p)] = h_p + (M_s a_cur)_p for every port and right-hand side
 template <typename TO, typename TV>
-hipError_t launch_sweep_pp(int S, int max_q, const TO* M, const int64_t* pofs, const int32_t* port_off,
+hipError_t launch_sweep_pp(int S, int max_q, int nrhs, const TO* M, const int64_t* pofs, const int32_t* port_off,
                            const int32_t* port_twin, const TV* h, const TV* a_cur, TV* a_next, hipStream_t st);
 
 // Port-node form for any A: K^-1[N, N] over a sub-circuit's k port nodes in the
@@ -189,6 +189,24 @@ hipError_t launch_sweep_pps(int S, int max_npn, int max_ports, const TO* Sp, con
                             const int32_t* pn_off, const int32_t* pn_pfirst, const int32_t* port_off,
                             const int32_t* port_twin, const TV* pc, const TV* pW, TV W, const TV* h,
                             const TV* a_cur, TV* a_next, int reverse, hipStream_t st);
+
+// Several right-hand sides: K^-1[N, N] (transpose: K^-T[N, N]) of every
+// sub-circuit as zero-padded MFMA A tiles (node_tile_rc, tiles.hpp) at Nt + ntofs[s],
+// np = node_tile_pad(k) ...
+template <typename T>
+hipError_t launch_port_node_tiles(int S, const int32_t* sub_off, const int64_t* kofs, const int32_t* pn_off,
+                                  const int32_t* pn_node, const T* K, const int64_t* ntofs, T* Nt, bool transpose,
+                                  hipStream_t st);
+// ... and the port-node sweep on them: per sub-circuit and right-hand side
+// t_n = sum_{p at n} c_p a_p, Z = K^-1[N, N] T on the matrix cores,
+// a_next[twin(p)] = beta_p z_n(p) + gamma_p a_p + h_p.  reverse as for
+// launch_sweep_pps.  One right-hand side's ppt_lds_bytes must fit lds_limit (else
+// hipErrorInvalidValue).
+template <typename T>
+hipError_t launch_sweep_ppt(int S, int max_npn, int max_ports, int nrhs, size_t lds_limit, const T* Nt,
+                            const int64_t* ntofs, const int32_t* pn_off, const int32_t* pn_pfirst,
+                            const int32_t* port_off, const int32_t* port_twin, const T* pc, const T* pbeta,
+                            const T* pgamma, const T* h, const T* a_cur, T* a_next, int reverse, hipStream_t st);
 
 // ---- residual -------------------------------------------------------------
 // Per right-hand side, the sum of squares of b - A x for the iterate of the

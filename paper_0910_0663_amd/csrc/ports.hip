@@ -105,27 +105,28 @@ __device__ inline void load16p(const T* p, T (&v)[Group<T>::G]) {
     }
 }
 
-// One port-to-port sweep, one workgroup per sub-circuit (a_next[twin(p)] =
-// h_p + (M a)_p).  SPLIT = 2 (q <= 32, one wavefront): lane l takes row l % 32
-// and half the column groups, and the halves are added with a cross-lane
-// shuffle.  SPLIT = 1: one row per thread (64 or 256 threads); with few large
-// sub-circuits the rows of each are also spread over gridDim.y workgroups.
-template <typename TO, typename TV, int SPLIT>
+// One port-to-port sweep, one workgroup per sub-circuit and block of up to R
+// right-hand sides (a_next[twin(p)] = h_p + (M a)_p).  SPLIT = 2 (q <= 32, one
+// wavefront, R = 1): lane l takes row l % 32 and half the column groups, and the
+// halves are added with a cross-lane shuffle.  SPLIT = 1: one row per thread.
+template <typename TO, typename TV, int SPLIT, int R>
 __global__ void __launch_bounds__(256)
-    k_sweep_pp(const TO* __restrict__ M, const int64_t* __restrict__ pofs, const int32_t* __restrict__ port_off,
-               const int32_t* __restrict__ port_twin, const TV* __restrict__ h, const TV* __restrict__ a_cur,
-               TV* __restrict__ a_next, int max_q) {
+    k_sweep_pp(int ny, int nrhs, const TO* __restrict__ M, const int64_t* __restrict__ pofs,
+               const int32_t* __restrict__ port_off, const int32_t* __restrict__ port_twin,
+               const TV* __restrict__ h, const TV* __restrict__ a_cur, TV* __restrict__ a_next) {
     constexpr int G = Group<TO>::G;
     extern __shared__ char smem[];
-    TV* av = reinterpret_cast<TV*>(smem);
-    const int s = xcd_block(blockIdx.x, gridDim.x);
+    TV* av = reinterpret_cast<TV*>(smem);  // [q][R]
+    const int u = xcd_block(blockIdx.x, gridDim.x);
+    const int s = R == 1 ? u : u / ny, r0 = R == 1 ? 0 : (u - s * ny) * R;
+    const int w = R == 1 ? 1 : min(R, nrhs - r0);
     const int p0 = port_off[s], q = port_off[s + 1] - p0;
     const int lane = threadIdx.x;
     const TO* Ms = M + pofs[s];
     const int ng = q / G, full = ng * G;
     const int bs = blockDim.x;
-    if (int(blockIdx.y) * bs >= q) return;  // no rows for this block (whole workgroup leaves)
-    for (int t = lane; t < q; t += bs) av[t] = a_cur[p0 + t];
+    for (int t = lane; t < q * R; t += bs)
+        av[t] = t % R < w ? a_cur[int64_t(p0 + t / R) * nrhs + r0 + t % R] : TV(0);
     __syncthreads();
     if constexpr (SPLIT == 2) {
         const int row = lane & 31, half = lane >> 5;
@@ -150,23 +151,118 @@ __global__ void __launch_bounds__(256)
         v += __shfl_down(v, 32, 64);
         if (half == 0 && row < q) a_next[port_twin[p0 + row]] = h[p0 + row] + v;
     } else {
-        for (int row = int(blockIdx.y) * bs + lane; row < q; row += bs * int(gridDim.y)) {
-            TV acc[G];
+        for (int row = lane; row < q; row += bs) {
+            TV acc[R][G];
 #pragma unroll
-            for (int j = 0; j < G; ++j) acc[j] = TV(0);
+            for (int k = 0; k < R; ++k)
+#pragma unroll
+                for (int j = 0; j < G; ++j) acc[k][j] = TV(0);
 #pragma unroll 4
             for (int g = 0; g < ng; ++g) {
                 TO v[G];
                 load16p<TO>(Ms + (int64_t(g) * q + row) * G, v);
 #pragma unroll
-                for (int j = 0; j < G; ++j) acc[j] += TV(v[j]) * av[g * G + j];
-            }
-            for (int c = full; c < q; ++c) acc[0] += TV(Ms[int64_t(full) * q + int64_t(c - full) * q + row]) * av[c];
-            TV v = acc[0];
+                for (int j = 0; j < G; ++j)
 #pragma unroll
-            for (int j = 1; j < G; ++j) v += acc[j];
-            a_next[port_twin[p0 + row]] = h[p0 + row] + v;
+                    for (int k = 0; k < R; ++k) acc[k][j] += TV(v[j]) * av[(g * G + j) * R + k];
+            }
+            for (int c = full; c < q; ++c) {
+                const TV v = TV(Ms[int64_t(full) * q + int64_t(c - full) * q + row]);
+#pragma unroll
+                for (int k = 0; k < R; ++k) acc[k][0] += v * av[c * R + k];
+            }
+            const int64_t tw = int64_t(port_twin[p0 + row]) * nrhs + r0, po = int64_t(p0 + row) * nrhs + r0;
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                TV v = acc[k][0];
+#pragma unroll
+                for (int j = 1; j < G; ++j) v += acc[k][j];
+                if (k < w) a_next[tw + k] = h[po + k] + v;
+            }
         }
+    }
+}
+
+// The same with few sub-circuits of many ports (tears at interfacial nodes): a
+// workgroup of KS wavefronts takes 64 rows of one sub-circuit, each wavefront
+// every KS-th chunk of its column groups, and the partial sums meet in LDS in
+// wavefront order.  Bound by latency: with one wavefront per 64 rows each lane had a
+// chain of q / G rounds of loads and the chip was idle (six sub-circuits of up to
+// 200 ports, 1.4 MB of operators: 7.5 us a sweep, now 5.0, of which ~2.4 are the
+// launch).
+template <typename TO, typename TV, int R, int KS>
+__global__ void __launch_bounds__(64 * KS)
+    k_sweep_pp_split(int ny, int nrhs, const TO* __restrict__ M, const int64_t* __restrict__ pofs,
+                     const int32_t* __restrict__ port_off, const int32_t* __restrict__ port_twin,
+                     const TV* __restrict__ h, const TV* __restrict__ a_cur, TV* __restrict__ a_next, int max_q) {
+    constexpr int G = Group<TO>::G, CH = 4;  // column groups per chunk, loaded together
+    extern __shared__ char smem[];
+    TV* av = reinterpret_cast<TV*>(smem);  // [max_q][R]
+    TV* part = av + max_q * R;             // [KS][64][R]
+    const int s = R == 1 ? int(blockIdx.x) : int(blockIdx.x) / ny;
+    const int r0 = R == 1 ? 0 : (int(blockIdx.x) - s * ny) * R;
+    const int w = R == 1 ? 1 : min(R, nrhs - r0);
+    const int p0 = port_off[s], q = port_off[s + 1] - p0;
+    const int row0 = int(blockIdx.y) * 64;
+    if (row0 >= q) return;  // uniform over the workgroup
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int row = row0 + lane, rowc = min(row, q - 1);
+    const TO* Ms = M + pofs[s];
+    const int ng = q / G, full = ng * G;
+    // this wavefront's first chunk is in flight while the waves are staged
+    TO v[CH][G];
+    auto load = [&](int g0) {
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            if (g0 + i < ng) {  // wave-uniform
+                load16p<TO>(Ms + (int64_t(g0 + i) * q + rowc) * G, v[i]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < G; ++j) v[i][j] = TO(0);
+            }
+        }
+    };
+    load(wave * CH);
+    for (int t = tid; t < q * R; t += 64 * KS)
+        av[t] = t % R < w ? a_cur[int64_t(p0 + t / R) * nrhs + r0 + t % R] : TV(0);
+    __syncthreads();
+    TV acc[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) acc[k] = TV(0);
+    for (int g0 = wave * CH; g0 < ng; g0 += KS * CH) {
+        TO u[CH][G];
+#pragma unroll
+        for (int i = 0; i < CH; ++i)
+#pragma unroll
+            for (int j = 0; j < G; ++j) u[i][j] = v[i][j];
+        load(g0 + KS * CH);
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int g = min(g0 + i, ng - 1);  // past the end: zeros times a staged wave
+#pragma unroll
+            for (int j = 0; j < G; ++j)
+#pragma unroll
+                for (int k = 0; k < R; ++k)
+                    acc[k] += g0 + i < ng ? TV(u[i][j]) * av[(g * G + j) * R + k] : TV(0);
+        }
+    }
+    if (wave == KS - 1)
+        for (int c = full; c < q; ++c) {
+            const TV m = TV(Ms[int64_t(full) * q + int64_t(c - full) * q + rowc]);
+#pragma unroll
+            for (int k = 0; k < R; ++k) acc[k] += m * av[c * R + k];
+        }
+#pragma unroll
+    for (int k = 0; k < R; ++k) part[(wave * 64 + lane) * R + k] = acc[k];
+    __syncthreads();
+    for (int t = tid; t < 64 * R; t += 64 * KS) {
+        const int i = t / R, k = t % R;
+        if (row0 + i >= q || k >= w) continue;
+        TV z = TV(0);
+#pragma unroll
+        for (int v2 = 0; v2 < KS; ++v2) z += part[v2 * 64 * R + t];
+        const int p = p0 + row0 + i;
+        a_next[int64_t(port_twin[p]) * nrhs + r0 + k] = h[int64_t(p) * nrhs + r0 + k] + z;
     }
 }
 
@@ -321,24 +417,50 @@ template hipError_t launch_wave_coupled<double>(int, int, Coupling<double>, cons
 template hipError_t launch_wave_coupled<float>(int, int, Coupling<float>, const int32_t*, const float*,
                                                const int32_t*, const float*, const float*, float*, hipStream_t);
 
-template <typename TO, typename TV>
-hipError_t launch_sweep_pp(int S, int max_q, const TO* M, const int64_t* pofs, const int32_t* port_off,
-                           const int32_t* port_twin, const TV* h, const TV* a_cur, TV* a_next, hipStream_t st) {
-    const size_t lds = size_t(max_q > 0 ? max_q : 1) * sizeof(TV);
-    if (lds > 65536) return hipErrorInvalidValue;
-    if (max_q <= 32)
-        hipLaunchKernelGGL((k_sweep_pp<TO, TV, 2>), dim3(S), dim3(64), lds, st, M, pofs, port_off, port_twin, h,
-                           a_cur, a_next, max_q);
-    else {
-        // few sub-circuits with many ports: one-wavefront blocks, each sub-circuit's rows
-        // spread over several
-        const bool split = S < 1024 && max_q > 64;
-        const int bs = split || max_q <= 64 ? 64 : 256;
-        const int ry = split ? (max_q + bs - 1) / bs : 1;
-        hipLaunchKernelGGL((k_sweep_pp<TO, TV, 1>), dim3(S, ry), dim3(bs), lds, st, M, pofs, port_off, port_twin,
-                           h, a_cur, a_next, max_q);
+template <typename TO, typename TV, int R>
+hipError_t launch_pp_r(int S, int max_q, int nrhs, const TO* M, const int64_t* pofs, const int32_t* port_off,
+                       const int32_t* port_twin, const TV* h, const TV* a_cur, TV* a_next, hipStream_t st) {
+    const int ny = (nrhs + R - 1) / R;
+    const unsigned nb = unsigned(S) * unsigned(ny);
+    const size_t lds = size_t(max_q > 0 ? max_q : 1) * R * sizeof(TV);
+    if constexpr (R == 1)
+        if (max_q <= 32) {
+            hipLaunchKernelGGL((k_sweep_pp<TO, TV, 2, 1>), dim3(nb), dim3(64), lds, st, ny, nrhs, M, pofs, port_off,
+                               port_twin, h, a_cur, a_next);
+            return hipGetLastError();
+        }
+    // few sub-circuits with many ports: the rows of each spread over several workgroups
+    // and its columns over their wavefronts
+    if (S < 1024 && max_q > 64) {
+        constexpr int KS = 8;
+        const size_t lds2 = lds + size_t(KS) * 64 * R * sizeof(TV);
+        if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(&k_sweep_pp_split<TO, TV, R, KS>), lds2);
+            e != hipSuccess)
+            return e;
+        hipLaunchKernelGGL((k_sweep_pp_split<TO, TV, R, KS>), dim3(nb, unsigned((max_q + 63) / 64)), dim3(64 * KS),
+                           lds2, st, ny, nrhs, M, pofs, port_off, port_twin, h, a_cur, a_next, max_q);
+        return hipGetLastError();
     }
+    hipLaunchKernelGGL((k_sweep_pp<TO, TV, 1, R>), dim3(nb), dim3(max_q <= 64 ? 64 : 256), lds, st, ny, nrhs, M, pofs,
+                       port_off, port_twin, h, a_cur, a_next);
     return hipGetLastError();
+}
+
+template <typename TO, typename TV>
+hipError_t launch_sweep_pp(int S, int max_q, int nrhs, const TO* M, const int64_t* pofs, const int32_t* port_off,
+                           const int32_t* port_twin, const TV* h, const TV* a_cur, TV* a_next, hipStream_t st) {
+    if (S == 0) return hipSuccess;
+    // the waves of a block of right-hand sides in 64 KiB of LDS
+    auto fits = [&](int r) { return size_t(max_q > 0 ? max_q : 1) * r * sizeof(TV) <= 65536; };
+    if (!fits(1)) return hipErrorInvalidValue;
+    if (nrhs == 1 || !fits(2))
+        return nrhs == 1 ? launch_pp_r<TO, TV, 1>(S, max_q, nrhs, M, pofs, port_off, port_twin, h, a_cur, a_next, st)
+                         : hipErrorInvalidValue;
+    if (nrhs == 2 || !fits(4))
+        return launch_pp_r<TO, TV, 2>(S, max_q, nrhs, M, pofs, port_off, port_twin, h, a_cur, a_next, st);
+    if (nrhs <= 4 || !fits(8))
+        return launch_pp_r<TO, TV, 4>(S, max_q, nrhs, M, pofs, port_off, port_twin, h, a_cur, a_next, st);
+    return launch_pp_r<TO, TV, 8>(S, max_q, nrhs, M, pofs, port_off, port_twin, h, a_cur, a_next, st);
 }
 
 template hipError_t launch_port_matrix<double>(int, const int32_t*, const int64_t*, const int32_t*, const int32_t*,
@@ -351,10 +473,10 @@ template hipError_t launch_port_h<double>(int, int, const int32_t*, const int32_
                                           const double*, double*, hipStream_t, Coupling<double>);
 template hipError_t launch_port_h<float>(int, int, const int32_t*, const int32_t*, const int32_t*, const float*,
                                          const float*, float*, hipStream_t, Coupling<float>);
-template hipError_t launch_sweep_pp<double, double>(int, int, const double*, const int64_t*, const int32_t*,
+template hipError_t launch_sweep_pp<double, double>(int, int, int, const double*, const int64_t*, const int32_t*,
                                                     const int32_t*, const double*, const double*, double*,
                                                     hipStream_t);
-template hipError_t launch_sweep_pp<float, float>(int, int, const float*, const int64_t*, const int32_t*,
+template hipError_t launch_sweep_pp<float, float>(int, int, int, const float*, const int64_t*, const int32_t*,
                                                   const int32_t*, const float*, const float*, float*, hipStream_t);
 
 }  // namespace vtm
@@ -676,5 +798,250 @@ template hipError_t launch_sweep_pps<float, float>(int, int, int, const float*, 
                                                    const int32_t*, const int32_t*, const int32_t*, const float*,
                                                    const float*, float, const float*, const float*, float*, int,
                                                    hipStream_t);
+
+}  // namespace vtm
+
+// ---------------------------------------------------------------------------
+// Several right-hand sides: the port-node form on the matrix cores.
+// ---------------------------------------------------------------------------
+namespace vtm {
+namespace {
+
+typedef double ppt_d4 __attribute__((ext_vector_type(4)));
+typedef float ppt_f4 __attribute__((ext_vector_type(4)));
+
+template <typename T>
+struct NodeMma;
+template <>
+struct NodeMma<double> {
+    using Frag = double2;
+    using Acc = ppt_d4;
+    static __device__ Acc step(const Frag& a, int j, double b, Acc acc) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(j ? a.y : a.x, b, acc, 0, 0, 0);
+    }
+    static __device__ int out_row(int l, int v) { return (l >> 4) + 4 * v; }
+};
+template <>
+struct NodeMma<float> {
+    using Frag = float4;
+    using Acc = ppt_f4;
+    static __device__ Acc step(const Frag& a, int j, float b, Acc acc) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(j == 0 ? a.x : j == 1 ? a.y : j == 2 ? a.z : a.w, b, acc, 0, 0, 0);
+    }
+    static __device__ int out_row(int l, int v) { return 4 * (l >> 4) + v; }
+};
+
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_port_node_tiles(const int32_t* __restrict__ sub_off, const int64_t* __restrict__ kofs,
+                      const int32_t* __restrict__ pn_off, const int32_t* __restrict__ pn_node, const T* __restrict__ K,
+                      const int64_t* __restrict__ ntofs, T* __restrict__ Nt, int transpose) {
+    const int s = blockIdx.x;
+    const int ns = sub_off[s + 1] - sub_off[s];
+    const int k0 = pn_off[s], k = pn_off[s + 1] - k0;
+    const int np = node_tile_pad(k);
+    const T* Ks = K + kofs[s];
+    T* out = Nt + ntofs[s];
+    const int64_t cnt = int64_t(np) * np;
+    for (int64_t d = threadIdx.x; d < cnt; d += blockDim.x) {
+        int r, c;
+        node_tile_rc<T>(np, d, r, c);
+        T v = T(0);
+        if (r < k && c < k) {
+            const int i = pn_node[k0 + (transpose ? c : r)], j = pn_node[k0 + (transpose ? r : c)];
+            v = Ks[inv_offset<T>(ns, i, j)];
+        }
+        out[d] = v;
+    }
+}
+
+// A tiles in flight per wavefront
+constexpr int kPptAhead = 4;
+
+// One workgroup per sub-circuit and block of w <= 16 right-hand sides.  NI > 0: a
+// thread keeps its (at most NI) items -- a port and a right-hand side -- in
+// registers from its first loads to its stores; 0: it reads them again.  All loads
+// that depend on nothing but the sub-circuit's offsets are issued first: the
+// waves, coefficients, h and twins of the thread's (port, right-hand side) items,
+// and the wavefront's first A tiles.  c a goes to LDS per port, is summed per port
+// node in port order into T (the B operand, [node][w]); each wavefront then forms
+// row tiles of Z, which replaces c a in LDS, and every item's thread its wave.
+// The matrix cores take 16 columns at a time; lanes of columns past w read column
+// w - 1 again and their results are dropped.  They are used for few columns too
+// because a vector form reads a staged value from LDS per multiply-add, and that
+// alone would take as long.  Bound by latency at the measured sizes (offsets, waves,
+// three barriers; 5 wavefronts per SIMD): 3,276 sub-circuits of 8x8, six right-hand
+// sides, FP64: 10.9 us a sweep, the full inverses it replaces 29.1; 768 of 16x16,
+// four, FP32: 5.9 against 35.  Held to 64 registers for 8 wavefronts per SIMD it
+// spills (19.8 us).
+template <typename T, int NI>
+__global__ void __launch_bounds__(512)
+    k_sweep_ppt(int ny, int rc, int nrhs, const T* __restrict__ Nt, const int64_t* __restrict__ ntofs,
+                const int32_t* __restrict__ pn_off, const int32_t* __restrict__ pn_pfirst,
+                const int32_t* __restrict__ port_off, const int32_t* __restrict__ port_twin, const T* __restrict__ pc,
+                const T* __restrict__ pbeta, const T* __restrict__ pgamma, const T* __restrict__ h,
+                const T* __restrict__ a_cur, T* __restrict__ a_next, int max_np, int max_rows, int reverse) {
+    using M = NodeMma<T>;
+    constexpr int KT = 64 / int(sizeof(T)), E = KT / 4;
+    extern __shared__ char smem[];
+    const int u = reverse ? xcd_block_reversed(blockIdx.x, gridDim.x) : xcd_block(blockIdx.x, gridDim.x);
+    const int s = u / ny, r0 = (u - s * ny) * rc;
+    const int w = min(rc, nrhs - r0);
+    T* tv = reinterpret_cast<T*>(smem);            // [max_np][rc]
+    T* ca = tv + max_np * rc;                      // [max_rows][rc]: c a per port, then Z per port node
+    int32_t* pnode = reinterpret_cast<int32_t*>(ca + max_rows * rc);  // [q] (pf after it)
+    const int p0 = port_off[s], q = port_off[s + 1] - p0;
+    const int k0 = pn_off[s], k = pn_off[s + 1] - k0;
+    int32_t* pf = pnode + q;                       // [k + 1]
+    const int np = node_tile_pad(k), kt_n = np / KT, mt_n = np / 16;
+    const int tid = threadIdx.x, bs = blockDim.x, lane = tid & 63, wave = tid >> 6, waves = bs >> 6;
+    const typename M::Frag* A0 = reinterpret_cast<const typename M::Frag*>(Nt + ntofs[s]) + lane;
+    typename M::Frag af[kPptAhead];
+#pragma unroll
+    for (int d = 0; d < kPptAhead; ++d)
+        if (wave < mt_n && d < kt_n) af[d] = A0[(int64_t(wave) * kt_n + d) * 64];
+    const int items = q * w;
+    constexpr int NR = NI > 0 ? NI : 1;
+    T va[NR], vh[NR], vb[NR], vg[NR];
+    int tw[NR];
+    if constexpr (NI > 0) {
+        T vc[NR];
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const int t = tid + i * bs;
+            va[i] = vh[i] = vb[i] = vg[i] = vc[i] = T(0);
+            tw[i] = 0;
+            if (t < items) {
+                const int p = p0 + t / w;
+                const int64_t o = int64_t(p) * nrhs + r0 + t % w;
+                va[i] = a_cur[o];
+                vc[i] = pc[p];
+                vh[i] = h[o];
+                vb[i] = pbeta[p];
+                vg[i] = pgamma[p];
+                tw[i] = port_twin[p];
+            }
+        }
+        for (int j = tid; j <= k; j += bs) pf[j] = pn_pfirst[k0 + j] - p0;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const int t = tid + i * bs;
+            if (t < items) ca[t] = vc[i] * va[i];
+        }
+    } else {
+        for (int j = tid; j <= k; j += bs) pf[j] = pn_pfirst[k0 + j] - p0;
+        for (int t = tid; t < items; t += bs) {
+            const int p = p0 + t / w;
+            ca[t] = pc[p] * a_cur[int64_t(p) * nrhs + r0 + t % w];
+        }
+    }
+    __syncthreads();
+    for (int t = tid; t < np * w; t += bs) {
+        const int j = t / w, r = t - j * w;
+        T acc = T(0);
+        if (j < k) {
+            const int f1 = pf[j + 1];
+            for (int p = pf[j]; p < f1; ++p) {
+                acc += ca[p * w + r];
+                if (r == 0) pnode[p] = j;
+            }
+        }
+        tv[t] = acc;
+    }
+    __syncthreads();
+    const int nc = min(lane & 15, w - 1);
+    for (int mt = wave; mt < mt_n; mt += waves) {
+        typename M::Acc acc;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[v] = T(0);
+        const int64_t row = int64_t(mt) * kt_n;
+        if (mt != wave) {
+#pragma unroll
+            for (int d = 0; d < kPptAhead; ++d)
+                if (d < kt_n) af[d] = A0[(row + d) * 64];
+        }
+        for (int kt = 0; kt < kt_n; kt += kPptAhead) {
+#pragma unroll
+            for (int d = 0; d < kPptAhead; ++d) {
+                if (kt + d < kt_n) {
+                    const typename M::Frag a = af[d];
+                    if (kt + d + kPptAhead < kt_n) af[d] = A0[(row + kt + d + kPptAhead) * 64];
+#pragma unroll
+                    for (int j = 0; j < E; ++j) {
+                        const T b = tv[((kt + d) * KT + 4 * j + (lane >> 4)) * w + nc];
+                        acc = M::step(a, j, b, acc);
+                    }
+                }
+            }
+        }
+        if ((lane & 15) < w) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) ca[(mt * 16 + M::out_row(lane, v)) * w + nc] = acc[v];
+        }
+    }
+    __syncthreads();
+    if constexpr (NI > 0) {
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const int t = tid + i * bs;
+            if (t < items) {
+                const int p = t / w, r = t - p * w;
+                a_next[int64_t(tw[i]) * nrhs + r0 + r] = vb[i] * ca[pnode[p] * w + r] + vg[i] * va[i] + vh[i];
+            }
+        }
+    } else {
+        for (int t = tid; t < items; t += bs) {
+            const int p = t / w, r = t - p * w;
+            const int64_t o = int64_t(p0 + p) * nrhs + r0 + r;
+            a_next[int64_t(port_twin[p0 + p]) * nrhs + r0 + r] =
+                pbeta[p0 + p] * ca[pnode[p] * w + r] + pgamma[p0 + p] * a_cur[o] + h[o];
+        }
+    }
+}
+
+}  // namespace
+
+template <typename T>
+hipError_t launch_port_node_tiles(int S, const int32_t* sub_off, const int64_t* kofs, const int32_t* pn_off,
+                                  const int32_t* pn_node, const T* K, const int64_t* ntofs, T* Nt, bool transpose,
+                                  hipStream_t st) {
+    hipLaunchKernelGGL(k_port_node_tiles<T>, dim3(S), dim3(256), 0, st, sub_off, kofs, pn_off, pn_node, K, ntofs, Nt,
+                       transpose ? 1 : 0);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_sweep_ppt(int S, int max_npn, int max_ports, int nrhs, size_t lds_limit, const T* Nt,
+                            const int64_t* ntofs, const int32_t* pn_off, const int32_t* pn_pfirst,
+                            const int32_t* port_off, const int32_t* port_twin, const T* pc, const T* pbeta,
+                            const T* pgamma, const T* h, const T* a_cur, T* a_next, int reverse, hipStream_t st) {
+    if (S == 0) return hipSuccess;
+    const int np = node_tile_pad(max_npn), rows = std::max(np, max_ports);
+    // at most 16 right-hand sides a workgroup (an MFMA's columns), fewer where their
+    // staging would leave a CU less than two workgroups
+    int rc = std::min(16, nrhs);
+    while (rc > 1 && ppt_lds_bytes<T>(np, max_ports, rc) > std::min<size_t>(lds_limit, 80 * 1024)) rc = (rc + 1) / 2;
+    const size_t lds = ppt_lds_bytes<T>(np, max_ports, rc);
+    if (lds > lds_limit) return hipErrorInvalidValue;
+    const int ny = (nrhs + rc - 1) / rc;
+    // a wavefront per row tile, up to 8
+    const int bs = 64 * std::min(8, std::max(1, np / 16));
+    const int64_t items = int64_t(max_ports) * rc;
+    auto kern = items <= 2 * bs ? k_sweep_ppt<T, 2> : items <= 4 * bs ? k_sweep_ppt<T, 4> : k_sweep_ppt<T, 0>;
+    if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds); e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(unsigned(S) * unsigned(ny)), dim3(bs), lds, st, ny, rc, nrhs, Nt, ntofs, pn_off,
+                       pn_pfirst, port_off, port_twin, pc, pbeta, pgamma, h, a_cur, a_next, np, rows, reverse);
+    return hipGetLastError();
+}
+
+#define VTM_PPT(T)                                                                                                   \
+    template hipError_t launch_port_node_tiles<T>(int, const int32_t*, const int64_t*, const int32_t*,              \
+                                                  const int32_t*, const T*, const int64_t*, T*, bool, hipStream_t); \
+    template hipError_t launch_sweep_ppt<T>(int, int, int, int, size_t, const T*, const int64_t*, const int32_t*,   \
+                                            const int32_t*, const int32_t*, const int32_t*, const T*, const T*,     \
+                                            const T*, const T*, const T*, T*, int, hipStream_t);
+VTM_PPT(double)
+VTM_PPT(float)
+#undef VTM_PPT
 
 }  // namespace vtm

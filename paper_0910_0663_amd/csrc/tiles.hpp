@@ -86,4 +86,28 @@ __host__ __device__ inline void tile_rc(int np, int64_t d, int& r, int& c) {
         c = kt * 8 + 4 * j + q;
 }
 
+// Port-node operators of the several-right-hand-side sweep (FP64 and FP32): k x k
+// entries zero-padded to np = roundup(k, 16), cut into tiles of 16 rows by
+// K = 64 / sizeof(T) columns, lane-major with 16 bytes per lane, E = K / 4 entries:
+// lane l holds A[16 mt + l % 16][K kt + 4 j + l / 16], j < E, the A operands of E
+// steps of a 16 x 16 x 4 MFMA.  Tile (mt, kt) starts at (mt (np / K) + kt) 64 E.
+__host__ __device__ inline int node_tile_pad(int k) { return (k + 15) & ~15; }
+
+template <typename T>
+__host__ __device__ inline void node_tile_rc(int np, int64_t d, int& r, int& c) {
+    constexpr int K = 64 / int(sizeof(T)), E = K / 4;
+    const int j = int(d % E), lane = int((d / E) % 64);
+    const int64_t tile = d / (64 * E);
+    const int kt_n = np / K;
+    r = int(tile / kt_n) * 16 + lane % 16;
+    c = int(tile % kt_n) * K + 4 * j + lane / 16;
+}
+
+// LDS bytes of that sweep with rc right-hand sides per workgroup: T (np rows), the
+// staged c a (q rows, then Z), each port's node and each node's first port
+template <typename T>
+__host__ __device__ inline size_t ppt_lds_bytes(int np, int q, int rc) {
+    return size_t(np + (q > np ? q : np)) * rc * sizeof(T) + size_t(q + np + 1) * 4;
+}
+
 }  // namespace vtm
