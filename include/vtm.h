@@ -83,7 +83,9 @@ typedef struct {
     int32_t use_graph;      /* 1: each check interval (its sweeps, the FP64 residual
                                and the copy of its sums to the host) is captured once
                                per shape and replayed as one hipGraph launch; check
-                               intervals are then check_every times a power of two */
+                               intervals are then check_every times a power of two.
+                               A solve that runs resident (below, vtm_solve) is one
+                               launch and captures nothing, on the same intervals */
     int32_t timing;         /* 1: HIP events around every sweep launch (report);
                                2: events around full sweeps and around each run of
                                consecutive port-to-port sweeps (their average then
@@ -308,6 +310,12 @@ vtm_status vtm_vertex_sca(const vtm_csr *A, const int32_t *label, const int32_t 
  *   nrhs    1 .. opt.nrhs_max.
  *   tol     > 0.
  *   rep     optional report.
+ *
+ * One right-hand side on a small circuit torn at branches runs resident: when
+ * every sub-circuit has at most 128 ports (FP32: 64, symmetric A) and the device
+ * holds all of them at once, the port-to-port sweeps and checks of a solve (of an
+ * inner solve when refining) are one cooperative launch.  Same sweeps, checks and
+ * residual history.  opt.timing runs a launch per sweep.
  *
  * A zero column converges at once with x = 0.  With a refining precision the
  * sweeps run in FP32/BF16 on A d = r and x += d, r = b - A x in FP64, until

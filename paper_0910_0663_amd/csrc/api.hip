@@ -17,6 +17,7 @@
 
 #include "kernels.hpp"
 #include "plan.hpp"
+#include "resident.hpp"
 #include "status.hpp"
 #include "vtm.h"
 
@@ -212,12 +213,21 @@ struct vtm_handle_s {
     size_t ev_used = 0;
     // captured check intervals (opt.use_graph), keyed by everything their launches depend on
     std::map<std::array<int, 6>, hipGraphExec_t> graphs;
+    // resident runs (one right-hand side, all sweeps and checks in one launch): the
+    // exchange words, the words' latest tag, and the run's outcome in pinned memory
+    bool resident = false;
+    DevBuf<double> res_slots, res_sums;
+    uint32_t res_epoch = 0;
+    vtm::ResidentState* res_state = nullptr;
+    vtm::ResidentState* res_state_dev = nullptr;
+    uint64_t res_wait_ticks = 400000000;  // 4 s
     bool capturing = false;               // no per-sweep timing events inside a capture
     hipStream_t gstream = nullptr;        // private non-blocking stream the graphs run on
     hipEvent_t gready = nullptr;          // orders it after the caller's stream
 
     ~vtm_handle_s() {
         if (h_norms) (void)hipHostFree(h_norms);
+        if (res_state) (void)hipHostFree(res_state);
         for (hipEvent_t e : ev) (void)hipEventDestroy(e);
         for (auto& kv : graphs) (void)hipGraphExecDestroy(kv.second);
         if (gready) (void)hipEventDestroy(gready);
@@ -733,55 +743,93 @@ vtm_status run_chunk(vtm_handle h, bool low, int nrhs, bool adjoint, int64_t chu
 }
 
 
-// Where the next residual check goes.  With adaptive checks, once two checks
-// show the residual falling, the per-sweep rate predicts the sweeps left to the
-// target; the next check comes after half of them (a multiple of m, at most
-// 64 m), so checks thin out far from the target and return to every m sweeps
-// near it.
-struct Cadence {
-    int64_t m = 1;
-    bool adaptive = false;
-    double reach = 0.5;     // fraction of the predicted sweeps to the target before the next check
-    int64_t cap = 64;       // at most this many m between checks
-    int64_t s_prev = -1, s_last = -1;
-    double r_prev = 0.0, r_last = 0.0;
-    void record(int64_t s, double r) {
-        s_prev = s_last;
-        r_prev = r_last;
-        s_last = s;
-        r_last = r;
-    }
-    int64_t next(double target) const {
-        if (!adaptive || s_prev < 0 || !(r_last < r_prev) || !(r_last > 0.0) || !(target > 0.0) ||
-            !(r_last > target))
-            return m;
-        const double rate = std::log(r_last / r_prev) / double(s_last - s_prev);  // < 0
-        const double left = std::log(target / r_last) / rate;                       // > 0
-        const int64_t k = int64_t(reach * left / double(m)) * m;
-        return std::min<int64_t>(std::max<int64_t>(k, m), cap * m);
-    }
-};
-
 double max_of(const std::vector<double>& v) {
     double mx = 0.0;
     for (double x : v) mx = std::isnan(x) ? x : std::max(mx, x);
     return mx;
 }
 
-// With graphs, check intervals are m times a power of two (a few graphs cover them all).
+// Whether a run of port-to-port sweeps whose checks come from port quantities can
+// be resident: with graphs too (such a run is one launch already; its intervals are
+// then those of graphs), but not with timing events, which time launches of a sweep.
+bool can_reside(vtm_handle h, int nrhs, bool iface) {
+    return h->resident && nrhs == 1 && iface && h->opt.timing == 0 &&
+           h->opt.check_every <= vtm::kResidentEvery;
+}
+
+// One resident run from the waves in buffer cur.  Returns with the outcome in
+// h->res_state and cur moved on; `lost` set (and the handle back to a launch per
+// sweep) when a wait ran out or the launch was refused: the waves are then gone.
+template <typename T>
+vtm_status run_resident(vtm_handle h, const vtm::ResidentControl& ctl, bool adjoint, int& cur, bool& lost) {
+    const vtm::Plan& P = h->plan;
+    const bool kt = adjoint && !P.symmetric;
+    const int64_t words = int64_t(vtm::resident_slot_words<T>(P.nports));
+    // a launch uses at most kResidentSweeps + 64 check_every tags
+    if (h->res_epoch > UINT32_MAX - (1u << 28)) {
+        VTM_HIP(vtm::launch_fill<double>(words, 0.0, h->res_slots.p, h->stream));
+        VTM_HIP(vtm::launch_fill<double>(int64_t(h->res_sums.count), 0.0, h->res_sums.p, h->stream));
+        h->res_epoch = 0;
+    }
+    vtm::ResidentArgs<T> a{};
+    a.ctl = ctl;
+    a.S = int(P.S);
+    a.nports = P.nports;
+    a.packed = h->pps ? 1 : 0;
+    a.W = T(P.nwires ? P.wW[0] : 0.0);
+    if constexpr (std::is_same_v<T, double>) {
+        a.op = h->pps ? h->S64.p : kt ? h->N64T.p : h->N64.p;
+        a.w = h->W64p.p;
+        a.c = h->c64.p, a.beta = h->beta64.p, a.gamma = h->gamma64.p, a.h = h->h64.p;
+        a.a[0] = h->a64[0].p, a.a[1] = h->a64[1].p;
+    } else {
+        a.op = h->pps ? h->S32.p : kt ? h->N32T.p : h->N32.p;
+        a.w = h->W32p.p;
+        a.c = h->c32.p, a.beta = h->beta32.p, a.gamma = h->gamma32.p, a.h = h->h32.p;
+        a.a[0] = h->a32[0].p, a.a[1] = h->a32[1].p;
+    }
+    a.ofs = h->pps ? h->sofs.p : h->nofs.p;
+    a.pn_off = h->pn_off.p, a.pn_pfirst = h->pn_pfirst.p, a.port_off = h->port_off.p, a.port_twin = h->port_twin.p;
+    a.c64 = h->c64.p, a.beta64 = h->beta64.p, a.gamma64 = h->gamma64.p, a.gd = h->pgd64.p, a.g = h->pg64.p;
+    a.cur = cur;
+    a.slots = reinterpret_cast<unsigned long long*>(h->res_slots.p);
+    a.sums = reinterpret_cast<unsigned long long*>(h->res_sums.p);
+    a.epoch = h->res_epoch;
+    a.wait_ticks = h->res_wait_ticks;
+    a.state = h->res_state_dev;
+    h->res_state->stop = vtm::kAborted;
+    h->res_state->timeout = 0;
+    lost = false;
+    const hipError_t e = vtm::launch_resident<T>(a, P.max_ports, h->stream);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        h->resident = false;
+        lost = true;
+        return VTM_OK;
+    }
+    VTM_HIP(hipStreamSynchronize(h->stream));
+    const vtm::ResidentState& r = *h->res_state;
+    if (r.stop == vtm::kAborted || r.timeout) {
+        h->resident = false;
+        lost = true;
+        return VTM_OK;
+    }
+    const int64_t ran = r.ctl.sweeps - ctl.sweeps;
+    h->res_epoch += uint32_t(ran);
+    cur ^= int(ran & 1);
+    return VTM_OK;
+}
+
+// The next check interval: k sweeps, or with graphs m times a power of two.
 int64_t graph_length(vtm_handle h, int64_t k) {
-    if (!h->opt.use_graph) return k;
-    const int64_t m = h->opt.check_every;
-    int64_t len = m;
-    while (2 * len <= k) len *= 2;
-    return len;
+    return h->opt.use_graph ? vtm::graph_length(h->opt.check_every, k) : k;
 }
 
 // Plain FP64 VTM on (bp -> xp).  Waves start at zero unless resume is set.
 vtm_status run_fp64(vtm_handle h, int nrhs, double tol, bool adjoint, bool resume, IterOut& out) {
     const vtm::Plan& P = h->plan;
     const int64_t np = P.nports * nrhs;
-    Cadence cad;
+    vtm::Cadence cad;
     cad.m = h->opt.check_every;
     cad.adaptive = h->opt.adaptive_checks != 0;
     int cur = 0;
@@ -816,13 +864,47 @@ vtm_status run_fp64(vtm_handle h, int nrhs, double tol, bool adjoint, bool resum
     };
     while (true) {
         const int64_t chunk = std::min<int64_t>(graph_length(h, cad.next(tol)), h->opt.max_sweeps - out.sweeps);
-        st = run_chunk(h, false, nrhs, adjoint, chunk, cur, out.rel, pp, out.sweeps == 0, iface, &bb);
-        if (st != VTM_OK) return st;
-        cur ^= int(chunk & 1);
-        out.sweeps += chunk;
-        ++out.checks;
-        out.record();
-        if ((st = timing_collect(h, out)) != VTM_OK) return st;
+        bool more = false;  // a resident run that ended only to report
+        if (can_reside(h, nrhs, iface) && (out.sweeps > 0 || chunk > 1)) {
+            vtm::ResidentControl ctl;
+            ctl.cad = cad;
+            ctl.tol = tol;
+            ctl.divergence = h->opt.divergence;
+            ctl.bb = bb[0];
+            ctl.max_sweeps = h->opt.max_sweeps;
+            ctl.sweeps = out.sweeps;
+            ctl.first = chunk;
+            ctl.pow2 = h->opt.use_graph ? 1 : 0;
+            if (out.sweeps == 0) {  // the first sweep, a full one, gives h
+                if ((st = sweep_once(h, false, 1, h->bp.p, h->xp.p, cur, adjoint, false, false, true)) != VTM_OK ||
+                    (st = port_h(h, false, 1)) != VTM_OK)
+                    return st;
+                cur ^= 1;
+                ctl.sweeps = 1;
+                ctl.first = chunk - 1;
+            }
+            bool lost = false;
+            if ((st = run_resident<double>(h, ctl, adjoint, cur, lost)) != VTM_OK) return st;
+            if (lost) return run_fp64(h, nrhs, tol, adjoint, resume, out = IterOut{});
+            const vtm::ResidentState& r = *h->res_state;
+            for (int k = 0; k < r.hist_len; ++k) {
+                out.rel[0] = r.hist[k];
+                out.sweeps = r.hist_sweeps[k];
+                out.record();
+            }
+            out.checks += r.checks;
+            cad = r.ctl.cad;
+            more = r.stop == vtm::kMore;
+        } else {
+            st = run_chunk(h, false, nrhs, adjoint, chunk, cur, out.rel, pp, out.sweeps == 0, iface, &bb);
+            if (st != VTM_OK) return st;
+            cur ^= int(chunk & 1);
+            out.sweeps += chunk;
+            ++out.checks;
+            out.record();
+            if ((st = timing_collect(h, out)) != VTM_OK) return st;
+        }
+        if (more) continue;
         bool bad = false;
         for (double v : out.rel)
             if (!std::isfinite(v) || v > h->opt.divergence) bad = true;
@@ -937,7 +1019,7 @@ vtm_status run_refine(vtm_handle h, int nrhs, double tol, bool adjoint, IterOut&
         std::vector<double> rr(nrhs);  // ||r||^2 per right-hand side, for the port-residual inner checks
         for (int r = 0; r < nrhs; ++r) rr[r] = h->h_norms[2 * r];
         VTM_HIP(vtm::launch_fill<float>(np, 0.0f, h->a32[0].p, h->stream));
-        Cadence cad;
+        vtm::Cadence cad;
         cad.m = h->opt.check_every;
         cad.adaptive = h->opt.adaptive_checks != 0;
         cad.reach = inner_reach(h, nrhs, ports_check);
@@ -949,7 +1031,50 @@ vtm_status run_refine(vtm_handle h, int nrhs, double tol, bool adjoint, IterOut&
         int64_t inner = 0;
         std::vector<double> best(nrhs, INFINITY);
         int since = 0;
-        while (true) {
+        bool ended = false;
+        while (can_reside(h, nrhs, iface)) {
+            const int64_t chunk =
+                std::min<int64_t>(graph_length(h, cad.next(goal)), h->opt.max_sweeps - inner);
+            if (inner == 0 && chunk < 2) break;
+            vtm::ResidentControl ctl;
+            ctl.cad = cad;
+            ctl.tol = target[0];
+            ctl.bb = rr[0];
+            ctl.max_sweeps = h->opt.max_sweeps;
+            ctl.sweeps = inner;
+            ctl.first = chunk;
+            ctl.inner = 1;
+            ctl.pow2 = h->opt.use_graph ? 1 : 0;
+            ctl.best = best[0];
+            ctl.since = since;
+            if (inner == 0) {  // the first sweep, a full one, gives h
+                if ((st = sweep_once(h, true, 1, h->b32.p, h->d32.p, cur, adjoint, false, false, true)) != VTM_OK ||
+                    (st = port_h(h, true, 1)) != VTM_OK)
+                    return st;
+                cur ^= 1;
+                ctl.sweeps = 1;
+                ctl.first = chunk - 1;
+            }
+            bool lost = false;
+            if ((st = run_resident<float>(h, ctl, adjoint, cur, lost)) != VTM_OK) return st;
+            if (lost) return run_refine(h, nrhs, tol, adjoint, out = IterOut{});
+            const vtm::ResidentState& r = *h->res_state;
+            inner = r.ctl.sweeps;
+            out.checks += r.checks;
+            cad = r.ctl.cad;
+            best[0] = r.ctl.best;
+            since = r.ctl.since;
+            if (r.stop == vtm::kBad) {
+                out.sweeps += inner;
+                out.status = VTM_E_DIVERGED;
+                return VTM_OK;
+            }
+            if (r.stop != vtm::kMore) {
+                ended = true;
+                break;
+            }
+        }
+        while (!ended) {
             // an inner solve may stall above its target (the low-precision inverse
             // bounds the reachable reduction), so its checks are at most 4 m apart
             const int64_t chunk =
@@ -1504,6 +1629,24 @@ static vtm_status setup_from_plan(std::unique_ptr<vtm_handle_s> h, vtm_handle* o
     }
 
     if ((st = build_values(h.get())) != VTM_OK) return st;
+    // resident runs: the port-node forms on cut branches, when every workgroup fits the
+    // device at once
+    if ((h->pps || h->ppn) && !P.vertex) {
+        const int blocks = fp64 ? vtm::resident_blocks<double>(int(P.S), P.max_ports, h->pps)
+                                : vtm::resident_blocks<float>(int(P.S), P.max_ports, h->pps);
+        if (blocks > 0) {
+            const size_t words =
+                fp64 ? vtm::resident_slot_words<double>(P.nports) : vtm::resident_slot_words<float>(P.nports);
+            VTM_HIP(h->res_slots.alloc(words));
+            VTM_HIP(h->res_sums.alloc(2 * size_t(blocks) + 2));
+            VTM_HIP(vtm::launch_fill<double>(int64_t(words), 0.0, h->res_slots.p, s));
+            VTM_HIP(vtm::launch_fill<double>(int64_t(h->res_sums.count), 0.0, h->res_sums.p, s));
+            VTM_HIP(hipHostMalloc(reinterpret_cast<void**>(&h->res_state), sizeof(vtm::ResidentState),
+                                  hipHostMallocMapped | hipHostMallocCoherent));
+            VTM_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&h->res_state_dev), h->res_state, 0));
+            h->resident = true;
+        }
+    }
     if (h->tiles) {
         const TuneKey key{h->device, o.precision, nr, o.batch_row_tiles, o.batch_rhs_block, P.S, P.n, P.nports,
                           P.mofs[P.S], P.qmofs[P.S], P.max_ns, P.max_ports};
@@ -1647,6 +1790,14 @@ vtm_status vtm_info(vtm_handle h, int64_t* n, int64_t* n_sub, int64_t* n_wires, 
         if (port_sweep_bytes) *port_sweep_bytes = pp_sweep_bytes(h, h->nrhs_max);
         return VTM_OK;
     });
+}
+
+// For tests, not part of the interface: bounds every wait of h's resident runs to
+// `ticks` of 10 ns (0: one try), to exercise the way back to a launch per sweep.
+// Returns whether h runs resident.
+int vtm_testing_wait_ticks(vtm_handle h, uint64_t ticks) {
+    h->res_wait_ticks = ticks;
+    return h->resident ? 1 : 0;
 }
 
 void vtm_destroy(vtm_handle h) {

@@ -77,6 +77,19 @@ __device__ inline int xcd_item_block(int b, int n_items, int m, bool reversed) {
     return ((reversed ? count - 1 - k : k) * 8 + x) * m + r;
 }
 
+// The outgoing wave of a port in the packed form, 2 W c z + (1 - 2 c) a + h (w2c = 2 W c),
+// rounded in one stated way wherever it is formed.
+template <typename T>
+__device__ inline T packed_wave_out(T w2c, T c, T z, T a, T h) {
+#pragma clang fp contract(off)
+    const T g = T(1) - T(2) * c;  // exact product
+    const T v = w2c * z;
+    if constexpr (sizeof(T) == 8)
+        return h + __builtin_fma(a, g, v);
+    else
+        return h + __builtin_fmaf(a, g, v);
+}
+
 // elements reserved for an n x n block (rounded up to a multiple of 4)
 __host__ __device__ inline int64_t inv_block_elems(int n) { return (int64_t(n) * n + 3) & ~int64_t(3); }
 

@@ -630,7 +630,7 @@ __device__ inline void pps_unit(int unit, int S, const TO* __restrict__ Sp, cons
     }
     if (r < k) zv[hb + r] = acc;
     __syncthreads();
-    if (has_port) a_next[tw] = TV(2) * w * c * zv[hb + pnode[hb + r]] + (TV(1) - TV(2) * c) * a + hp;
+    if (has_port) a_next[tw] = packed_wave_out<TV>(TV(2) * w * c, c, zv[hb + pnode[hb + r]], a, hp);
 }
 
 // One workgroup (one wavefront) per unit: a pair of sub-circuits when HALF.
@@ -744,7 +744,7 @@ __global__ void __launch_bounds__(64 * WV)
         TV z = TV(0);
 #pragma unroll
         for (int v = 0; v < WV; ++v) z += zp[v][n];
-        a_next[tw] = TV(2) * w * c * z + (TV(1) - TV(2) * c) * a + hp;
+        a_next[tw] = packed_wave_out<TV>(TV(2) * w * c, c, z, a, hp);
     }
 }
 

@@ -1,0 +1,587 @@
+// Resident port-to-port sweeps.
+//
+// A small circuit's sweep as a launch of its own costs 4-8 us, nearly all of it
+// the launch and the first round trips to memory, and each residual check another
+// 25-30 us of launches and host round trip.  Here one cooperative launch holds
+// every sub-circuit's port operator in registers and runs all the sweeps and
+// checks of a solve: workgroups exchange waves directly, each waiting only for the
+// ports of its own neighbours, so there is no grid-wide barrier between sweeps (the
+// iteration is the same: sweep k + 1 of a sub-circuit reads the waves sweep k of its
+// neighbours sent).  Bound by the exchange's latency; alone it takes 1.3 us a sweep up to
+// 400 workgroups, 1.6 at 1,024, 3.1 at 4,096 (there the polls' traffic).  Measured, solve
+// before and after: 64x64 in 16x16 blocks to 1e-10 (296 sweeps) 1.3-1.5 -> 0.51 ms;
+// 331x290 in random cuts (272 sweeps) 1.7 -> 0.69 ms; 768x640 in 8x8 blocks (7,680
+// sub-circuits, 832 sweeps) 6.9 -> 4.6 ms, 5.4 us a sweep.
+//
+// A circuit runs resident whenever it fits: at the largest that does, above, a sweep
+// still takes 5.4 us against 8.1 as a launch.
+//
+// Exchange.  A wave travels as 8-byte words, each 32 bits of data and the 32-bit
+// number of its sweep (FP64: two words), written and read as relaxed agent-scope
+// atomics: a reader that finds the number it waits for has the data, with no fence
+// and no separate flag.  Two words sets alternate.  A writer reaches a set again
+// only two sweeps later, after it has received the wave its twin sent between, and
+// the twin sent that after its workgroup had read the earlier set.
+//
+// Checks.  Every workgroup sends its sum of squares of the port residual the same
+// way; one more workgroup adds them in a fixed order, decides (the rules of the host
+// driver) and publishes the sweeps until the next check, or 0.
+//
+// Every wait is bounded: one that runs out raises the abort word, which all waits
+// look at, the kernel ends, and the host runs the solve with a launch per sweep.
+#include "resident.hpp"
+
+#include "kernels.hpp"
+#include "layout.hpp"
+
+#include <algorithm>
+
+namespace vtm {
+
+namespace {
+
+typedef unsigned long long u64;
+
+__device__ inline u64 word_load(const u64* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void word_store(u64* p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+__device__ inline void send(u64* slot, double v, unsigned tag) {
+    const u64 b = u64(__double_as_longlong(v)), t = u64(tag) << 32;
+    word_store(slot, (b & 0xffffffffull) | t);
+    word_store(slot + 1, (b >> 32) | t);
+}
+__device__ inline void send(u64* slot, float v, unsigned tag) {
+    word_store(slot, u64(__float_as_uint(v)) | (u64(tag) << 32));
+}
+__device__ inline bool receive(const u64* slot, unsigned tag, double& v) {
+    const u64 lo = word_load(slot), hi = word_load(slot + 1);
+    if (unsigned(lo >> 32) != tag || unsigned(hi >> 32) != tag) return false;
+    v = __longlong_as_double((long long)((lo & 0xffffffffull) | (hi << 32)));
+    return true;
+}
+__device__ inline bool receive(const u64* slot, unsigned tag, float& v) {
+    const u64 w = word_load(slot);
+    if (unsigned(w >> 32) != tag) return false;
+    v = __uint_as_float(unsigned(w));
+    return true;
+}
+
+// The waves' words through buffer instructions: an FP64 wave's two words are one
+// 16-byte access (each word carries its own tag, so only 8-byte halves need to be
+// whole), which halves the requests of a poll.  Agent scope (sc1), as an atomic's;
+// the empty asm before a load keeps the compiler from reusing an earlier one.
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+constexpr int kAgent = 16;
+__device__ inline void send(__amdgpu_buffer_rsrc_t r, unsigned slot, double v, unsigned tag) {
+    const u64 b = u64(__double_as_longlong(v));
+    const u32x4 w = {unsigned(b), tag, unsigned(b >> 32), tag};
+    __builtin_amdgcn_raw_buffer_store_b128(w, r, int(slot * 16u), 0, kAgent);
+}
+__device__ inline void send(__amdgpu_buffer_rsrc_t r, unsigned slot, float v, unsigned tag) {
+    const u32x2 w = {__float_as_uint(v), tag};
+    __builtin_amdgcn_raw_buffer_store_b64(w, r, int(slot * 8u), 0, kAgent);
+}
+__device__ inline bool receive(__amdgpu_buffer_rsrc_t r, unsigned slot, unsigned tag, double& v) {
+    asm volatile("" ::: "memory");
+    const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(r, int(slot * 16u), 0, kAgent);
+    v = __longlong_as_double((long long)(u64(w.x) | (u64(w.z) << 32)));
+    return w.y == tag && w.w == tag;
+}
+__device__ inline bool receive(__amdgpu_buffer_rsrc_t r, unsigned slot, unsigned tag, float& v) {
+    asm volatile("" ::: "memory");
+    const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(r, int(slot * 8u), 0, kAgent);
+    v = __uint_as_float(w.x);
+    return w.y == tag;
+}
+
+// Repeats `ready` for the lanes that `want` it until it holds for all of them; false
+// when the bound ran out here or elsewhere.  Wave-uniform (all lanes of a wavefront
+// call it together).  The clock and the abort word are looked at once in 256 tries;
+// a bound of 0 gives up after the first.
+template <typename F>
+__device__ inline bool wait_for(bool want, F ready, u64* abort_word, unsigned tag, u64 ticks) {
+    u64 t0 = 0;
+    for (unsigned n = 1;; ++n) {
+        if (want) want = !ready();  // a lane that has its data asks no more
+        if (!__any(want)) return true;
+        if ((n & 255u) == 0 || ticks == 0) {
+            if (unsigned(word_load(abort_word)) == tag) return false;
+            const u64 now = __builtin_amdgcn_s_memrealtime();
+            if (t0 == 0) t0 = now;
+            if (now - t0 >= ticks) {
+                word_store(abort_word, tag);
+                return false;
+            }
+        }
+    }
+}
+
+// Shapes by the largest port count QB (per_simd: wavefronts a SIMD should hold, which
+// bounds the registers; more sub-circuits then fit the chip) of a sub-circuit.  Row p of the operator
+// (lane) is port p's node against every port's node: z_n(p) = sum_p' S(n_p, n_p') c_p' a_p'.
+// Up to 32 ports, one wavefront takes two sub-circuits, all 32 columns of a row in a
+// lane (64 registers in FP64).  Above, a workgroup takes one: RG groups of 64 rows
+// by CG groups of COLS columns, the partial sums meeting in LDS; 16-32 columns a lane
+// keep the chain of multiply-adds short and the registers low.
+//
+// FP32 (packed operators, up to 64 ports) forms z in the order of the packed sweep of a
+// launch per sweep (ports.hip), bit for bit: row r is port node r, and lane r holds for
+// each diagonal d both S(r, r + d) and S(r - d, r); t = c a summed per node is staged
+// between zeros.  An FP32 inner solve stops where rounding is a visible part of its
+// residual, so another order would now and then end it at another check.
+template <int QB>
+struct Shape;
+template <>
+struct Shape<32> {
+    static constexpr int RG = 1, CG = 1, COLS = 32, SUBS = 2;
+    template <typename T>
+    static constexpr int per_simd() { return 4; }
+};
+template <>
+struct Shape<64> {
+    static constexpr int RG = 1, CG = 4, COLS = 16, SUBS = 1;
+    template <typename T>
+    static constexpr int per_simd() { return 5; }
+};
+template <>
+struct Shape<96> {
+    static constexpr int RG = 2, CG = 4, COLS = 24, SUBS = 1;
+    template <typename T>
+    static constexpr int per_simd() { return 4; }
+};
+template <>
+struct Shape<128> {
+    static constexpr int RG = 2, CG = 4, COLS = 32, SUBS = 1;
+    template <typename T>
+    static constexpr int per_simd() { return 4; }
+};
+
+// pair m of diagonals of a packed triangle (ports.hip)
+__device__ inline int packed_at(int k, int i, int j) {
+    const int lo = min(i, j), d = max(i, j) - lo, m = d >> 1;
+    return 2 * m * (k - m + 1) + 2 * lo + (d & 1);
+}
+
+// The last workgroup controls the run: it collects the n other workgroups' sums at
+// every check, decides, and publishes.  (In a workgroup of its own the decision's
+// logarithms hold no registers beside an operator.)
+template <typename T>
+__device__ __forceinline__ void control(const ResidentArgs<T>& A, unsigned n) {
+    __shared__ double red[8];
+    __shared__ int bad;
+    __shared__ unsigned next_s;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6;
+    u64* const decision = A.sums + 2 * size_t(n);
+    u64* const abort_word = decision + 1;
+    ResidentState* const st = A.state;
+    ResidentControl ctl = A.ctl;
+    int checks = 0, hist = 0;
+    unsigned tag = A.epoch, run = unsigned(ctl.first);
+    if (tid == 0) bad = 0;
+    while (true) {
+        tag += run;
+        // every workgroup's sum: each thread its strided share in order, then a tree
+        double sum = 0.0;
+        for (unsigned b0 = 0; b0 < n; b0 += blockDim.x) {
+            double v = 0.0;
+            const unsigned b = b0 + tid;
+            const u64* const slot = A.sums + 2 * size_t(b < n ? b : 0);
+            if (!wait_for(b < n, [&] { return receive(slot, tag, v); }, abort_word, A.epoch + 1, A.wait_ticks)) {
+                bad = st->timeout = 1;
+                break;
+            }
+            sum += b < n ? v : 0.0;
+        }
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d);
+        if (lane == 0) red[wave] = sum;
+        __syncthreads();
+        if (bad) return;
+        if (tid == 0) {
+            sum = red[0];
+            for (int v = 1; v < waves; ++v) sum += red[v];
+            const double rel = ctl.bb > 0.0 ? sqrt(sum / ctl.bb) : sqrt(sum);
+            ctl.sweeps += run;
+            ++checks;
+            int stop = kAborted;
+            const bool finite = isfinite(rel);
+            if (!ctl.inner) {
+                st->hist[hist] = rel;
+                st->hist_sweeps[hist] = ctl.sweeps;
+                ++hist;
+                if (!finite || rel > ctl.divergence)
+                    stop = kBad;
+                else if (rel <= ctl.tol)
+                    stop = kDone;
+                else if (ctl.sweeps >= ctl.max_sweeps)
+                    stop = kSweepLimit;
+            } else {
+                const bool improved = rel < 0.8 * ctl.best;
+                if (rel < ctl.best) ctl.best = rel;
+                ctl.since = improved ? 0 : ctl.since + 1;
+                if (!finite)
+                    stop = kBad;
+                else if (rel <= ctl.tol)
+                    stop = kDone;
+                else if (ctl.since >= 2)
+                    stop = kStalled;
+                else if (ctl.sweeps >= ctl.max_sweeps)
+                    stop = kSweepLimit;
+            }
+            unsigned nx = 0;
+            if (stop == kAborted) {
+                ctl.cad.record(ctl.sweeps, rel);
+                if (hist == kResidentHist || ctl.sweeps - A.ctl.sweeps >= kResidentSweeps) {
+                    stop = kMore;
+                } else {
+                    int64_t n2 = ctl.cad.next(ctl.inner && ctl.tol > 1.0 ? 1.0 : ctl.tol);
+                    if (ctl.pow2) n2 = graph_length(ctl.cad.m, n2);
+                    if (n2 > ctl.max_sweeps - ctl.sweeps) n2 = ctl.max_sweeps - ctl.sweeps;
+                    nx = unsigned(n2);
+                }
+            }
+            if (nx == 0) {
+                st->ctl = ctl;
+                st->checks = checks;
+                st->hist_len = hist;
+                st->rel = rel;
+                st->stop = stop;
+            }
+            word_store(decision, u64(nx) | (u64(tag) << 32));
+            next_s = nx;
+        }
+        __syncthreads();
+        run = next_s;
+        if (run == 0) return;
+        __syncthreads();  // next_s is read before the next check writes it
+    }
+}
+
+// staged t of one sub-circuit: rows of zeros before and after it
+template <int QB>
+constexpr int kSpan = 3 * (QB <= 32 ? 32 : 64);
+
+template <typename T, int QB>
+__global__ void __launch_bounds__(64 * Shape<QB>::RG * Shape<QB>::CG, Shape<QB>::template per_simd<T>())
+    k_resident(ResidentArgs<T> A) {
+    const unsigned nb = gridDim.x - 1;         // workgroups that sweep
+    if (blockIdx.x == nb) {
+        control<T>(A, nb);
+        return;
+    }
+    using Sh = Shape<QB>;
+    constexpr int RG = Sh::RG, CG = Sh::CG, COLS = Sh::COLS, SUBS = Sh::SUBS;
+    constexpr int L = 64 / SUBS;               // lanes of a sub-circuit's row group
+    constexpr int ROWS = L * RG;               // rows (ports) of a sub-circuit
+    constexpr int STAGE = CG * COLS + 2;       // staged c a of a sub-circuit (the pad keeps two sub-circuits'
+                                               // broadcast reads in different banks)
+    constexpr int W = sizeof(T) / 4;           // words of a wave
+    constexpr bool ORDERED = sizeof(T) == 4;   // the packed sweep's order (see above)
+    constexpr int CHUNKS = ORDERED && CG > 1 ? 8 : CG;
+    __shared__ alignas(16) T ca[SUBS][STAGE];
+    __shared__ T zp[CHUNKS][64 * RG];
+    __shared__ T ts[ORDERED ? SUBS : 1][ORDERED ? kSpan<QB> : 1];
+    __shared__ double xs[64 * RG], vs[64 * RG], red[8];
+    __shared__ int32_t node[64 * RG], first[64 * RG], cnt[64 * RG];
+    __shared__ int bad;
+    __shared__ unsigned next_s;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int unit = xcd_block(blockIdx.x, nb);
+    const int sub = SUBS == 2 ? lane >> 5 : 0;
+    const int rg = wave % RG, cg = wave / RG;
+    const int row = SUBS == 2 ? (lane & 31) : rg * 64 + lane;
+    const int s = min(unit * SUBS + sub, A.S - 1);
+    const bool real = unit * SUBS + sub < A.S;
+    const int p0 = A.port_off[s], q = real ? A.port_off[s + 1] - p0 : 0;
+    const int k0 = A.pn_off[s], k = A.pn_off[s + 1] - k0;
+    const int base = sub * 32;                 // this sub-circuit's entries of node, first, cnt, xs, vs
+    const bool owner = cg == 0 && row < q;     // this thread exchanges port p0 + row
+    u64* const abort_word = A.sums + 2 * size_t(nb) + 1;
+    const __amdgpu_buffer_rsrc_t slots =
+        __builtin_amdgcn_make_buffer_rsrc(A.slots, 0, int(unsigned(A.nports) * unsigned(W) * 16u), 0x00020000);
+    ResidentState* const st = A.state;
+
+    // ports of each node: node, first and count per port
+    if (tid == 0) bad = 0;
+    if (cg == 0) {
+        for (int j = row; j < (real ? k : 0); j += ROWS) {
+            const int f0 = A.pn_pfirst[k0 + j] - p0, f1 = A.pn_pfirst[k0 + j + 1] - p0;
+            for (int p = f0; p < f1; ++p) {
+                node[base + p] = j;
+                first[base + p] = f0;
+                cnt[base + p] = f1 - f0;
+            }
+        }
+        for (int j = row; j < STAGE; j += ROWS) ca[sub][j] = T(0);
+    }
+    __syncthreads();
+    if constexpr (ORDERED)
+        for (int j = row; cg == 0 && j < kSpan<QB>; j += ROWS) ts[sub][j] = T(0);
+    // this lane's diagonals when ORDERED: chunks of 8, cg and cg + 4 of them with several wavefronts
+    auto diagonal = [&](int j) { return CG == 1 ? j : 8 * (j < 8 ? cg : cg + 4) + (j & 7); };
+    // the operator's row, columns cg COLS .. of this lane
+    T op[COLS], lo[ORDERED ? COLS : 1];
+    if constexpr (ORDERED) {
+        const T* blk = A.op + A.ofs[s];
+#pragma unroll
+        for (int j = 0; j < COLS; ++j) {
+            const int d = diagonal(j);
+            op[j] = real && row + d < k ? blk[packed_at(k, row, row + d)] : T(0);
+            lo[j] = real && d > 0 && row < k && row >= d ? blk[packed_at(k, row - d, row)] : T(0);
+        }
+    } else {
+        const T* blk = A.op + A.ofs[s];
+        const int i = row < q ? node[base + row] : 0;
+#pragma unroll
+        for (int j = 0; j < COLS; ++j) {
+            const int col = cg * COLS + j;
+            T v = T(0);
+            if (row < q && col < q) {
+                const int jn = node[base + col];
+                v = A.packed ? blk[packed_at(k, i, jn)] : blk[inv_offset<T>(k, i, jn)];
+            }
+            op[j] = v;
+        }
+    }
+    // ports of this lane's node (ORDERED)
+    int f0 = 0, f1 = 0;
+    if (ORDERED && real && row < k) {
+        f0 = A.pn_pfirst[k0 + row] - p0;
+        f1 = A.pn_pfirst[k0 + row + 1] - p0;
+    }
+    T a = T(0), o = T(0), o_prev = T(0), h = T(0), c = T(0), be = T(0), ga = T(0), an = T(0);
+    int tw = 0;
+    const int p = p0 + row;
+    if (owner) {
+        tw = A.port_twin[p];
+        a = A.a[A.cur][p];
+        o_prev = A.a[A.cur][tw];
+        h = A.h[p];
+        c = A.c[p];
+        if (A.packed) {
+            // beta and gamma from the rounded c, as the packed sweep forms them: the lines then
+            // stay exactly passive in FP32 too
+            be = T(2) * (A.w ? A.w[p] : A.W) * c;
+            ga = T(1) - T(2) * c;
+        } else {
+            be = A.beta[p];
+            ga = A.gamma[p];
+        }
+    }
+    unsigned left = unsigned(A.ctl.first);
+    unsigned tag = A.epoch;
+    const unsigned abort_tag = A.epoch + 1;    // this launch's: no other launch on these words has it
+
+    while (true) {
+        // one sweep
+        ++tag;
+        const unsigned set = (tag & 1) ? unsigned(A.nports) : 0u;
+        if (owner) ca[sub][row] = c * a;
+        __syncthreads();
+        if (bad) return;
+        T z = T(0);
+        if constexpr (ORDERED) {
+#pragma clang fp contract(off)
+            constexpr int MID = kSpan<QB> / 3;
+            if (cg == 0 && real && row < k) {
+                T t = T(0);
+                for (int i = f0; i < f1; ++i) t += ca[sub][i];
+                ts[sub][MID + row] = t;
+            }
+            __syncthreads();
+            const T* tr = &ts[sub][MID + row];
+            if constexpr (CG == 1) {
+#pragma unroll
+                for (int j = 0; j < COLS; ++j) {
+                    z = __builtin_fmaf(op[j], tr[j], z);
+                    const T up = lo[j] * tr[-j];
+                    z += j > 0 ? up : T(0);
+                }
+                zp[0][tid] = z;
+            } else {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    T zc = T(0);
+#pragma unroll
+                    for (int j = 8 * i; j < 8 * i + 8; ++j) {
+                        const int d = diagonal(j);
+                        zc = __builtin_fmaf(op[j], tr[d], zc);
+                        const T up = lo[j] * tr[-d];
+                        zc += d > 0 ? up : T(0);
+                    }
+                    zp[cg + 4 * i][row] = zc;
+                }
+            }
+            __syncthreads();
+            if (owner) {
+                const int n = base + node[base + row];
+                if constexpr (CG == 1) {
+                    z = zp[0][n];
+                } else {
+                    z = T(0);
+#pragma unroll
+                    for (int v = 0; v < CHUNKS; ++v) z += zp[v][n];
+                }
+                o = packed_wave_out<T>(be, c, z, a, h);
+            }
+        } else {
+        T z0 = T(0), z1 = T(0), z2 = T(0), z3 = T(0);
+#pragma unroll
+        for (int j = 0; j < COLS; j += 4) {
+            const T* cc = &ca[sub][cg * COLS + j];
+            z0 += op[j] * cc[0];
+            z1 += op[j + 1] * cc[1];
+            z2 += op[j + 2] * cc[2];
+            z3 += op[j + 3] * cc[3];
+            // bounds the staged values read ahead (their registers would displace op's)
+            if (j % 8 == 4 && j + 4 < COLS) asm volatile("" : "+v"(z0), "+v"(z1), "+v"(z2), "+v"(z3) : : "memory");
+        }
+        z = (z0 + z1) + (z2 + z3);
+        if constexpr (CG > 1) {
+            zp[cg][rg * 64 + lane] = z;
+            __syncthreads();
+            if (cg == 0) {
+                z = zp[0][row];
+#pragma unroll
+                for (int v = 1; v < CG; ++v) z += zp[v][row];
+            }
+        }
+        if (owner) o = be * z + ga * a + h;
+        }
+        if (cg == 0) {
+            if (owner) {
+                send(slots, set + unsigned(tw), o, tag);
+            }
+            if (!wait_for(owner, [&] { return receive(slots, set + unsigned(p), tag, an); }, abort_word, abort_tag,
+                             A.wait_ticks))
+                bad = st->timeout = 1;
+        }
+        if (--left == 0) {
+            // the residual from port quantities: with o and an the waves that left and
+            // arrived in this sweep, x_i = (o - gamma a) / beta on this side of a wire and
+            // x_j = (an - gamma o_prev) / beta on the other (both ends share the wire's
+            // coefficients; the twin's incoming wave was this port's previous one)
+            double be64 = 1.0, ga64 = 0.0;
+            if (owner) {
+                be64 = A.beta64[p];
+                ga64 = A.gamma64[p];
+                xs[base + row] = (double(o) - ga64 * double(a)) / be64;
+            }
+            __syncthreads();
+            if (bad) return;
+            if (owner) {
+                const double xj = (double(an) - ga64 * double(o_prev)) / be64;
+                vs[base + row] = A.gd[p] * xs[base + first[base + row]] + A.g[p] * xj - A.c64[p] * double(a);
+            }
+            __syncthreads();
+            double rr = 0.0;
+            if (owner && first[base + row] == row) {
+                double r = 0.0;
+                for (int i = 0; i < cnt[base + row]; ++i) r += vs[base + row + i];
+                rr = r * r;
+            }
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) rr += __shfl_xor(rr, d);
+            if (lane == 0) red[wave] = rr;
+            __syncthreads();
+            if (tid == 0) {
+                rr = red[0];
+#pragma unroll
+                for (int v = 1; v < RG; ++v) rr += red[v];
+                send(A.sums + 2 * size_t(blockIdx.x), rr, tag);
+            }
+            if (wave == 0) {
+                unsigned nx = 0;
+                const u64* const slot = A.sums + 2 * size_t(nb);
+                const bool ok = wait_for(
+                    true,
+                    [&] {
+                        const u64 v = word_load(slot);
+                        nx = unsigned(v);
+                        return unsigned(v >> 32) == tag;
+                    },
+                    abort_word, abort_tag, A.wait_ticks);
+                if (!ok) bad = st->timeout = 1;
+                next_s = nx;
+            }
+            __syncthreads();
+            if (bad) return;
+            left = next_s;
+            if (left == 0) {
+                if (owner) {
+                    // the last sweep read buffer cur when the run had an odd number of sweeps
+                    const int in = (A.cur + int((tag - A.epoch - 1) & 1)) & 1;
+                    A.a[in][p] = a;
+                    A.a[in ^ 1][p] = an;
+                }
+                return;
+            }
+        }
+        o_prev = o;
+        a = an;
+    }
+}
+
+template <typename T, int QB>
+int blocks_of(int S) {
+    using Sh = Shape<QB>;
+    int dev = 0, cus = 0, coop = 0, per = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, reinterpret_cast<const void*>(&k_resident<T, QB>),
+                                                     64 * Sh::RG * Sh::CG, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    const int64_t blocks = (int64_t(S) + Sh::SUBS - 1) / Sh::SUBS;
+    return blocks < int64_t(per) * cus ? int(blocks) : 0;  // and the controlling one
+}
+
+template <typename T, int QB>
+hipError_t launch_q(const ResidentArgs<T>& args, hipStream_t st) {
+    using Sh = Shape<QB>;
+    ResidentArgs<T> a = args;
+    void* params[] = {&a};
+    return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_resident<T, QB>),
+                                      dim3((unsigned(args.S) + Sh::SUBS - 1) / Sh::SUBS + 1), dim3(64 * Sh::RG * Sh::CG),
+                                      params, 0, st);
+}
+
+}  // namespace
+
+template <typename T>
+int resident_blocks(int S, int max_ports, bool packed) {
+    if (S < 1 || max_ports > 128) return 0;
+    if constexpr (sizeof(T) == 4) {
+        if (!packed || max_ports > 64) return 0;
+        return max_ports <= 32 ? blocks_of<T, 32>(S) : blocks_of<T, 64>(S);
+    } else {
+        return max_ports <= 32   ? blocks_of<T, 32>(S)
+               : max_ports <= 64 ? blocks_of<T, 64>(S)
+               : max_ports <= 96 ? blocks_of<T, 96>(S)
+                                 : blocks_of<T, 128>(S);
+    }
+}
+
+template <typename T>
+hipError_t launch_resident(const ResidentArgs<T>& args, int max_ports, hipStream_t st) {
+    if (args.S < 1 || max_ports > 128) return hipErrorInvalidValue;
+    if constexpr (sizeof(T) == 4) {
+        if (!args.packed || max_ports > 64) return hipErrorInvalidValue;
+        return max_ports <= 32 ? launch_q<T, 32>(args, st) : launch_q<T, 64>(args, st);
+    } else {
+        return max_ports <= 32   ? launch_q<T, 32>(args, st)
+               : max_ports <= 64 ? launch_q<T, 64>(args, st)
+               : max_ports <= 96 ? launch_q<T, 96>(args, st)
+                                 : launch_q<T, 128>(args, st);
+    }
+}
+
+template int resident_blocks<double>(int, int, bool);
+template int resident_blocks<float>(int, int, bool);
+template hipError_t launch_resident<double>(const ResidentArgs<double>&, int, hipStream_t);
+template hipError_t launch_resident<float>(const ResidentArgs<float>&, int, hipStream_t);
+
+}  // namespace vtm
