@@ -869,14 +869,16 @@ constexpr int kPptAhead = 4;
 // The matrix cores take 16 columns at a time; lanes of columns past w read column
 // w - 1 again and their results are dropped.  They are used for few columns too
 // because a vector form reads a staged value from LDS per multiply-add, and that
-// alone would take as long.  Bound by latency at the measured sizes (offsets, waves,
-// three barriers; 5 wavefronts per SIMD): 3,276 sub-circuits of 8x8, six right-hand
-// sides, FP64: 10.9 us a sweep, the full inverses it replaces 29.1; 768 of 16x16,
-// four, FP32: 5.9 against 35.  Held to 64 registers for 8 wavefronts per SIMD it
-// spills (19.8 us).
+// alone would take as long.  At the measured sizes it is bound by instructions and by
+// latency (226 vector instructions a wavefront, 3 of its 7 us waiting on memory), not
+// by bytes: 3,276 sub-circuits of 8x8, six right-hand sides, FP64: 9.3 us a sweep (10.9
+// with a run-time division per item and gamma, a and h held apart), the full inverses
+// it replaces 29.1; 768 of 16x16, four, FP32: 5.8 against 35.  A form that reads the
+// packed triangles instead (40% of the operator's bytes) and picks its operands out of
+// LDS took 11.5 us.
 template <typename T, int NI>
 __global__ void __launch_bounds__(512)
-    k_sweep_ppt(int ny, int rc, int nrhs, const T* __restrict__ Nt, const int64_t* __restrict__ ntofs,
+    k_sweep_ppt(int ny, int rc, unsigned irc, int nrhs, const T* __restrict__ Nt, const int64_t* __restrict__ ntofs,
                 const int32_t* __restrict__ pn_off, const int32_t* __restrict__ pn_pfirst,
                 const int32_t* __restrict__ port_off, const int32_t* __restrict__ port_twin, const T* __restrict__ pc,
                 const T* __restrict__ pbeta, const T* __restrict__ pgamma, const T* __restrict__ h,
@@ -887,6 +889,9 @@ __global__ void __launch_bounds__(512)
     const int u = reverse ? xcd_block_reversed(blockIdx.x, gridDim.x) : xcd_block(blockIdx.x, gridDim.x);
     const int s = u / ny, r0 = (u - s * ny) * rc;
     const int w = min(rc, nrhs - r0);
+    // t / w (t < 2^28, w <= 16) as one multiplication
+    const unsigned iw = w == rc ? irc : 0xffffffffu / unsigned(w) + 1u;
+    auto over = [&](int t) { return w == 1 ? t : int(__umulhi(unsigned(t), iw)); };
     T* tv = reinterpret_cast<T*>(smem);            // [max_np][rc]
     T* ca = tv + max_np * rc;                      // [max_rows][rc]: c a per port, then Z per port node
     int32_t* pnode = reinterpret_cast<int32_t*>(ca + max_rows * rc);  // [q] (pf after it)
@@ -896,24 +901,33 @@ __global__ void __launch_bounds__(512)
     const int np = node_tile_pad(k), kt_n = np / KT, mt_n = np / 16;
     const int tid = threadIdx.x, bs = blockDim.x, lane = tid & 63, wave = tid >> 6, waves = bs >> 6;
     const typename M::Frag* A0 = reinterpret_cast<const typename M::Frag*>(Nt + ntofs[s]) + lane;
+    // this wavefront's A tiles in order: row tiles wave, wave + waves, ..., each kt_n long;
+    // the next kPptAhead are always in flight, across row tiles too
     typename M::Frag af[kPptAhead];
+    int lmt = wave, lkt = 0;
+    auto next_tile = [&](typename M::Frag& f) {
+        if (lmt < mt_n) f = A0[(int64_t(lmt) * kt_n + lkt) * 64];
+        if (++lkt == kt_n) {
+            lkt = 0;
+            lmt += waves;
+        }
+    };
 #pragma unroll
-    for (int d = 0; d < kPptAhead; ++d)
-        if (wave < mt_n && d < kt_n) af[d] = A0[(int64_t(wave) * kt_n + d) * 64];
+    for (int d = 0; d < kPptAhead; ++d) next_tile(af[d]);
     const int items = q * w;
     constexpr int NR = NI > 0 ? NI : 1;
-    T va[NR], vh[NR], vb[NR], vg[NR];
+    T vb[NR], vr[NR];  // beta, gamma a + h
     int tw[NR];
     if constexpr (NI > 0) {
-        T vc[NR];
+        T va[NR], vh[NR], vg[NR], vc[NR];
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
             const int t = tid + i * bs;
             va[i] = vh[i] = vb[i] = vg[i] = vc[i] = T(0);
             tw[i] = 0;
             if (t < items) {
-                const int p = p0 + t / w;
-                const int64_t o = int64_t(p) * nrhs + r0 + t % w;
+                const int pl = over(t), p = p0 + pl;
+                const int64_t o = int64_t(p) * nrhs + r0 + (t - pl * w);
                 va[i] = a_cur[o];
                 vc[i] = pc[p];
                 vh[i] = h[o];
@@ -927,17 +941,18 @@ __global__ void __launch_bounds__(512)
         for (int i = 0; i < NR; ++i) {
             const int t = tid + i * bs;
             if (t < items) ca[t] = vc[i] * va[i];
+            vr[i] = vg[i] * va[i] + vh[i];
         }
     } else {
         for (int j = tid; j <= k; j += bs) pf[j] = pn_pfirst[k0 + j] - p0;
         for (int t = tid; t < items; t += bs) {
-            const int p = p0 + t / w;
-            ca[t] = pc[p] * a_cur[int64_t(p) * nrhs + r0 + t % w];
+            const int pl = over(t), p = p0 + pl;
+            ca[t] = pc[p] * a_cur[int64_t(p) * nrhs + r0 + (t - pl * w)];
         }
     }
     __syncthreads();
     for (int t = tid; t < np * w; t += bs) {
-        const int j = t / w, r = t - j * w;
+        const int j = over(t), r = t - j * w;
         T acc = T(0);
         if (j < k) {
             const int f1 = pf[j + 1];
@@ -954,25 +969,22 @@ __global__ void __launch_bounds__(512)
         typename M::Acc acc;
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[v] = T(0);
-        const int64_t row = int64_t(mt) * kt_n;
-        if (mt != wave) {
+        // kt_n is a multiple of 2 (FP64) or 1 (FP32); the ring turns by U tiles
+        constexpr int U = sizeof(T) == 8 ? 2 : 1;
+        for (int kt = 0; kt < kt_n; kt += U) {
 #pragma unroll
-            for (int d = 0; d < kPptAhead; ++d)
-                if (d < kt_n) af[d] = A0[(row + d) * 64];
-        }
-        for (int kt = 0; kt < kt_n; kt += kPptAhead) {
+            for (int d = 0; d < U; ++d) {
+                const typename M::Frag a = af[d];
 #pragma unroll
-            for (int d = 0; d < kPptAhead; ++d) {
-                if (kt + d < kt_n) {
-                    const typename M::Frag a = af[d];
-                    if (kt + d + kPptAhead < kt_n) af[d] = A0[(row + kt + d + kPptAhead) * 64];
-#pragma unroll
-                    for (int j = 0; j < E; ++j) {
-                        const T b = tv[((kt + d) * KT + 4 * j + (lane >> 4)) * w + nc];
-                        acc = M::step(a, j, b, acc);
-                    }
+                for (int j = 0; j < E; ++j) {
+                    const T b = tv[((kt + d) * KT + 4 * j + (lane >> 4)) * w + nc];
+                    acc = M::step(a, j, b, acc);
                 }
             }
+#pragma unroll
+            for (int d = 0; d + U < kPptAhead; ++d) af[d] = af[d + U];
+#pragma unroll
+            for (int d = kPptAhead - U; d < kPptAhead; ++d) next_tile(af[d]);
         }
         if ((lane & 15) < w) {
 #pragma unroll
@@ -985,16 +997,16 @@ __global__ void __launch_bounds__(512)
         for (int i = 0; i < NR; ++i) {
             const int t = tid + i * bs;
             if (t < items) {
-                const int p = t / w, r = t - p * w;
-                a_next[int64_t(tw[i]) * nrhs + r0 + r] = vb[i] * ca[pnode[p] * w + r] + vg[i] * va[i] + vh[i];
+                const int p = over(t), r = t - p * w;
+                a_next[int64_t(tw[i]) * nrhs + r0 + r] = vb[i] * ca[pnode[p] * w + r] + vr[i];
             }
         }
     } else {
         for (int t = tid; t < items; t += bs) {
-            const int p = t / w, r = t - p * w;
+            const int p = over(t), r = t - p * w;
             const int64_t o = int64_t(p0 + p) * nrhs + r0 + r;
             a_next[int64_t(port_twin[p0 + p]) * nrhs + r0 + r] =
-                pbeta[p0 + p] * ca[pnode[p] * w + r] + pgamma[p0 + p] * a_cur[o] + h[o];
+                pbeta[p0 + p] * ca[pnode[p] * w + r] + (pgamma[p0 + p] * a_cur[o] + h[o]);
         }
     }
 }
@@ -1029,7 +1041,8 @@ hipError_t launch_sweep_ppt(int S, int max_npn, int max_ports, int nrhs, size_t 
     const int64_t items = int64_t(max_ports) * rc;
     auto kern = items <= 2 * bs ? k_sweep_ppt<T, 2> : items <= 4 * bs ? k_sweep_ppt<T, 4> : k_sweep_ppt<T, 0>;
     if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds); e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(unsigned(S) * unsigned(ny)), dim3(bs), lds, st, ny, rc, nrhs, Nt, ntofs, pn_off,
+    hipLaunchKernelGGL(kern, dim3(unsigned(S) * unsigned(ny)), dim3(bs), lds, st, ny, rc,
+                       rc > 1 ? 0xffffffffu / unsigned(rc) + 1u : 0u, nrhs, Nt, ntofs, pn_off,
                        pn_pfirst, port_off, port_twin, pc, pbeta, pgamma, h, a_cur, a_next, np, rows, reverse);
     return hipGetLastError();
 }
