@@ -274,14 +274,14 @@ def batched_pp_roofline(vtm, torch, w):
     """HBM roofline of the batched port-to-port sweep (BF16 and FP64 operator tiles,
     64 right-hand sides): algorithmic bytes per launch over the average launch time
     from HIP events around each run of port-to-port sweeps (timing mode 2).
-    Bytes: the padded q_s x q_s operator of every sub-circuit once (q_s = cut wires
-    at s, padded to a multiple of 32; 2 or 8 bytes an entry), and per port and
+    Bytes: the q_s x q_s operator of every sub-circuit once (q_s = cut wires at s,
+    padded to whole tiles of 16 x 32 in BF16, 16 x 8 in FP64; 2 or 8 bytes an entry),
+    and per port and
     right-hand side the incident wave, h and the outgoing wave (4 or 8 bytes each),
     plus a 4-byte twin index per port."""
     i, j = w.edges[:, 0], w.edges[:, 1]
     cut = w.part[i] != w.part[j]
     q = np.bincount(w.part[i[cut]], minlength=w.n_sub) + np.bincount(w.part[j[cut]], minlength=w.n_sub)
-    qp = (q + 31) // 32 * 32
     ports = int(q.sum())
     b = torch.as_tensor(w.b, dtype=torch.float64, device="cuda")
     x = torch.empty_like(b)
@@ -292,7 +292,9 @@ def batched_pp_roofline(vtm, torch, w):
         _, rep = s.solve(b, w.tol, x)
         s.close()
         us = rep.pp_kernel_ms / max(rep.pp_launches, 1) * 1e3
-        nbytes = int((qp.astype(np.int64) ** 2).sum() * e_op + ports * w.nrhs * 3 * e_vec + ports * 4)
+        kt = 32 if e_op == 2 else 8   # columns of an operand tile
+        tiles = ((q + 15) // 16 * 16).astype(np.int64) * ((q + kt - 1) // kt * kt)
+        nbytes = int(tiles.sum() * e_op + ports * w.nrhs * 3 * e_vec + ports * 4)
         gbs = nbytes / (us * 1e-6) / 1e9
         out["bf16" if prec == "bf16_refine" else "fp64"] = {
             "bound": "hbm", "kernel": "k_sweep_mfma_pp", "achieved": round(gbs, 1), "peak": 8000.0,

@@ -141,6 +141,7 @@ struct vtm_handle_s {
     DevBuf<float> K32;
     DevBuf<__bf16> Kbf;
     DevBuf<int64_t> mofs;
+    int64_t tile_total = 0, qtile_total = 0;  // elements of the tiled inverses and port operators
     bool tiles = false;
     // MFMA tiles of the transposed inverses (adjoint of an unsymmetric A)
     DevBuf<double> K64T;
@@ -600,11 +601,12 @@ vtm_status autotune(vtm_handle h) {
         else
             VTM_HIP(vtm::launch_fill<double>(P.nports * nrhs, 0.0, h->h64.p, h->stream));
         float best_pp = INFINITY;
-        // variants: bit 0 five row tiles, bit 1 eight wavefronts, bit 2 one row tile (bit 0 unused)
+        // variants: bit 0 five row tiles, bit 1 eight wavefronts, bit 2 one row tile (bit 0
+        // unused), bit 3 with bit 2 six wavefronts
         const bool forced_rows = h->opt.batch_row_tiles > 0;
-        for (int variant = 0; variant < 8 && st == VTM_OK; ++variant)
+        for (int variant : {0, 1, 2, 3, 4, 6, 12})
             for (int rc = 64; rc >= 16 && st == VTM_OK; rc -= 16) {
-                if ((variant & 5) == 5 || (forced_rows && (variant & 4))) continue;
+                if (forced_rows && (variant & 4)) continue;
                 if (!(variant & 4) && ((variant & 1) < v_lo || (variant & 1) > v_hi)) continue;
                 if (rc > 16 && rc >= nrhs + 16) continue;
                 if (h->opt.batch_rhs_block > 0 && rc != h->opt.batch_rhs_block) continue;
@@ -1158,11 +1160,11 @@ vtm_status solve_common(vtm_handle h, const double* b, double* x, int32_t nrhs, 
         rep->pp_launches = out.pp_launches;
         rep->batch_row_tiles = h->tiles ? (h->mfma_variant == 1 ? 5 : (h->mfma_variant == 2 ? 1 : 3)) : 0;
         rep->batch_rhs_block = h->tiles ? h->mfma_rc : 0;
-        // pp variant bits: 0 five row tiles, 1 eight wavefronts, 2 one row tile
+        // pp variant bits: 0 five row tiles, 1 eight wavefronts, 2 one row tile, 3 six wavefronts
         const int ppv = h->pp_variant;
         rep->pp_shape[0] = h->ppb ? ((ppv & 4) ? 1 : (ppv & 1) ? 5 : 3) : 0;
         rep->pp_shape[1] = h->ppb ? std::min(h->pp_rc, (nrhs + 15) / 16 * 16) : 0;
-        rep->pp_shape[2] = h->ppb ? ((ppv & 2) ? 8 : 4) : 0;
+        rep->pp_shape[2] = h->ppb ? ((ppv & 8) ? 6 : (ppv & 2) ? 8 : 4) : 0;
         if (rep->relres)
             for (int r = 0; r < nrhs; ++r) rep->relres[r] = out.rel[r];
         const int64_t len = std::min<int64_t>(int64_t(out.hist.size()), std::max(rep->history_cap, 0));
@@ -1176,6 +1178,14 @@ vtm_status solve_common(vtm_handle h, const double* b, double* x, int32_t nrhs, 
     if (out.status == VTM_E_DIVERGED) return fail(VTM_E_DIVERGED, "the iteration diverged");
     if (out.status == VTM_E_MAXITER) return fail(VTM_E_MAXITER, "no convergence within the sweep limit");
     return VTM_OK;
+}
+
+// Element offset of each tiled block of sizes off[s + 1] - off[s] (tiles.hpp), and the total.
+template <typename T>
+std::vector<int64_t> tile_offsets(const std::vector<int32_t>& off) {
+    std::vector<int64_t> ofs(off.size(), 0);
+    for (size_t s = 0; s + 1 < off.size(); ++s) ofs[s + 1] = ofs[s] + vtm::tile_elems<T>(off[s + 1] - off[s]);
+    return ofs;
 }
 
 }  // namespace
@@ -1308,7 +1318,7 @@ static vtm_status build_values(vtm_handle_s* h) {
     const vtm_options& o = h->opt;
     const vtm::Plan& P = h->plan;
     hipStream_t s = h->stream;
-    const int64_t nk = P.kofs[P.S], nm = P.mofs[P.S];
+    const int64_t nk = P.kofs[P.S], nm = h->tile_total;
     VTM_HIP(h->val.upload(P.val, s));
     if (!P.symmetric) {
         std::vector<int32_t> rT, cT;
@@ -1402,7 +1412,7 @@ static vtm_status build_values(vtm_handle_s* h) {
     if (flag & 1) return fail(VTM_E_SINGULAR, "a sub-circuit matrix is singular");
     // port-to-port operators from the inverses
     if (h->ppb) {  // batched form: in tile order, from the FP64 inverses in inv64
-        const int64_t nq = P.qmofs[P.S];
+        const int64_t nq = h->qtile_total;
         if (o.precision == VTM_FP64) {
             VTM_HIP(h->M64t.alloc(nq));
             VTM_HIP(vtm::launch_port_matrix_tiles<double>(int(P.S), h->sub_off.p, h->kofs.p, h->port_off.p,
@@ -1566,7 +1576,10 @@ static vtm_status setup_from_plan(std::unique_ptr<vtm_handle_s> h, vtm_handle* o
     h->tiles = o.precision == VTM_BF16_REFINE || (o.precision == VTM_FP64 && nr >= 16 && fits64);
     if (h->tiles) {
         if (nr > 64 && o.precision == VTM_BF16_REFINE) return fail(VTM_E_UNSUPPORTED, "BF16 path takes at most 64 RHS");
-        VTM_HIP(h->mofs.upload(P.mofs, s));
+        const auto ofs = o.precision == VTM_FP64 ? tile_offsets<double>(P.sub_off) : tile_offsets<__bf16>(P.sub_off);
+        h->tile_total = ofs.back();
+        VTM_HIP(h->mofs.upload(ofs, s));
+        VTM_HIP(hipStreamSynchronize(s));
     }
     if (P.coupled) {
         VTM_HIP(h->brow.upload(P.brow, s));
@@ -1601,7 +1614,10 @@ static vtm_status setup_from_plan(std::unique_ptr<vtm_handle_s> h, vtm_handle* o
                                       : vtm::pp_lds_bytes<__bf16>(qpad, 16, false)) <= h->lds_limit;
     const bool fp64 = o.precision == VTM_FP64;
     if (h->ppb) {
-        VTM_HIP(h->qmofs.upload(P.qmofs, s));
+        const auto ofs = fp64 ? tile_offsets<double>(P.port_off) : tile_offsets<__bf16>(P.port_off);
+        h->qtile_total = ofs.back();
+        VTM_HIP(h->qmofs.upload(ofs, s));
+        VTM_HIP(hipStreamSynchronize(s));
         VTM_HIP(fp64 ? h->h64.alloc(P.nports * nr) : h->h32.alloc(P.nports * nr));
     }
     if (h->pp || h->ppb) VTM_HIP(h->pn_pfirst.upload(P.pn_pfirst, s));
@@ -1780,8 +1796,8 @@ vtm_status vtm_info(vtm_handle h, int64_t* n, int64_t* n_sub, int64_t* n_wires, 
         if (n) *n = P.n;
         if (n_sub) *n_sub = P.S;
         if (n_wires) *n_wires = P.nwires;
-        if (inverse_bytes) *inverse_bytes = (h->tiles ? P.mofs[P.S] : P.kofs[P.S]) * esize;
-        const int64_t op = h->ppb   ? P.qmofs[P.S] * esize
+        if (inverse_bytes) *inverse_bytes = (h->tiles ? h->tile_total : P.kofs[P.S]) * esize;
+        const int64_t op = h->ppb   ? h->qtile_total * esize
                            : h->ppn ? P.nofs[P.S] * esize
                            : h->pps ? P.sofs[P.S] * esize
                            : h->pp  ? P.pofs[P.S] * esize

@@ -18,6 +18,8 @@
 #include "layout.hpp"
 #include "tiles.hpp"
 
+#include <algorithm>
+
 namespace vtm {
 
 // batched sweeps: k tiles of A in flight per wavefront (port-to-port FP64, BF16)
@@ -90,19 +92,20 @@ struct Mma<double> {
     static __device__ int out_row(int l, int v) { return (l >> 4) + 4 * v; }
 };
 
-// The GEMM core of the batched sweeps: D = A B for one padded np x np block A
-// (tile order, tiles.hpp) and the staged np x w block B in LDS.  A wavefront
+// The GEMM core of the batched sweeps: D = A B for one block A of mt_n x kt_n tiles
+// (tiles.hpp) and the staged block B of w columns in LDS.  A wavefront
 // takes up to RT row tiles (mt = wave, wave + W, ...) per pass and walks k: per
 // k tile it loads the NT B fragments once from LDS and its row tiles' A tiles
 // from HBM (the next k tile's A tiles are already in flight), then issues the
-// MFMAs.  epi(row, n, value) receives every element of D (rows < np, n < 16 NT);
+// MFMAs.  epi(row, n, value) receives every element of D (rows < 16 mt_n, n < 16 NT);
 // mt_lim >= 0 forms only the first mt_lim row tiles.
 template <typename T, int NT, int RT, int WAVES, int PD64 = kMfmaPD64, typename Epi>
-__device__ inline void tile_gemm(const T* Ablk, int np, const T* sb, int bsel, int w, Epi epi, int mt_lim = -1) {
+__device__ inline void tile_gemm(const T* Ablk, int mt_n, int kt_n, const T* sb, int bsel, int w, Epi epi,
+                                 int mt_lim = -1) {
     using M = Mma<T>;
     using TV = typename M::TV;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int MT = mt_lim >= 0 ? min(np / 16, mt_lim) : np / 16, KT = np / M::KT;
+    const int MT = mt_lim >= 0 ? min(mt_n, mt_lim) : mt_n, KT = kt_n;
     const typename M::AFrag* A0 = reinterpret_cast<const typename M::AFrag*>(Ablk) + lane;
     for (int g0 = 0; g0 < MT; g0 += WAVES * RT) {
         int mts[RT];
@@ -163,7 +166,8 @@ __device__ inline void tile_gemm(const T* Ablk, int np, const T* sb, int bsel, i
     }
 }
 
-// Block (y, s): sub-circuit s, right-hand sides [r0, r0 + w), w <= rc <= 16 * NT.
+// Block (y, s): sub-circuit s, right-hand sides [r0, r0 + w), w <= rc = 16 NT (known
+// at compile time, so that the index divisions of the staging are).
 // TB: element type of the right-hand side b (BF16 for the BF16 path: the staged
 // operand is BF16 anyway).  write_x = 0 stores x only on port rows (all the
 // wave update needs); the last sweep before a residual check passes 1.
@@ -174,9 +178,10 @@ __global__ void __launch_bounds__(kBlock)
                  const int32_t* __restrict__ port_twin, const typename Mma<T>::TV* __restrict__ pc,
                  const typename Mma<T>::TV* __restrict__ pbeta, const typename Mma<T>::TV* __restrict__ pgamma,
                  const TB* __restrict__ b, const typename Mma<T>::TV* __restrict__ a_cur,
-                 typename Mma<T>::TV* __restrict__ a_next, typename Mma<T>::TV* __restrict__ x, int nrhs, int rc,
+                 typename Mma<T>::TV* __restrict__ a_next, typename Mma<T>::TV* __restrict__ x, int nrhs,
                  int write_x, int S, int port_rows) {
     using M = Mma<T>;
+    constexpr int rc = 16 * NT;
     using TV = typename M::TV;
     extern __shared__ char smem[];
     T* sb = reinterpret_cast<T*>(smem);
@@ -189,7 +194,7 @@ __global__ void __launch_bounds__(kBlock)
     const int w = min(rc, nrhs - r0);
     const int off = sub_off[s];
     const int ns = sub_off[s + 1] - off;
-    const int np = tile_pad(ns);
+    const int np = tile_cols<T>(ns);
     const int p0 = port_off[s], p1 = port_off[s + 1];
     const int tid = threadIdx.x;
 
@@ -214,7 +219,7 @@ __global__ void __launch_bounds__(kBlock)
     }
     __syncthreads();
     const bool vec = (nrhs % V) == 0;
-    const int rv = rc / V;
+    constexpr int rv = rc / V;
     if (vec) {
         // SU items per thread per round; each item's b load is waited on only after
         // its ports' loads are issued (b is added last), so a round costs about one
@@ -300,14 +305,15 @@ __global__ void __launch_bounds__(kBlock)
     // port_rows: only the row tiles of the port nodes, numbered first (the last
     // port's node is the last of them)
     const int mt_lim = port_rows ? (nps > 0 ? pnode[nps - 1] + 16 : 0) / 16 : -1;
-    tile_gemm<T, NT, RT, kWaves, kMfmaFullPD64>(K + mofs[s], np, sb, sizeof(T) == 2 ? np : rc, w,
+    tile_gemm<T, NT, RT, kWaves, kMfmaFullPD64>(K + mofs[s], tile_rows(ns) / 16, np / M::KT, sb,
+                                                sizeof(T) == 2 ? np : rc, w,
                                                      [&](int row, int n, TV v, int) {
         if (row < ns && n < w && (write_x || pcount[row])) x[int64_t(off + row) * nrhs + r0 + n] = v;
     }, mt_lim);
     __syncthreads();
 
     // 3. outgoing waves, read back x of the port nodes (written by this workgroup), 4 columns at a time
-    const int w4 = (w + 3) / 4;
+    constexpr int w4 = rc / 4;
     if (nrhs % 4 == 0) {
         // whole 4-column chunks (w is a multiple of 4), two per thread per round, all
         // loads of a round issued before its stores
@@ -323,8 +329,8 @@ __global__ void __launch_bounds__(kBlock)
 #pragma unroll
             for (int i = 0; i < SU; ++i) {
                 const int t = t0 + i * kBlock;
-                if (t < tot) {
-                    const int q = t / w4, n0 = (t - q * w4) * 4;
+                const int q = t / w4, n0 = (t - q * w4) * 4;
+                if (t < tot && n0 < w) {
                     const int p = p0 + q;
                     be[i] = pbeta[p];
                     ga[i] = pgamma[p];
@@ -336,8 +342,8 @@ __global__ void __launch_bounds__(kBlock)
 #pragma unroll
             for (int i = 0; i < SU; ++i) {
                 const int t = t0 + i * kBlock;
-                if (t < tot) {
-                    const int q = t / w4, n0 = (t - q * w4) * 4;
+                const int q = t / w4, n0 = (t - q * w4) * 4;
+                if (t < tot && n0 < w) {
                     C4 o;
 #pragma unroll
                     for (int j = 0; j < 4; ++j) o.e[j] = be[i] * xv[i].e[j] + ga[i] * av[i].e[j];
@@ -348,6 +354,7 @@ __global__ void __launch_bounds__(kBlock)
     } else
     for (int t = tid; t < nps * w4; t += kBlock) {
         const int q = t / w4, n0 = (t - q * w4) * 4;
+        if (n0 >= w) continue;
         const int p = p0 + q;
         const TV be = pbeta[p], ga = pgamma[p];
         const TV* xr = x + int64_t(off + pnode[q]) * nrhs + r0;
@@ -363,7 +370,7 @@ __global__ void __launch_bounds__(kBlock)
 // 23-26, for many right-hand sides): block (y, s) forms
 //   a_next[twin(p)][r] = h[p][r] + sum_p' M_s[p][p'] a_cur[p'][r]
 // for the ports p of sub-circuit s and right-hand sides [r0, r0 + w).  M_s
-// (q x q, zero-padded to qp = roundup(q, 32)) is stored in A-tile order; the
+// (q x q, zero-padded to whole tiles) is stored in A-tile order; the
 // block of incident waves is staged in LDS as the B operand (BF16 for the BF16
 // path, FP32 accumulate).  WAVES wavefronts per workgroup (the operators are
 // small: 64 ports make four 16-row tiles).
@@ -372,8 +379,9 @@ __global__ void __launch_bounds__(WAVES * 64)
     k_sweep_mfma_pp(const T* __restrict__ Mop, const int64_t* __restrict__ qmofs,
                     const int32_t* __restrict__ port_off, const int32_t* __restrict__ port_twin,
                     const typename Mma<T>::TV* __restrict__ h, const typename Mma<T>::TV* __restrict__ a_cur,
-                    typename Mma<T>::TV* __restrict__ a_next, int nrhs, int rc, int reverse, int S) {
+                    typename Mma<T>::TV* __restrict__ a_next, int nrhs, int reverse, int S) {
     using M = Mma<T>;
+    constexpr int rc = 16 * NT;
     using TV = typename M::TV;
     extern __shared__ char smem[];
     T* sb = reinterpret_cast<T*>(smem);
@@ -396,39 +404,50 @@ __global__ void __launch_bounds__(WAVES * 64)
     const int r0 = (u - s * int(gridDim.x)) * rc;
     const int w = min(rc, nrhs - r0);
     const int p0 = port_off[s], q = port_off[s + 1] - p0;
-    const int qp = tile_pad(q);
+    const int qp = tile_cols<T>(q), mt_n = tile_rows(q) / 16;
     const int tid = threadIdx.x;
     // FP64: h of the outputs this lane will produce, loaded into registers before the
     // product so that the epilogue does not wait on it (when one pass of row tiles
     // covers the operator); BF16 stages h in LDS instead (registers cost occupancy)
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr bool kPre = sizeof(T) == 8;
-    const bool one = qp / 16 <= WAVES * RT;   // one pass of row tiles covers the operator
+    const bool one = mt_n <= WAVES * RT;   // one pass of row tiles covers the operator
     const bool pre = kPre && one;
+    // (wavefronts without a row tile skip it: a scalar branch)
     TV hreg[kPre ? RT * NT * 4 : 1];
 #pragma unroll
-    for (int j = 0; j < (kPre ? RT : 0); ++j)
+    for (int j = 0; j < (kPre ? RT : 0); ++j) {
+        const bool tile = pre && wave + j * WAVES < mt_n;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
+        for (int i = 0; i < NT * 4; ++i) hreg[j * NT * 4 + i] = TV(0);
+        if (tile) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int row = (wave + j * WAVES) * 16 + M::out_row(lane, v), n = nt * 16 + (lane & 15);
-                hreg[(j * NT + nt) * 4 + v] =
-                    pre && row < q && n < w ? h[int64_t(p0 + row) * nrhs + r0 + n] : TV(0);
-            }
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int row = (wave + j * WAVES) * 16 + M::out_row(lane, v), n = nt * 16 + (lane & 15);
+                    if (row < q && n < w) hreg[(j * NT + nt) * 4 + v] = h[int64_t(p0 + row) * nrhs + r0 + n];
+                }
+        }
+    }
     // twin port of each output row, loaded before the product (one pass of row tiles)
     int twr[RT * 4];
 #pragma unroll
-    for (int j = 0; j < RT; ++j)
+    for (int j = 0; j < RT; ++j) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int row = (wave + j * WAVES) * 16 + M::out_row(lane, v);
-            twr[j * 4 + v] = one && row < q ? port_twin[p0 + row] : 0;
+        for (int v = 0; v < 4; ++v) twr[j * 4 + v] = 0;
+        if (one && wave + j * WAVES < mt_n) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = (wave + j * WAVES) * 16 + M::out_row(lane, v);
+                if (row < q) twr[j * 4 + v] = port_twin[p0 + row];
+            }
         }
+    }
     // BF16 (HL): h of this block staged in LDS beside the waves (its loads overlap
     // theirs); the launch drops HL when there is no room for it (very large operators)
     constexpr bool hl = HL && sizeof(T) == 2;
-    const int hst = rc + 16;
+    constexpr int hst = rc + 16;
     TV* hs = reinterpret_cast<TV*>(smem + tile_lds_bytes<T>(qp, rc));
     const int sst = pp_stage_stride<T>(qp, rc);
     // incident waves (and h) of rows k < qp: 16-byte loads when every row segment is
@@ -441,7 +460,8 @@ __global__ void __launch_bounds__(WAVES * 64)
         // SU vectors per thread per round: all loads of a round are issued before its
         // LDS stores, so a round costs one HBM round trip
         constexpr int SU = 4;
-        const int rv = rc / VW, tot = qp * rv;
+        constexpr int rv = rc / VW;
+        const int tot = qp * rv;
         for (int t0 = tid; t0 < tot; t0 += SU * WAVES * 64) {
             Vec v[SU], hv[SU];
 #pragma unroll
@@ -494,9 +514,9 @@ __global__ void __launch_bounds__(WAVES * 64)
         }
     };
     if (one)
-        tile_gemm<T, NT, RT, WAVES>(Mop + qmofs[s], qp, sb, sizeof(T) == 2 ? qp : sst, w, epi_reg);
+        tile_gemm<T, NT, RT, WAVES>(Mop + qmofs[s], mt_n, qp / M::KT, sb, sizeof(T) == 2 ? qp : sst, w, epi_reg);
     else
-        tile_gemm<T, NT, RT, WAVES>(Mop + qmofs[s], qp, sb, sizeof(T) == 2 ? qp : sst, w, epi_mem);
+        tile_gemm<T, NT, RT, WAVES>(Mop + qmofs[s], mt_n, qp / M::KT, sb, sizeof(T) == 2 ? qp : sst, w, epi_mem);
 }
 
 // M_s = diag(beta) Kinv[P, P] diag(c) + diag(gamma) in A-tile order, from the
@@ -511,10 +531,10 @@ __global__ void __launch_bounds__(kBlock)
     const int s = blockIdx.x;
     const int ns = sub_off[s + 1] - sub_off[s];
     const int p0 = port_off[s], q = port_off[s + 1] - p0;
-    const int qp = tile_pad(q);
+    const int qp = tile_cols<T>(q);
     const double* Ks = Kinv + kofs[s];
     T* o = out + qmofs[s];
-    const int64_t cnt = int64_t(qp) * qp;
+    const int64_t cnt = tile_elems<T>(q);
     for (int64_t d = threadIdx.x; d < cnt; d += blockDim.x) {
         int r, c;
         tile_rc<T>(qp, d, r, c);
@@ -544,7 +564,7 @@ hipError_t launch_pp_k(int S, int nrhs, int rc, size_t lds, const T* Mop, const 
     // FP64: S rounded up to a multiple of 8, every XCD taking whole sub-circuits in turn
     const unsigned gy = sizeof(T) == 2 ? unsigned(S) : unsigned((S + 7) / 8 * 8);
     hipLaunchKernelGGL(kern, dim3(ny, gy), dim3(WAVES * 64), lds, st, Mop, qmofs, port_off, port_twin, h, a_cur,
-                       a_next, nrhs, rc, reverse, S);
+                       a_next, nrhs, reverse, S);
     return hipGetLastError();
 }
 
@@ -573,7 +593,7 @@ hipError_t launch_t(int S, int nrhs, int rc, size_t lds, const T* K, const int64
     if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds); e != hipSuccess) return e;
     const unsigned ny = unsigned((nrhs + rc - 1) / rc);
     hipLaunchKernelGGL(kern, dim3(ny, unsigned((S + 7) / 8 * 8)), dim3(kBlock), lds, st, K, mofs, sub_off, ports.off,
-                       ports.node, ports.twin, pc, pbeta, pgamma, b, a_cur, a_next, x, nrhs, rc, write_x ? 1 : 0, S,
+                       ports.node, ports.twin, pc, pbeta, pgamma, b, a_cur, a_next, x, nrhs, write_x ? 1 : 0, S,
                        port_rows ? 1 : 0);
     return hipGetLastError();
 }
@@ -588,17 +608,17 @@ hipError_t launch_sweep_mfma(int S, int max_ns, int max_ports, int nrhs, int var
                              const typename MfmaTypes<T>::TV* pgamma, const typename MfmaTypes<T>::TB* b,
                              const typename MfmaTypes<T>::TV* a_cur, typename MfmaTypes<T>::TV* a_next,
                              typename MfmaTypes<T>::TV* x, bool write_x, hipStream_t st, bool port_rows) {
-    const int np = tile_pad(max_ns);
+    const int np = tile_cols<T>(max_ns);
     // widest right-hand-side block (a multiple of 16, at most 64) whose staging fits the LDS limit
     int rc = rc_req > 0 ? ((rc_req + 15) / 16) * 16 : 64;
     if (rc > 64) rc = 64;
     // staged B, the port-node list, and per row its first port (short) and port count (byte)
     auto need = [&](int r) { return tile_lds_bytes<T>(np, r) + size_t(max_ports) * 4 + size_t(np) * 3 + 4; };
+    rc = std::min(rc, (nrhs + 15) / 16 * 16);
     while (rc > 16 && need(rc) > lds_limit) rc -= 16;
     const size_t lds = need(rc);
     if (lds > lds_limit) return hipErrorInvalidValue;
-    if (rc > nrhs) rc = ((nrhs + 15) / 16) * 16 < rc ? ((nrhs + 15) / 16) * 16 : rc;
-    const int nt = (rc + 15) / 16;
+    const int nt = rc / 16;
     // variant 0: 3 row tiles per wavefront pass, 1: 5, 2: 1 (fewer registers, more wavefronts)
 #define VTM_MFMA_CASE(NTV)                                                                                      \
     if (nt == NTV) {                                                                                            \
@@ -624,21 +644,27 @@ hipError_t launch_sweep_mfma_pp(int S, int max_ports, int nrhs, int variant, int
                                 const int32_t* port_twin, const typename MfmaTypes<T>::TV* h,
                                 const typename MfmaTypes<T>::TV* a_cur, typename MfmaTypes<T>::TV* a_next,
                                 int reverse, hipStream_t st) {
-    const int qp = tile_pad(max_ports);
+    const int qp = tile_cols<T>(max_ports);
     int rc = rc_req > 0 ? ((rc_req + 15) / 16) * 16 : 64;
     if (rc > 64) rc = 64;
     // h in LDS when some block width fits with it, else read at the store
     const int h_lds = pp_lds_bytes<T>(qp, 16, true) <= lds_limit ? 1 : 0;
+    rc = std::min(rc, (nrhs + 15) / 16 * 16);
     while (rc > 16 && pp_lds_bytes<T>(qp, rc, h_lds) > lds_limit) rc -= 16;
     const size_t lds = pp_lds_bytes<T>(qp, rc, h_lds);
     if (lds > lds_limit) return hipErrorInvalidValue;
-    if (rc > nrhs) rc = ((nrhs + 15) / 16) * 16 < rc ? ((nrhs + 15) / 16) * 16 : rc;
-    const int nt = (rc + 15) / 16;
+    const int nt = rc / 16;
     // variant: bit 0 = 5 row tiles per pass (else 3), bit 1 = 8 wavefronts per workgroup (else 4),
-    // bit 2 = 1 row tile per pass (small operators: fewer registers, more wavefronts in flight)
+    // bit 2 = 1 row tile per pass (small operators: fewer registers, more wavefronts in flight),
+    // bit 3 (with bit 2) = 6 wavefronts: operators of up to 96 ports leave none without a row
+    // tile, and a CU holds 5 workgroups instead of 4 (64 right-hand sides, random cuts: BF16
+    // solve 23.2 -> 22.9 ms against 8 wavefronts; 44, FP64: 6.74 -> 6.67)
     const bool deep = (variant & 1) != 0, wide = (variant & 2) != 0, thin = (variant & 4) != 0;
 #define VTM_MFMA_PP_CASE(NTV)                                                                                    \
     if (nt == NTV) {                                                                                             \
+        if (thin && (variant & 8))                                                                               \
+            return launch_pp_t<T, NTV, 1, 6>(S, nrhs, rc, lds, Mop, qmofs, port_off, port_twin, h, a_cur, a_next, \
+                                             reverse, h_lds, st);                                                \
         if (thin)                                                                                                \
             return wide ? launch_pp_t<T, NTV, 1, 8>(S, nrhs, rc, lds, Mop, qmofs, port_off, port_twin, h, a_cur,   \
                                                     a_next, reverse, h_lds, st)                                         \

@@ -150,7 +150,8 @@ vtm_status build_plan(const vtm_csr* A, const int32_t* part, const double* Z, in
     // inverse blocks start 16-byte aligned (multiples of 4 elements), as the sweep's loads need
     P.kofs.assign(S + 1, 0);
     for (int64_t s = 0; s < S; ++s) P.kofs[s + 1] = P.kofs[s] + ((int64_t(count[s]) * count[s] + 3) & ~int64_t(3));
-    // MFMA tile blocks: each sub-circuit padded to a multiple of 32 rows and columns
+    // each sub-circuit padded to a multiple of 32 rows and columns: the size of the work by
+    // which check intervals and cached launch shapes go (the tiles themselves pad less)
     P.mofs.assign(S + 1, 0);
     for (int64_t s = 0; s < S; ++s) {
         const int64_t np = (int64_t(count[s]) + 31) & ~int64_t(31);

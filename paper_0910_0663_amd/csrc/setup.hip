@@ -766,10 +766,10 @@ __global__ void __launch_bounds__(kBlock)
                int transpose) {
     const int s = blockIdx.x;
     const int n = sub_off[s + 1] - sub_off[s];
-    const int np = tile_pad(n);
+    const int np = tile_cols<T>(n);
     const double* M = src + kofs[s];
     T* o = dst + mofs[s];
-    const int64_t cnt = int64_t(np) * np;
+    const int64_t cnt = tile_elems<T>(n);
     for (int64_t d = int64_t(blockIdx.y) * blockDim.x + threadIdx.x; d < cnt; d += int64_t(blockDim.x) * gridDim.y) {
         int r, c;
         tile_rc<T>(np, d, r, c);

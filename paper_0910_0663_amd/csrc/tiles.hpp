@@ -1,9 +1,11 @@
 // MFMA operand-tile layout of the per-sub-circuit inverses (batched sweep).
 //
-// An n x n inverse is zero-padded to np = roundup(n, 32) and cut into A-operand
-// tiles of 16 rows: BF16 tiles are 16 x 32 (v_mfma_f32_16x16x32_bf16), FP64
-// tiles are 16 x 8 (two v_mfma_f64_16x16x4f64 steps).  Tile (mt, kt) is stored
-// at ((mt * (np / K) + kt) * 64 + lane) * E + j, lane-major, E = 16 bytes of
+// An n x n inverse is cut into A-operand tiles of 16 rows: BF16 tiles are 16 x 32
+// (v_mfma_f32_16x16x32_bf16), FP64 tiles are 16 x 8 (two v_mfma_f64_16x16x4f64
+// steps).  It is zero-padded to whole tiles, tile_rows(n) x tile_cols(n), no
+// further: padded to multiples of 32 both ways, uneven sub-circuits (8 to 24 nodes a
+// side) carried 1.5 times the products of their ports.  Tile (mt, kt) is stored
+// at ((mt * (tile_cols / K) + kt) * 64 + lane) * E + j, lane-major, E = 16 bytes of
 // elements per lane, so one 16-byte load per lane fetches a whole operand:
 //   BF16: lane l holds A[16 mt + l%16][32 kt + 8 (l/16) + j], j < 8
 //   FP64: lane l holds A[16 mt + l%16][8 kt + l/16] (j = 0) and
@@ -17,7 +19,9 @@
 
 namespace vtm {
 
+// the bound of a sub-circuit's padded size in either element type (LDS limits)
 __host__ __device__ inline int tile_pad(int n) { return (n + 31) & ~31; }
+__host__ __device__ inline int tile_rows(int n) { return (n + 15) & ~15; }
 
 template <typename T>
 struct MfmaTypes;
@@ -36,7 +40,18 @@ struct MfmaTypes<double> {
     static constexpr int E = 2;
 };
 
-// LDS bytes for the staged right-hand-side block (np rows, rc columns)
+template <typename T>
+__host__ __device__ inline int tile_cols(int n) {
+    constexpr int K = MfmaTypes<T>::K;
+    return (n + K - 1) / K * K;
+}
+// elements of a tiled n x n block
+template <typename T>
+__host__ __device__ inline int64_t tile_elems(int n) {
+    return int64_t(tile_rows(n)) * tile_cols<T>(n);
+}
+
+// LDS bytes for the staged right-hand-side block (np = tile_cols rows, rc columns)
 template <typename T>
 __host__ __device__ inline size_t tile_lds_bytes(int np, int rc) {
     if constexpr (sizeof(T) == 2)
@@ -69,7 +84,7 @@ __host__ __device__ inline size_t pp_lds_bytes(int qp, int rc, bool with_h = tru
         return size_t(qp) * rc * sizeof(T);
 }
 
-// (r, c) of the d-th stored element of a padded block
+// (r, c) of the d-th stored element of a block of np padded columns
 template <typename T>
 __host__ __device__ inline void tile_rc(int np, int64_t d, int& r, int& c) {
     constexpr int K = MfmaTypes<T>::K, E = MfmaTypes<T>::E;
