@@ -477,17 +477,17 @@ vtm_status sweep_once(vtm_handle h, bool low, int nrhs, const void* b, void* x, 
     } else if (pp && h->ppn) {
         const vtm::Plan& P = h->plan;
         if (!low)
-            VTM_HIP((vtm::launch_sweep_ppn<double, double>(int(P.S), P.max_npn, P.max_ports,
+            VTM_HIP((vtm::launch_sweep_ppn<double, double>(int(P.S), P.max_npn, P.max_ports, P.nofs[P.S] * 8,
                                                            adjoint && !P.symmetric ? h->N64T.p : h->N64.p, h->nofs.p,
                                                            h->pn_off.p, h->pn_pfirst.p, h->port_off.p, h->port_twin.p,
                                                            h->c64.p, h->beta64.p, h->gamma64.p, h->h64.p,
-                                                           h->a64[cur].p, h->a64[cur ^ 1].p, h->stream)));
+                                                           h->a64[cur].p, h->a64[cur ^ 1].p, cur, h->stream)));
         else
-            VTM_HIP((vtm::launch_sweep_ppn<float, float>(int(P.S), P.max_npn, P.max_ports,
+            VTM_HIP((vtm::launch_sweep_ppn<float, float>(int(P.S), P.max_npn, P.max_ports, P.nofs[P.S] * 4,
                                                          adjoint && !P.symmetric ? h->N32T.p : h->N32.p, h->nofs.p,
                                                          h->pn_off.p, h->pn_pfirst.p, h->port_off.p, h->port_twin.p,
                                                          h->c32.p, h->beta32.p, h->gamma32.p, h->h32.p,
-                                                         h->a32[cur].p, h->a32[cur ^ 1].p, h->stream)));
+                                                         h->a32[cur].p, h->a32[cur ^ 1].p, cur, h->stream)));
     } else if (pp && h->pps) {
         const vtm::Plan& P = h->plan;
         const double W = P.nwires ? P.wW[0] : 0.0;

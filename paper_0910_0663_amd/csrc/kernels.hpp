@@ -162,12 +162,13 @@ hipError_t launch_port_node_dense(int S, const int32_t* sub_off, const int64_t* 
                                   hipStream_t st);
 // ... and its sweep: t_n = sum_{p at n} c_p a_p, z = K^-1[N, N] t,
 // a_next[twin(p)] = beta_p z_n(p) + gamma_p a_p + h_p (LDS 2 max_npn values +
-// 4 max_ports bytes, at most 64 KiB, else hipErrorInvalidValue).
+// 4 max_ports bytes, at most 64 KiB, else hipErrorInvalidValue).  op_bytes: the
+// operators' size in all.  reverse as for launch_sweep_pps.
 template <typename TO, typename TV>
-hipError_t launch_sweep_ppn(int S, int max_npn, int max_ports, const TO* Sn, const int64_t* nofs,
+hipError_t launch_sweep_ppn(int S, int max_npn, int max_ports, int64_t op_bytes, const TO* Sn, const int64_t* nofs,
                             const int32_t* pn_off, const int32_t* pn_pfirst, const int32_t* port_off,
                             const int32_t* port_twin, const TV* pc, const TV* pbeta, const TV* pgamma, const TV* h,
-                            const TV* a_cur, TV* a_next, hipStream_t st);
+                            const TV* a_cur, TV* a_next, int reverse, hipStream_t st);
 
 // Symmetric A: upper triangle of S = K^-1[port nodes, port nodes] per
 // sub-circuit as row-interleaved pairs of diagonals (pair m from 2m (k - m + 1),

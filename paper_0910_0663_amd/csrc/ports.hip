@@ -90,14 +90,20 @@ __global__ void __launch_bounds__(kBlock)
     a_next[int64_t(port_twin[p]) * nrhs + r] = v;
 }
 
-template <typename T>
+typedef double pp_d2 __attribute__((ext_vector_type(2)));
+typedef float pp_f4 __attribute__((ext_vector_type(4)));
+
+// 16 bytes of operator entries (NT: non-temporal)
+template <typename T, bool NT = false>
 __device__ inline void load16p(const T* p, T (&v)[Group<T>::G]) {
     if constexpr (sizeof(T) == 8) {
-        const double2 w = *reinterpret_cast<const double2*>(p);
+        const pp_d2* q = reinterpret_cast<const pp_d2*>(p);
+        const pp_d2 w = NT ? __builtin_nontemporal_load(q) : *q;
         v[0] = w.x;
         v[1] = w.y;
     } else {
-        const float4 w = *reinterpret_cast<const float4*>(p);
+        const pp_f4* q = reinterpret_cast<const pp_f4*>(p);
+        const pp_f4 w = NT ? __builtin_nontemporal_load(q) : *q;
         v[0] = w.x;
         v[1] = w.y;
         v[2] = w.z;
@@ -290,20 +296,27 @@ __global__ void __launch_bounds__(kBlock)
     }
 }
 
-// One workgroup per sub-circuit, one port node (row of K^-1[N, N]) per thread.
+// One workgroup per sub-circuit, one port node (row of K^-1[N, N]) per thread.  Of
+// every 16 sub-circuits the first `keep` read their operators as usual and the others
+// non-temporally (launch_sweep_ppn).  Bound by HBM: 4,096 sub-circuits of 296 port nodes
+// in FP32 (1.44 GB) 255 us a sweep, 5.6 TB/s, with every operator read as usual in one
+// order; 247 with every other sweep backwards; 220, 6.5 TB/s, with 3 of 16 kept.
+// Non-temporal loads take no room in the 256 MB memory-side cache, so a kept share
+// that fits it is found there by every sweep; read as usual, a stream several times
+// its size leaves nothing of itself behind.
 template <typename TO, typename TV>
 __global__ void __launch_bounds__(512)
     k_sweep_ppn(const TO* __restrict__ Sn, const int64_t* __restrict__ nofs, const int32_t* __restrict__ pn_off,
                 const int32_t* __restrict__ pn_pfirst, const int32_t* __restrict__ port_off,
                 const int32_t* __restrict__ port_twin, const TV* __restrict__ pc, const TV* __restrict__ pbeta,
                 const TV* __restrict__ pgamma, const TV* __restrict__ h, const TV* __restrict__ a_cur,
-                TV* __restrict__ a_next, int max_npn) {
+                TV* __restrict__ a_next, int max_npn, int reverse, int keep) {
     constexpr int G = Group<TO>::G;
     extern __shared__ char smem[];
     TV* tv = reinterpret_cast<TV*>(smem);
     TV* zv = tv + max_npn;
     int32_t* pnode = reinterpret_cast<int32_t*>(zv + max_npn);
-    const int s = xcd_block(blockIdx.x, gridDim.x);
+    const int s = reverse ? xcd_block_reversed(blockIdx.x, gridDim.x) : xcd_block(blockIdx.x, gridDim.x);
     const int k0 = pn_off[s], k = pn_off[s + 1] - k0;
     const int p0 = port_off[s], p1 = port_off[s + 1];
     const int tid = threadIdx.x, bs = blockDim.x;
@@ -321,23 +334,29 @@ __global__ void __launch_bounds__(512)
     __syncthreads();
     // z = K^-1[N, N] t
     const int ng = k / G, full = ng * G;
-    for (int row = tid; row < k; row += bs) {
-        TV acc[G];
+    auto product = [&](auto nt) {
+        for (int row = tid; row < k; row += bs) {
+            TV acc[G];
 #pragma unroll
-        for (int j = 0; j < G; ++j) acc[j] = TV(0);
+            for (int j = 0; j < G; ++j) acc[j] = TV(0);
 #pragma unroll 4
-        for (int g = 0; g < ng; ++g) {
-            TO v[G];
-            load16p<TO>(Ss + (int64_t(g) * k + row) * G, v);
+            for (int g = 0; g < ng; ++g) {
+                TO v[G];
+                load16p<TO, decltype(nt)::value>(Ss + (int64_t(g) * k + row) * G, v);
 #pragma unroll
-            for (int j = 0; j < G; ++j) acc[j] += TV(v[j]) * tv[g * G + j];
+                for (int j = 0; j < G; ++j) acc[j] += TV(v[j]) * tv[g * G + j];
+            }
+            for (int c = full; c < k; ++c) acc[0] += TV(Ss[int64_t(full) * k + int64_t(c - full) * k + row]) * tv[c];
+            TV v = acc[0];
+#pragma unroll
+            for (int j = 1; j < G; ++j) v += acc[j];
+            zv[row] = v;
         }
-        for (int c = full; c < k; ++c) acc[0] += TV(Ss[int64_t(full) * k + int64_t(c - full) * k + row]) * tv[c];
-        TV v = acc[0];
-#pragma unroll
-        for (int j = 1; j < G; ++j) v += acc[j];
-        zv[row] = v;
-    }
+    };
+    if ((s & 15) < keep)
+        product(std::false_type{});
+    else
+        product(std::true_type{});
     __syncthreads();
     for (int p = p0 + tid; p < p1; p += bs)
         a_next[port_twin[p]] = pbeta[p] * zv[pnode[p - p0]] + pgamma[p] * a_cur[p] + h[p];
@@ -355,16 +374,22 @@ hipError_t launch_port_node_dense(int S, const int32_t* sub_off, const int64_t* 
 }
 
 template <typename TO, typename TV>
-hipError_t launch_sweep_ppn(int S, int max_npn, int max_ports, const TO* Sn, const int64_t* nofs,
+hipError_t launch_sweep_ppn(int S, int max_npn, int max_ports, int64_t op_bytes, const TO* Sn, const int64_t* nofs,
                             const int32_t* pn_off, const int32_t* pn_pfirst, const int32_t* port_off,
                             const int32_t* port_twin, const TV* pc, const TV* pbeta, const TV* pgamma, const TV* h,
-                            const TV* a_cur, TV* a_next, hipStream_t st) {
+                            const TV* a_cur, TV* a_next, int reverse, hipStream_t st) {
     const size_t lds = 2 * size_t(max_npn) * sizeof(TV) + size_t(max_ports) * 4;
     if (lds > 65536) return hipErrorInvalidValue;
+    // Up to twice the memory-side cache, plain loads in alternating order reuse more of it
+    // (358 MB: 30.9 ms a solve, 31.4 with the share that fits kept, 29.8 with none kept; 192
+    // MB: 17.2, and 21-23 with any non-temporal); above, the share that fits is kept (700 MB:
+    // 65.0 -> 58.7 ms, 59.5 with none kept; 1.44 GB: 144 -> 128, 133).
+    constexpr int64_t kCache = int64_t(256) << 20;
+    const int keep = op_bytes <= 2 * kCache ? 16 : std::max(1, int((16 * kCache + op_bytes / 2) / op_bytes));
     // one pass over the rows where possible
     const int bs = std::min(512, std::max(64, ((max_npn + 63) / 64) * 64));
     hipLaunchKernelGGL((k_sweep_ppn<TO, TV>), dim3(S), dim3(bs), lds, st, Sn, nofs, pn_off, pn_pfirst, port_off,
-                       port_twin, pc, pbeta, pgamma, h, a_cur, a_next, max_npn);
+                       port_twin, pc, pbeta, pgamma, h, a_cur, a_next, max_npn, reverse, keep);
     return hipGetLastError();
 }
 
@@ -374,14 +399,14 @@ template hipError_t launch_port_node_dense<double>(int, const int32_t*, const in
 template hipError_t launch_port_node_dense<float>(int, const int32_t*, const int64_t*, const int32_t*,
                                                   const int32_t*, const float*, const int64_t*, float*, bool,
                                                   hipStream_t);
-template hipError_t launch_sweep_ppn<double, double>(int, int, int, const double*, const int64_t*, const int32_t*,
+template hipError_t launch_sweep_ppn<double, double>(int, int, int, int64_t, const double*, const int64_t*, const int32_t*,
                                                      const int32_t*, const int32_t*, const int32_t*, const double*,
                                                      const double*, const double*, const double*, const double*,
-                                                     double*, hipStream_t);
-template hipError_t launch_sweep_ppn<float, float>(int, int, int, const float*, const int64_t*, const int32_t*,
+                                                     double*, int, hipStream_t);
+template hipError_t launch_sweep_ppn<float, float>(int, int, int, int64_t, const float*, const int64_t*, const int32_t*,
                                                    const int32_t*, const int32_t*, const int32_t*, const float*,
                                                    const float*, const float*, const float*, const float*, float*,
-                                                   hipStream_t);
+                                                   int, hipStream_t);
 
 template <typename TO>
 hipError_t launch_port_matrix(int S, const int32_t* sub_off, const int64_t* kofs, const int32_t* port_off,
