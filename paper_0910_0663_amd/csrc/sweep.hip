@@ -238,6 +238,99 @@ __global__ void __launch_bounds__(kBlock)
     }
 }
 
+// The single right-hand-side sweep of a few large sub-circuits in FP64: a workgroup of
+// KS wavefronts takes 64 rows of one sub-circuit, each wavefront every KS-th chunk of
+// the columns, and the partial sums meet in LDS in wavefront order.  With one wavefront
+// per 64 rows (k_sweep1) six sub-circuits of 2,000 nodes are 192 wavefronts, each with
+// two chunks in flight: 77 us for 180 MB of inverses (2.4 TB/s), bound by latency;
+// split eight ways 27 us (6.8 TB/s, from the memory-side cache).
+template <int CH, int KS>
+__global__ void __launch_bounds__(64 * KS)
+    k_sweep1_split(const double* __restrict__ K, const int64_t* __restrict__ kofs, const int32_t* __restrict__ sub_off,
+                   const int32_t* __restrict__ port_off, const int32_t* __restrict__ port_node,
+                   const int32_t* __restrict__ port_slot, const int32_t* __restrict__ port_twin,
+                   const double* __restrict__ pc, const double* __restrict__ pbeta, const double* __restrict__ pgamma,
+                   const double* __restrict__ b, const double* __restrict__ a_cur, double* __restrict__ a_next,
+                   double* __restrict__ x, int max_ns, int max_slot, int port_rows) {
+    constexpr int G = Group<double>::G;
+    extern __shared__ char smem[];
+    double* rhs = reinterpret_cast<double*>(smem);   // [max_ns]
+    double* part = rhs + max_ns;                     // [KS][64]
+    const int s = blockIdx.x;
+    const int off = sub_off[s];
+    const int ns = sub_off[s + 1] - off;
+    const int p0 = port_off[s], p1 = port_off[s + 1];
+    const int tid = threadIdx.x, bs = 64 * KS, lane = tid & 63, wave = tid >> 6;
+    // port_rows: as in k_sweep1
+    const int nrow = port_rows ? (p1 > p0 ? port_node[p1 - 1] + 1 : 0) : ns;
+    const int row0 = int(blockIdx.y) * 64;
+    if (row0 >= nrow) return;  // uniform over the workgroup
+    const int row = row0 + lane, rowc = min(row, ns - 1);
+    const double* Ks = K + kofs[s];
+    const int full = (ns / G) * G;
+    const int ngroups = full / G;
+    const int nch = (ngroups + CH - 1) / CH;
+    double buf[2][CH][G];
+    auto load_chunk = [&](double (&v)[CH][G], int ch) {
+#pragma unroll
+        for (int j = 0; j < CH; ++j) load16<double>(Ks + (int64_t(min(ch * CH + j, ngroups - 1)) * ns + rowc) * G, v[j]);
+    };
+    if (wave < nch) load_chunk(buf[0], wave);
+    for (int t = tid; t < ns; t += bs) rhs[t] = b[off + t];
+    __syncthreads();
+    for (int pb = p0; pb < p1; pb += bs) {
+        const int p = pb + tid;
+        const bool ok = p < p1;
+        const int node = ok ? port_node[p] : 0;
+        const int slot = ok ? port_slot[p] : -1;
+        const double c = ok ? pc[p] : 0.0;
+        const double a = ok ? a_cur[p] : 0.0;
+        for (int sl = 0; sl <= max_slot; ++sl) {
+            if (slot == sl) rhs[node] += c * a;
+            __syncthreads();
+        }
+    }
+    double acc[G];
+#pragma unroll
+    for (int q = 0; q < G; ++q) acc[q] = 0.0;
+    auto consume = [&](double (&v)[CH][G], int ch) {
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+            const int g = ch * CH + j;
+            if (g < ngroups) {  // wave-uniform
+#pragma unroll
+                for (int q = 0; q < G; ++q) acc[q] += v[j][q] * rhs[g * G + q];
+            }
+        }
+    };
+    for (int ch = wave; ch < nch; ch += 2 * KS) {
+        if (ch + KS < nch) load_chunk(buf[1], ch + KS);
+        consume(buf[0], ch);
+        if (ch + KS < nch) {
+            if (ch + 2 * KS < nch) load_chunk(buf[0], ch + 2 * KS);
+            consume(buf[1], ch + KS);
+        }
+    }
+    if (wave == KS - 1)
+        for (int c = full; c < ns; ++c) acc[0] += Ks[int64_t(full) * ns + int64_t(c - full) * ns + rowc] * rhs[c];
+    double v = acc[0];
+#pragma unroll
+    for (int q = 1; q < G; ++q) v += acc[q];
+    part[wave * 64 + lane] = v;
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+        for (int k = 1; k < KS; ++k) v += part[k * 64 + lane];
+        part[lane] = v;
+        if (row < nrow) x[off + row] = v;
+    }
+    __syncthreads();
+    for (int p = p0 + tid; p < p1; p += bs) {
+        const int i = port_node[p] - row0;
+        if (i >= 0 && i < 64) a_next[port_twin[p]] = pbeta[p] * part[i] + pgamma[p] * a_cur[p];
+    }
+}
+
 template <typename TO, typename TV, int R>
 hipError_t launch_r(int S, int max_ns, int nrhs, const TO* K, const int64_t* kofs, const int32_t* sub_off,
                     PortArrays ports, const TV* pc, const TV* pbeta, const TV* pgamma, const TV* b,
@@ -275,6 +368,20 @@ hipError_t launch_sweep(int S, int max_ns, int nrhs, const TO* K, const int64_t*
         const int ry = split ? (max_ns + bs - 1) / bs : 1;
         const size_t lds = size_t(xs_lds ? 2 : 1) * max_ns * sizeof(TV);
         constexpr int CH = kSweepChunk > 0 ? kSweepChunk : 1;
+        // FP64 with fewer row blocks than four a CU: their columns over KS wavefronts too
+        // (FP32 keeps its order of summation, which its inner solves' stops can depend on)
+        if constexpr (sizeof(TO) == 8) {
+            constexpr int KS = 8;
+            const size_t lds2 = (size_t(max_ns) + 64 * KS) * sizeof(TV);
+            if (split && int64_t(S) * ry <= 1024 && lds2 <= lds_limit) {
+                auto kern = k_sweep1_split<4, KS>;
+                if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds2); e != hipSuccess) return e;
+                hipLaunchKernelGGL(kern, dim3(S, ry), dim3(64 * KS), lds2, st, K, kofs, sub_off, ports.off, ports.node,
+                                   ports.slot, ports.twin, pc, pbeta, pgamma, b, a_cur, a_next, x, max_ns,
+                                   ports.max_slot, port_rows ? 1 : 0);
+                return hipGetLastError();
+            }
+        }
         if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(&k_sweep1<TO, TV, CH>), lds);
             e != hipSuccess)
             return e;
