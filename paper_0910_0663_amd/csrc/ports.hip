@@ -91,6 +91,7 @@ __global__ void __launch_bounds__(kBlock)
 }
 
 typedef double pp_d2 __attribute__((ext_vector_type(2)));
+typedef unsigned long long u64p;
 typedef float pp_f4 __attribute__((ext_vector_type(4)));
 
 // 16 bytes of operator entries (NT: non-temporal)
@@ -528,6 +529,9 @@ constexpr int kPpsChunk = 8;
 // chunks issued before the first barrier when two sub-circuits share a wavefront
 // (the rest stream that far ahead)
 constexpr int kPpsPre = 2;
+// the same in FP64 (pps_pair64): 1 to 4 chunks ahead make 22.6, 22.0, 21.2, 21.2 ms of
+// a 2048 x 2048 solve, and 5.58, 5.60, 5.36, 5.50 ms of one of 1000 x 1000
+constexpr int kPpsPre64 = 3;
 // wavefronts per sub-circuit when a sub-circuit has 33..64 port nodes (k_sweep_pps_split)
 constexpr int kPpsSplit = 8;
 
@@ -658,7 +662,118 @@ __device__ inline void pps_unit(int unit, int S, const TO* __restrict__ Sp, cons
     if (has_port) a_next[tw] = packed_wave_out<TV>(TV(2) * w * c, c, zv[hb + pnode[hb + r]], a, hp);
 }
 
-// One workgroup (one wavefront) per unit: a pair of sub-circuits when HALF.
+// v of the lane below (0 in lane 0): one shift of the wavefront
+__device__ inline double shift_up(double v) {
+    const u64p b = __builtin_bit_cast(u64p, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, int(unsigned(b)), 0x138, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, int(unsigned(b >> 32)), 0x138, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, u64p(unsigned(lo)) | (u64p(unsigned(hi)) << 32));
+}
+
+// The same in FP64, the lower triangle's products gathered by single-lane shifts: with
+// the diagonals taken from the last to the first, low = shift_up(low + S(r, r + d) t_r)
+// ends as sum_{d>0} S(r - d, r) t_{r-d}.  A shift is two register moves; a product
+// shuffled d lanes up goes through LDS twice, and those instructions bound the sweep of
+// operators that the memory-side cache holds (1000 x 1000 in 8x8 blocks, 70 MB: a solve
+// 6.62 -> 5.36 ms; 1500 x 1500, 158 MB: 12.1 -> 11.1).  Past that it is the stream of the
+// operators (2048 x 2048, 295 MB: 21.9 -> 21.2, 3000 x 3000: 53.3 -> 52.3), for which the
+// loads run one chunk further ahead.  They are range-checked buffer loads: a lane past the
+// end of a pair reads zeros, so that nothing of one sub-circuit is shifted into the other.
+// FP32 keeps the shuffles, and with them the order of its sums: its inner solves stop near
+// the rounding floor, where another order moves the sweep at which they stop.
+__device__ inline void pps_pair64(int unit, int S, const double* __restrict__ Sp, const int64_t* __restrict__ sofs,
+                                  const int32_t* __restrict__ pn_off, const int32_t* __restrict__ pn_pfirst,
+                                  const int32_t* __restrict__ port_off, const int32_t* __restrict__ port_twin,
+                                  const double* __restrict__ pc, const double* __restrict__ pW, double W,
+                                  const double* __restrict__ h, const double* __restrict__ a_cur,
+                                  double* __restrict__ a_next, double* ca, double* tv, double* zv, int32_t* pnode) {
+    constexpr int L = 32, CH = kPpsChunk, NCH = L / CH, PRE = kPpsPre64;
+    static_assert(L % CH == 0 && CH % 2 == 0 && PRE >= 1 && PRE <= NCH, "whole pairs in chunks that tile the lanes");
+    const int tid = threadIdx.x, r = tid % L, hb = tid - r, half = tid / L;
+    const int tb = half * 64;  // this sub-circuit's t region
+    // wave-uniform offsets of the two sub-circuits, indices clamped to S
+    const int sb = unit * 2;
+    const int sa = min(sb, S), sm = min(sb + 1, S), sz = min(sb + 2, S);
+    const int nA = pn_off[sa], nB = pn_off[sm], nC = pn_off[sz];
+    const int pA = port_off[sa], pB = port_off[sm], pC = port_off[sz];
+    const int64_t eA = sofs[sa], eB = sofs[sm], eC = sofs[sz];
+    const int n0 = half ? nB : nA, k = half ? nC - nB : nB - nA;
+    const int p0 = half ? pB : pA, q = half ? pC - pB : pB - pA;
+    const int kmax = max(nB - nA, nC - nB), top = (kmax + CH - 1) / CH;
+    // the two blocks are neighbours in memory: one resource over both
+    const __amdgpu_buffer_rsrc_t ops =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(Sp) + eA, 0, int(unsigned(eC - eA) * 8u), 0x00020000);
+    const unsigned blk = half ? unsigned(eB - eA) * 8u : 0u;
+    const bool has_port = r < q;
+    double c = 0.0, a = 0.0, hp = 0.0, w = W;
+    int tw = 0;
+    if (has_port) {
+        const int p = p0 + r;
+        c = pc[p];
+        a = a_cur[p];
+        hp = h[p];
+        tw = port_twin[p];
+        if (pW) w = pW[p];
+        ca[hb + r] = c * a;
+    }
+    int f0 = 0, f1 = 0;
+    if (r < k) f0 = pn_pfirst[n0 + r] - p0;
+    {
+        const int nx = __shfl(f0, tid + 1);  // lane r + 1's first port (the last lane: q)
+        f1 = r + 1 < k ? nx : q;
+    }
+    double buf[L];  // diagonal d of this lane's row (compile-time indices only)
+    auto load = [&](int ci) {
+#pragma unroll
+        for (int j = 0; j < CH / 2; ++j) {
+            const int m = ci * (CH / 2) + j;
+            const unsigned off = r + 2 * m < k ? blk + 8u * unsigned(pair_start(k, m) + 2 * r) : 0x80000000u;
+            const pp_d2 v2 = __builtin_bit_cast(pp_d2, __builtin_amdgcn_raw_buffer_load_b128(ops, int(off), 0, 0));
+            buf[2 * m] = v2.x;
+            buf[2 * m + 1] = v2.y;
+        }
+    };
+#pragma unroll
+    for (int ci = NCH - 1; ci >= 0; --ci)
+        if (ci < top && ci >= top - PRE) load(ci);
+    tv[tid] = 0.0;
+    tv[tid + 64] = 0.0;
+    __syncthreads();
+    // t_n = sum of c_p a_p over the ports at n, in port order
+    if (r < k) {
+        double acc = 0.0;
+        for (int i = f0; i < f1; ++i) {
+            acc += ca[hb + i];
+            pnode[hb + i] = r;
+        }
+        tv[tb + r] = acc;
+    }
+    __syncthreads();
+    // a t that is not finite makes every z of its sub-circuit so, and is kept out of the
+    // shifts: its products with the zeros past a pair's end would reach the other one
+    const double t = tv[tb + r];
+    const bool finite = __builtin_isfinite(t);
+    const bool lost = ((~__ballot(finite)) >> hb & 0xffffffffull) != 0;
+    const double tr = finite ? t : 0.0;
+    double acc = lost ? __builtin_nan("") : 0.0, low = 0.0;
+#pragma unroll
+    for (int ci = NCH - 1; ci >= 0; --ci) {
+        if (ci >= top) continue;  // scalar
+        if (ci >= PRE) load(ci - PRE);
+#pragma unroll
+        for (int j = CH - 1; j >= 0; --j) {
+            const int d = ci * CH + j;
+            acc += buf[d] * tv[tb + r + d];
+            if (d > 0) low = shift_up(low + buf[d] * tr);
+        }
+    }
+    if (r < k) zv[hb + r] = acc + low;
+    __syncthreads();
+    if (has_port) a_next[tw] = packed_wave_out<double>(2.0 * w * c, c, zv[hb + pnode[hb + r]], a, hp);
+}
+
+// One workgroup (one wavefront) per unit: a pair of sub-circuits when HALF (then FP64
+// takes pps_pair64).
 template <typename TO, typename TV, bool HALF>
 __global__ void __launch_bounds__(64)
     k_sweep_pps(int S, const TO* __restrict__ Sp, const int64_t* __restrict__ sofs,
@@ -672,8 +787,12 @@ __global__ void __launch_bounds__(64)
     // reads first are the ones the previous sweep read last (still in the
     // memory-side cache), while each XCD keeps the same units (and its L2)
     const int unit = reverse ? xcd_block_reversed(blockIdx.x, gridDim.x) : xcd_block(blockIdx.x, gridDim.x);
-    pps_unit<TO, TV, HALF>(unit, S, Sp, sofs, pn_off, pn_pfirst, port_off, port_twin, pc, pW, W, h, a_cur, a_next,
-                           ca, tv, zv, pnode);
+    if constexpr (HALF && sizeof(TO) == 8)
+        pps_pair64(unit, S, Sp, sofs, pn_off, pn_pfirst, port_off, port_twin, pc, pW, W, h, a_cur, a_next, ca, tv, zv,
+                   pnode);
+    else
+        pps_unit<TO, TV, HALF>(unit, S, Sp, sofs, pn_off, pn_pfirst, port_off, port_twin, pc, pW, W, h, a_cur, a_next,
+                               ca, tv, zv, pnode);
 }
 
 // One sub-circuit of up to 64 port nodes per workgroup of WV wavefronts: lane r of
