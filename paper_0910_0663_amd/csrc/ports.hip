@@ -363,6 +363,97 @@ __global__ void __launch_bounds__(512)
         a_next[port_twin[p]] = pbeta[p] * zv[pnode[p - p0]] + pgamma[p] * a_cur[p] + h[p];
 }
 
+// The same in FP64, 64 rows per workgroup: their columns spread over KS wavefronts, whose
+// partial sums meet in LDS.  Every row block of a sub-circuit forms all of t again.  One
+// workgroup per sub-circuit leaves a chip of 256 compute units with five wavefronts on
+// each of 210 of them (44 x 40 x 52 nodes in blocks of 8, 296 port nodes: 19.2 us a
+// sweep; here 18.1, 7.3 TB/s of 132 MB in the memory-side cache), or four loads in flight
+// a wavefront to a workgroup that waits for its slowest (96 x 90 x 92, 1 GB: a solve 107.7
+// -> 94.0 ms).  Six column pairs in flight keep the kernel under 64 registers, so four
+// workgroups share a compute unit; four and eight: 11.0 and 11.1 ms where six make 10.8.
+constexpr int kPpnSplit = 8, kPpnPairs = 6;  // wavefronts, column pairs in flight in each
+template <int KS, int CH>
+__global__ void __launch_bounds__(64 * KS)
+    k_sweep_ppn_split(int ry, const double* __restrict__ Sn, const int64_t* __restrict__ nofs,
+                      const int32_t* __restrict__ pn_off, const int32_t* __restrict__ pn_pfirst,
+                      const int32_t* __restrict__ port_off, const int32_t* __restrict__ port_twin,
+                      const double* __restrict__ pc, const double* __restrict__ pbeta,
+                      const double* __restrict__ pgamma, const double* __restrict__ h,
+                      const double* __restrict__ a_cur, double* __restrict__ a_next, int max_npn, int reverse,
+                      int keep) {
+    extern __shared__ char smem[];
+    double* tv = reinterpret_cast<double*>(smem);
+    double* part = tv + max_npn;
+    int32_t* pnode = reinterpret_cast<int32_t*>(part + 64 * KS);
+    const int unit = reverse ? xcd_block_reversed(blockIdx.x, gridDim.x) : xcd_block(blockIdx.x, gridDim.x);
+    const int s = unit / ry, row0 = (unit - s * ry) * 64;
+    const int k0 = pn_off[s], k = pn_off[s + 1] - k0;
+    if (row0 >= k) return;
+    const int p0 = port_off[s];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row = row0 + lane, rowc = min(row, k - 1);
+    const double* Ss = Sn + nofs[s];
+    const int ng = k / 2;  // whole column pairs; this wavefront takes wave, wave + KS, ...
+    double v[CH][2];
+    auto product = [&](auto nt) {
+        auto load = [&](int g, double (&u)[2]) {
+            if (g < ng) load16p<double, decltype(nt)::value>(Ss + (int64_t(g) * k + rowc) * 2, u);
+        };
+#pragma unroll
+        for (int i = 0; i < CH; ++i) load(wave + KS * i, v[i]);
+        // this block's ports, one per thread
+        const int b0 = pn_pfirst[k0 + row0], b1 = pn_pfirst[k0 + min(row0 + 64, k)];
+        const int pb = b0 + tid;
+        double beta = 0.0, rest = 0.0;
+        int twin = 0;
+        if (pb < b1) {
+            beta = pbeta[pb];
+            rest = pgamma[pb] * a_cur[pb] + h[pb];
+            twin = port_twin[pb];
+        }
+        // t per port node, in port order
+        for (int j = tid; j < k; j += 64 * KS) {
+            const int f0 = pn_pfirst[k0 + j], f1 = pn_pfirst[k0 + j + 1];
+            double acc = 0.0;
+            for (int p = f0; p < f1; ++p) {
+                acc += pc[p] * a_cur[p];
+                pnode[p - p0] = j - row0;
+            }
+            tv[j] = acc;
+        }
+        __syncthreads();
+        double acc0 = 0.0, acc1 = 0.0;
+        for (int g0 = wave; g0 < ng; g0 += KS * CH) {
+#pragma unroll
+            for (int i = 0; i < CH; ++i) {
+                const int g = g0 + KS * i;
+                if (g < ng) {
+                    acc0 += v[i][0] * tv[2 * g];
+                    acc1 += v[i][1] * tv[2 * g + 1];
+                }
+                load(g + KS * CH, v[i]);
+            }
+        }
+        if ((k & 1) && wave == KS - 1) acc0 += Ss[int64_t(2 * ng) * k + rowc] * tv[k - 1];
+        part[wave * 64 + lane] = acc0 + acc1;
+        __syncthreads();
+        auto z = [&](int p) {
+            const int r = pnode[p - p0];
+            double v2 = 0.0;
+#pragma unroll
+            for (int w = 0; w < KS; ++w) v2 += part[w * 64 + r];
+            return v2;
+        };
+        if (pb < b1) a_next[twin] = beta * z(pb) + rest;
+        for (int p = pb + 64 * KS; p < b1; p += 64 * KS)
+            a_next[port_twin[p]] = pbeta[p] * z(p) + (pgamma[p] * a_cur[p] + h[p]);
+    };
+    if ((s & 15) < keep)
+        product(std::false_type{});
+    else
+        product(std::true_type{});
+}
+
 }  // namespace
 
 template <typename TO>
@@ -387,6 +478,21 @@ hipError_t launch_sweep_ppn(int S, int max_npn, int max_ports, int64_t op_bytes,
     // 65.0 -> 58.7 ms, 59.5 with none kept; 1.44 GB: 144 -> 128, 133).
     constexpr int64_t kCache = int64_t(256) << 20;
     const int keep = op_bytes <= 2 * kCache ? 16 : std::max(1, int((16 * kCache + op_bytes / 2) / op_bytes));
+    // FP64: rows and columns of a sub-circuit spread out, where a column's wavefronts have
+    // enough of it or the sub-circuits alone do not fill the chip (solves, one workgroup per
+    // sub-circuit / spread: 105 of 296 port nodes 11.0 / 7.2 ms, 512 of 98 8.6 / 6.7, 1,728 of
+    // 98 21.4 / 23.9, 1,764 of 92 5.1 / 5.5, 961 of 124 5.37 / 5.18, 1,000 of 152 20.2 / 19.1).
+    // FP32 keeps the order of its sums: its inner solves stop near the rounding floor.
+    if constexpr (sizeof(TO) == 8) {
+        const int64_t ry = (max_npn + 63) / 64;
+        const size_t need = (size_t(max_npn) + 64 * kPpnSplit) * 8 + size_t(max_ports) * 4;
+        if ((max_npn > 112 || (max_npn > 64 && S <= 512)) && S * ry <= INT32_MAX && need <= 65536) {
+            hipLaunchKernelGGL((k_sweep_ppn_split<kPpnSplit, kPpnPairs>), dim3(unsigned(S * ry)), dim3(64 * kPpnSplit),
+                               need, st, int(ry), Sn, nofs, pn_off, pn_pfirst, port_off, port_twin, pc, pbeta, pgamma,
+                               h, a_cur, a_next, max_npn, reverse, keep);
+            return hipGetLastError();
+        }
+    }
     // one pass over the rows where possible
     const int bs = std::min(512, std::max(64, ((max_npn + 63) / 64) * 64));
     hipLaunchKernelGGL((k_sweep_ppn<TO, TV>), dim3(S), dim3(bs), lds, st, Sn, nofs, pn_off, pn_pfirst, port_off,
