@@ -802,7 +802,7 @@ vtm_status run_resident(vtm_handle h, const vtm::ResidentControl& ctl, bool adjo
     h->res_state->stop = vtm::kAborted;
     h->res_state->timeout = 0;
     lost = false;
-    const hipError_t e = vtm::launch_resident<T>(a, P.max_ports, h->stream);
+    const hipError_t e = vtm::launch_resident<T>(a, P.max_npn, P.max_ports, h->stream);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         h->resident = false;
@@ -1648,8 +1648,8 @@ static vtm_status setup_from_plan(std::unique_ptr<vtm_handle_s> h, vtm_handle* o
     // resident runs: the port-node forms on cut branches, when every workgroup fits the
     // device at once
     if ((h->pps || h->ppn) && !P.vertex) {
-        const int blocks = fp64 ? vtm::resident_blocks<double>(int(P.S), P.max_ports, h->pps)
-                                : vtm::resident_blocks<float>(int(P.S), P.max_ports, h->pps);
+        const int blocks = fp64 ? vtm::resident_blocks<double>(int(P.S), P.max_npn, P.max_ports, h->pps)
+                                : vtm::resident_blocks<float>(int(P.S), P.max_npn, P.max_ports, h->pps);
         if (blocks > 0) {
             const size_t words =
                 fp64 ? vtm::resident_slot_words<double>(P.nports) : vtm::resident_slot_words<float>(P.nports);

@@ -258,6 +258,67 @@ __device__ __forceinline__ void control(const ResidentArgs<T>& A, unsigned n) {
     }
 }
 
+// One check of a sweeping workgroup: its sum of squares of the port residual is sent,
+// and next_s becomes the sweeps until the next check.  A thread of the first `waves`
+// wavefronts that is an owner holds port p, the entry base + row of first, cnt, xs and
+// vs.  False: a wait ran out.
+//
+// The residual from port quantities: with o and an the waves that left and
+// arrived in this sweep, x_i = (o - gamma a) / beta on this side of a wire and
+// x_j = (an - gamma o_prev) / beta on the other (both ends share the wire's
+// coefficients; the twin's incoming wave was this port's previous one).
+template <typename T>
+__device__ __forceinline__ bool residual_check(const ResidentArgs<T>& A, unsigned nb, bool owner, int p, int base,
+                                               int row, T o, T a, T an, T o_prev, double* xs, double* vs, double* red,
+                                               int waves, const int32_t* first, const int32_t* cnt, int& bad,
+                                               unsigned& next_s, unsigned tag, unsigned abort_tag) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    u64* const decision = A.sums + 2 * size_t(nb);
+    double be64 = 1.0, ga64 = 0.0;
+    if (owner) {
+        be64 = A.beta64[p];
+        ga64 = A.gamma64[p];
+        xs[base + row] = (double(o) - ga64 * double(a)) / be64;
+    }
+    __syncthreads();
+    if (bad) return false;
+    if (owner) {
+        const double xj = (double(an) - ga64 * double(o_prev)) / be64;
+        vs[base + row] = A.gd[p] * xs[base + first[base + row]] + A.g[p] * xj - A.c64[p] * double(a);
+    }
+    __syncthreads();
+    double rr = 0.0;
+    if (owner && first[base + row] == row) {
+        double r = 0.0;
+        for (int i = 0; i < cnt[base + row]; ++i) r += vs[base + row + i];
+        rr = r * r;
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) rr += __shfl_xor(rr, d);
+    if (lane == 0) red[wave] = rr;
+    __syncthreads();
+    if (tid == 0) {
+        rr = red[0];
+        for (int v = 1; v < waves; ++v) rr += red[v];
+        send(A.sums + 2 * size_t(blockIdx.x), rr, tag);
+    }
+    if (wave == 0) {
+        unsigned nx = 0;
+        const bool ok = wait_for(
+            true,
+            [&] {
+                const u64 v = word_load(decision);
+                nx = unsigned(v);
+                return unsigned(v >> 32) == tag;
+            },
+            decision + 1, abort_tag, A.wait_ticks);
+        if (!ok) bad = A.state->timeout = 1;
+        next_s = nx;
+    }
+    __syncthreads();
+    return !bad;
+}
+
 // staged t of one sub-circuit: rows of zeros before and after it
 template <int QB>
 constexpr int kSpan = 3 * (QB <= 32 ? 32 : 64);
@@ -458,55 +519,9 @@ __global__ void __launch_bounds__(64 * Shape<QB>::RG * Shape<QB>::CG, Shape<QB>:
                 bad = st->timeout = 1;
         }
         if (--left == 0) {
-            // the residual from port quantities: with o and an the waves that left and
-            // arrived in this sweep, x_i = (o - gamma a) / beta on this side of a wire and
-            // x_j = (an - gamma o_prev) / beta on the other (both ends share the wire's
-            // coefficients; the twin's incoming wave was this port's previous one)
-            double be64 = 1.0, ga64 = 0.0;
-            if (owner) {
-                be64 = A.beta64[p];
-                ga64 = A.gamma64[p];
-                xs[base + row] = (double(o) - ga64 * double(a)) / be64;
-            }
-            __syncthreads();
-            if (bad) return;
-            if (owner) {
-                const double xj = (double(an) - ga64 * double(o_prev)) / be64;
-                vs[base + row] = A.gd[p] * xs[base + first[base + row]] + A.g[p] * xj - A.c64[p] * double(a);
-            }
-            __syncthreads();
-            double rr = 0.0;
-            if (owner && first[base + row] == row) {
-                double r = 0.0;
-                for (int i = 0; i < cnt[base + row]; ++i) r += vs[base + row + i];
-                rr = r * r;
-            }
-#pragma unroll
-            for (int d = 32; d > 0; d >>= 1) rr += __shfl_xor(rr, d);
-            if (lane == 0) red[wave] = rr;
-            __syncthreads();
-            if (tid == 0) {
-                rr = red[0];
-#pragma unroll
-                for (int v = 1; v < RG; ++v) rr += red[v];
-                send(A.sums + 2 * size_t(blockIdx.x), rr, tag);
-            }
-            if (wave == 0) {
-                unsigned nx = 0;
-                const u64* const slot = A.sums + 2 * size_t(nb);
-                const bool ok = wait_for(
-                    true,
-                    [&] {
-                        const u64 v = word_load(slot);
-                        nx = unsigned(v);
-                        return unsigned(v >> 32) == tag;
-                    },
-                    abort_word, abort_tag, A.wait_ticks);
-                if (!ok) bad = st->timeout = 1;
-                next_s = nx;
-            }
-            __syncthreads();
-            if (bad) return;
+            if (!residual_check(A, nb, owner, p, base, row, o, a, an, o_prev, xs, vs, red, RG, first, cnt, bad, next_s,
+                                tag, abort_tag))
+                return;
             left = next_s;
             if (left == 0) {
                 if (owner) {
@@ -523,20 +538,233 @@ __global__ void __launch_bounds__(64 * Shape<QB>::RG * Shape<QB>::CG, Shape<QB>:
     }
 }
 
-template <typename T, int QB>
-int blocks_of(int S) {
-    using Sh = Shape<QB>;
+// Larger sub-circuits, FP64: up to 64 RG port nodes and 512 ports, a compute unit each.
+// Rows are port nodes; wavefront w takes the column pairs w, w + 8, ..., whose entries
+// of every row lane it keeps: the first REG of them in registers, the next LDS ones in
+// LDS, and the last STREAM (RG = 5 only) are read every sweep, forwards and backwards in
+// turn so that the XCD's L2, which stays warm inside a launch, holds most of them.  As a
+// launch a sweep reads every operator from the memory-side cache.  Solves, a launch per
+// sweep and resident: 210 sub-circuits of 296 port nodes (44x40x52) 10.8 -> 4.7 ms, 7.2 us
+// a sweep for 18; 105 of them 7.2 -> 3.6; 216 of 218 (42x42x42 in blocks of 7) 9.9 -> 2.8;
+// 64 of 196 (400x400 in blocks of 50) 1.95 -> 1.28.  Eight pairs in registers: nine spill.
+template <int RG>
+struct Wide {
+    static constexpr int PAIRS = 4 * RG;  // 32 RG column pairs over eight wavefronts
+    static constexpr int REG = RG >= 5 ? 8 : RG == 4 ? 12 : PAIRS;
+    static constexpr int LDS = RG >= 5 ? 3 : PAIRS - REG;
+    static constexpr int STREAM = PAIRS - REG - LDS;
+};
+constexpr int kWidePorts = 512, kWideRows = 5;
+
+template <int RG>
+__global__ void __launch_bounds__(512, 2) k_resident_wide(ResidentArgs<double> A) {
+    const unsigned nb = gridDim.x - 1;
+    if (blockIdx.x == nb) {
+        control<double>(A, nb);
+        return;
+    }
+    using Wd = Wide<RG>;
+    constexpr int PAIRS = Wd::PAIRS, REG = Wd::REG, LP = Wd::LDS, ST = Wd::STREAM, ROWS = 64 * RG;
+    constexpr int AHEAD = ST > 0 ? 2 : 1;
+    __shared__ double2 keep[LP > 0 ? LP * RG * 512 : 1];
+    __shared__ double part[8 * ROWS < 2 * kWidePorts ? 2 * kWidePorts : 8 * ROWS];
+    __shared__ alignas(16) double tv[16 * PAIRS];
+    __shared__ double ca[kWidePorts], red[8];
+    __shared__ int32_t node[kWidePorts], first[kWidePorts], cnt[kWidePorts];
+    __shared__ int bad;
+    __shared__ unsigned next_s;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int s = xcd_block(blockIdx.x, nb);
+    const int p0 = A.port_off[s], q = A.port_off[s + 1] - p0;
+    const int k0 = A.pn_off[s], k = A.pn_off[s + 1] - k0;
+    const int pairs = (k + 1) >> 1;
+    const bool owner = tid < q;
+    int p = p0 + tid;
+    u64* const abort_word = A.sums + 2 * size_t(nb) + 1;
+    const __amdgpu_buffer_rsrc_t slots =
+        __builtin_amdgcn_make_buffer_rsrc(A.slots, 0, int(unsigned(A.nports) * 32u), 0x00020000);
+    // the operator, range-checked: rows past the last one read what follows, or zeros
+    const __amdgpu_buffer_rsrc_t ops =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(A.op) + A.ofs[s], 0, k * k * 8, 0x00020000);
+
+    if (tid == 0) bad = 0;
+    for (int j = tid; j < 16 * PAIRS; j += 512) tv[j] = 0.0;
+    // this thread's port node, and the ports of each node
+    int f0 = 0, f1 = 0;
+    if (tid < k) {
+        f0 = A.pn_pfirst[k0 + tid] - p0;
+        f1 = A.pn_pfirst[k0 + tid + 1] - p0;
+        for (int i = f0; i < f1; ++i) {
+            node[i] = tid;
+            first[i] = f0;
+            cnt[i] = f1 - f0;
+        }
+    }
+    // entries of this lane's rows in column pair g (wave-uniform): zeros past the operator;
+    // a last single column comes with what follows it, which meets a zero of tv
+    auto entries = [&](int g, double2 (&v)[RG]) {
+        const bool whole = 2 * g + 1 < k;
+        const unsigned vo = 2 * g < k ? unsigned(lane * (whole ? 16 : 8)) + unsigned(g * k * 16) : 0x80000000u;
+#pragma unroll
+        for (int rg = 0; rg < RG; ++rg)
+            v[rg] = __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(
+                                                    ops, int(vo + unsigned(rg * (whole ? 1024 : 512))), 0, 0));
+    };
+    double2 op[REG][RG];
+#pragma unroll
+    for (int i = 0; i < REG; ++i) entries(wave + 8 * i, op[i]);
+    if constexpr (LP > 0)
+        for (int i = 0; i < LP; ++i) {
+            double2 v[RG];
+            entries(wave + 8 * (REG + i), v);
+#pragma unroll
+            for (int rg = 0; rg < RG; ++rg) keep[(i * RG + rg) * 512 + tid] = v[rg];
+        }
+    // the streamed pairs of this wavefront, and those of them that are there
+    const int count = ST > 0 ? max(0, min(ST, (pairs - wave - 8 * (REG + LP) + 7) >> 3)) : 0;
+    double2 sv[AHEAD][RG];
+    auto stream = [&](int e, bool back, double2 (&buf)[RG]) {
+        if (e < count) entries(wave + 8 * (REG + LP + (back ? count - 1 - e : e)), buf);  // wave-uniform
+    };
+    // (the port's coefficients are read anew every sweep: their registers would displace op's)
+    double a = 0.0, o = 0.0, o_prev = 0.0, an = 0.0;
+    int tw = 0;
+    if (owner) {
+        tw = A.port_twin[p];
+        a = A.a[A.cur][p];
+        o_prev = A.a[A.cur][tw];
+    }
+    unsigned left = unsigned(A.ctl.first);
+    unsigned tag = A.epoch;
+    const unsigned abort_tag = A.epoch + 1;
+    if constexpr (ST > 0) {
+#pragma unroll
+        for (int e = 0; e < AHEAD; ++e) stream(e, (tag + 1) & 1, sv[e]);
+    }
+
+    while (true) {
+        ++tag;
+        const unsigned set = (tag & 1) ? unsigned(A.nports) : 0u;
+        asm volatile("" : "+v"(p));  // or the addresses of all its coefficients are kept, too
+        if (owner) ca[tid] = A.c[p] * a;
+        __syncthreads();
+        if (bad) return;
+        if (tid < k) {
+            double t = 0.0;
+            for (int i = f0; i < f1; ++i) t += ca[i];
+            tv[tid] = t;
+        }
+        __syncthreads();
+        double acc[RG];
+#pragma unroll
+        for (int rg = 0; rg < RG; ++rg) acc[rg] = 0.0;
+        auto pair = [&](int g) { return *reinterpret_cast<const double2*>(tv + 2 * g); };
+#pragma unroll
+        for (int i = 0; i < REG; ++i) {
+            const double2 t = pair(wave + 8 * i);
+#pragma unroll
+            for (int rg = 0; rg < RG; ++rg) acc[rg] = fma(op[i][rg].y, t.y, fma(op[i][rg].x, t.x, acc[rg]));
+            // bounds the staged values read ahead (their registers would displace op's)
+            if (i % 2 == 1) asm volatile("" : "+v"(acc[0]) : : "memory");
+        }
+#pragma unroll
+        for (int i = 0; i < LP; ++i) {
+            const double2 t = pair(wave + 8 * (REG + i));
+#pragma unroll
+            for (int rg = 0; rg < RG; ++rg) {
+                const double2 v = keep[(i * RG + rg) * 512 + tid];
+                acc[rg] = fma(v.y, t.y, fma(v.x, t.x, acc[rg]));
+            }
+            asm volatile("" : "+v"(acc[0]) : : "memory");
+        }
+        if constexpr (ST > 0) {
+            const bool back = tag & 1;
+            for (int e0 = 0; e0 < count; e0 += AHEAD) {
+#pragma unroll
+                for (int e = 0; e < AHEAD; ++e) {
+                    if (e0 + e >= count) continue;  // wave-uniform
+                    const double2 t = pair(wave + 8 * (REG + LP + (back ? count - 1 - e0 - e : e0 + e)));
+#pragma unroll
+                    for (int rg = 0; rg < RG; ++rg) acc[rg] = fma(sv[e][rg].y, t.y, fma(sv[e][rg].x, t.x, acc[rg]));
+                    stream(e0 + e + AHEAD, back, sv[e]);
+                }
+            }
+        }
+#pragma unroll
+        for (int rg = 0; rg < RG; ++rg) part[wave * ROWS + rg * 64 + lane] = acc[rg];
+        double be = 0.0, rest = 0.0;
+        if (owner) {
+            be = A.beta[p];
+            rest = A.gamma[p] * a + A.h[p];
+        }
+        __syncthreads();
+        if (owner) {
+            const int n = node[tid];
+            double z = 0.0;
+#pragma unroll
+            for (int w = 0; w < 8; ++w) z += part[w * ROWS + n];
+            o = be * z + rest;
+            send(slots, set + unsigned(tw), o, tag);
+        }
+        // the next sweep's first streamed pairs are on their way while the waves are
+        if constexpr (ST > 0) {
+#pragma unroll
+            for (int e = 0; e < AHEAD; ++e) stream(e, (tag + 1) & 1, sv[e]);
+        }
+        if (!wait_for(owner, [&] { return receive(slots, set + unsigned(p), tag, an); }, abort_word, abort_tag,
+                      A.wait_ticks))
+            bad = A.state->timeout = 1;
+        if (--left == 0) {
+            __syncthreads();  // part's sums are read before the check takes its place
+            if (!residual_check(A, nb, owner, p, 0, tid, o, a, an, o_prev, part, part + kWidePorts, red, 8, first, cnt,
+                                bad, next_s, tag, abort_tag))
+                return;
+            left = next_s;
+            if (left == 0) {
+                if (owner) {
+                    // the last sweep read buffer cur when the run had an odd number of sweeps
+                    const int in = (A.cur + int((tag - A.epoch - 1) & 1)) & 1;
+                    A.a[in][p] = a;
+                    A.a[in ^ 1][p] = an;
+                }
+                return;
+            }
+        }
+        o_prev = o;
+        a = an;
+    }
+}
+
+// workgroups of `kernel` (threads each) that the current device holds at once, at most
+// `blocks` and the controlling one: blocks or 0
+int fitting(const void* kernel, int threads, int64_t blocks) {
     int dev = 0, cus = 0, coop = 0, per = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, reinterpret_cast<const void*>(&k_resident<T, QB>),
-                                                     64 * Sh::RG * Sh::CG, 0) != hipSuccess) {
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, 0) != hipSuccess) {
         (void)hipGetLastError();
         return 0;
     }
-    const int64_t blocks = (int64_t(S) + Sh::SUBS - 1) / Sh::SUBS;
-    return blocks < int64_t(per) * cus ? int(blocks) : 0;  // and the controlling one
+    return blocks < int64_t(per) * cus ? int(blocks) : 0;
+}
+
+const void* wide_kernel(int max_npn) {
+    switch ((max_npn + 63) / 64) {
+        case 0:
+        case 1:
+        case 2: return reinterpret_cast<const void*>(&k_resident_wide<2>);
+        case 3: return reinterpret_cast<const void*>(&k_resident_wide<3>);
+        case 4: return reinterpret_cast<const void*>(&k_resident_wide<4>);
+        default: return reinterpret_cast<const void*>(&k_resident_wide<5>);
+    }
+}
+
+template <typename T, int QB>
+int blocks_of(int S) {
+    using Sh = Shape<QB>;
+    return fitting(reinterpret_cast<const void*>(&k_resident<T, QB>), 64 * Sh::RG * Sh::CG,
+                   (int64_t(S) + Sh::SUBS - 1) / Sh::SUBS);
 }
 
 template <typename T, int QB>
@@ -552,12 +780,16 @@ hipError_t launch_q(const ResidentArgs<T>& args, hipStream_t st) {
 }  // namespace
 
 template <typename T>
-int resident_blocks(int S, int max_ports, bool packed) {
-    if (S < 1 || max_ports > 128) return 0;
+int resident_blocks(int S, int max_npn, int max_ports, bool packed) {
+    if (S < 1) return 0;
     if constexpr (sizeof(T) == 4) {
         if (!packed || max_ports > 64) return 0;
         return max_ports <= 32 ? blocks_of<T, 32>(S) : blocks_of<T, 64>(S);
     } else {
+        if (max_ports > 128) {
+            if (packed || max_ports > kWidePorts || max_npn > 64 * kWideRows) return 0;
+            return fitting(wide_kernel(max_npn), 512, S);
+        }
         return max_ports <= 32   ? blocks_of<T, 32>(S)
                : max_ports <= 64 ? blocks_of<T, 64>(S)
                : max_ports <= 96 ? blocks_of<T, 96>(S)
@@ -566,12 +798,19 @@ int resident_blocks(int S, int max_ports, bool packed) {
 }
 
 template <typename T>
-hipError_t launch_resident(const ResidentArgs<T>& args, int max_ports, hipStream_t st) {
-    if (args.S < 1 || max_ports > 128) return hipErrorInvalidValue;
+hipError_t launch_resident(const ResidentArgs<T>& args, int max_npn, int max_ports, hipStream_t st) {
+    if (args.S < 1) return hipErrorInvalidValue;
     if constexpr (sizeof(T) == 4) {
         if (!args.packed || max_ports > 64) return hipErrorInvalidValue;
         return max_ports <= 32 ? launch_q<T, 32>(args, st) : launch_q<T, 64>(args, st);
     } else {
+        if (max_ports > 128) {
+            if (args.packed || max_ports > kWidePorts || max_npn > 64 * kWideRows) return hipErrorInvalidValue;
+            ResidentArgs<T> a = args;
+            void* params[] = {&a};
+            return hipLaunchCooperativeKernel(wide_kernel(max_npn), dim3(unsigned(args.S) + 1), dim3(512), params, 0,
+                                              st);
+        }
         return max_ports <= 32   ? launch_q<T, 32>(args, st)
                : max_ports <= 64 ? launch_q<T, 64>(args, st)
                : max_ports <= 96 ? launch_q<T, 96>(args, st)
@@ -579,9 +818,9 @@ hipError_t launch_resident(const ResidentArgs<T>& args, int max_ports, hipStream
     }
 }
 
-template int resident_blocks<double>(int, int, bool);
-template int resident_blocks<float>(int, int, bool);
-template hipError_t launch_resident<double>(const ResidentArgs<double>&, int, hipStream_t);
-template hipError_t launch_resident<float>(const ResidentArgs<float>&, int, hipStream_t);
+template int resident_blocks<double>(int, int, int, bool);
+template int resident_blocks<float>(int, int, int, bool);
+template hipError_t launch_resident<double>(const ResidentArgs<double>&, int, int, hipStream_t);
+template hipError_t launch_resident<float>(const ResidentArgs<float>&, int, int, hipStream_t);
 
 }  // namespace vtm

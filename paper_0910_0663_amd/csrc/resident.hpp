@@ -112,14 +112,15 @@ inline size_t resident_slot_words(int64_t nports) {
 }
 
 // Sweeping workgroups of a run, 0 when it cannot run resident: some sub-circuit has more
-// than 128 ports (FP32: more than 64, or the operators are not packed), or the current
-// device cannot hold every workgroup at once.
+// than 128 ports (FP64, dense operators: more than 512, or 320 port nodes; FP32: more than
+// 64, or the operators are not packed), or the current device cannot hold every workgroup
+// at once.
 template <typename T>
-int resident_blocks(int S, int max_ports, bool packed);
+int resident_blocks(int S, int max_npn, int max_ports, bool packed);
 
 // One run.  hipErrorCooperativeLaunchTooLarge (or another launch error) leaves
 // everything as it was.
 template <typename T>
-hipError_t launch_resident(const ResidentArgs<T>& args, int max_ports, hipStream_t st);
+hipError_t launch_resident(const ResidentArgs<T>& args, int max_npn, int max_ports, hipStream_t st);
 
 }  // namespace vtm

@@ -21,12 +21,12 @@ def torch():
 
 
 # port nodes of the largest sub-circuit: 65 (a last row block of one row, an odd column),
-# 81, 113 and 129 (one row past two blocks), 144, 218 and 260 with up to three ports a
-# node; one, several and ragged sub-circuits, fewer column pairs than a wavefront's first
-# loads and several times as many; both directions of an unsymmetric A
+# 81, 113, 129 (one row past two blocks), 218, 260 and 271, with one to three ports a node;
+# several and ragged sub-circuits, fewer column pairs than a wavefront's first loads and
+# several times as many; both directions of an unsymmetric A
 @pytest.mark.parametrize("cfg,dims,block,k", [
-    (2, (65, 130), (65, 65), 65), (3, (9, 9, 18), (9, 9, 9), 81), (2, (113, 14), (113, 7), 113),
-    (2, (129, 20), (129, 10), 129), (3, (12, 12, 24), (12, 12, 12), 144), (3, (17, 16, 18), (8, 8, 8), 260),
+    (2, (66, 66), (33, 33), 65), (2, (82, 82), (41, 41), 81), (2, (114, 114), (57, 57), 113),
+    (2, (130, 130), (65, 65), 129), (3, (20, 20, 20), (10, 10, 10), 271), (3, (17, 16, 18), (8, 8, 8), 260),
     (3, (21, 22, 20), (7, 7, 7), 218),
 ])
 def test_iterates(torch, cfg, dims, block, k):

@@ -72,7 +72,7 @@ def iterate(torch, w, k, resident, adjoint=False, **kw):
     (2, dict(dims=(72, 72), block=(24, 24)), True, False),
     (2, dict(dims=(75, 60), block=(25, 25)), True, False),
     (2, dict(dims=(96, 96), block=(32, 32)), True, False),
-    (2, dict(dims=(99, 99), block=(33, 33)), False, False),
+    (2, dict(dims=(99, 99), block=(33, 33)), True, False),
     (3, dict(dims=(9, 10, 12), block=(3, 3, 3)), True, False),
     (3, dict(dims=(12, 12, 13), block=(4, 4, 4)), True, False),
     (4, dict(dims=(100, 90)), True, False),
