@@ -313,9 +313,10 @@ vtm_status vtm_vertex_sca(const vtm_csr *A, const int32_t *label, const int32_t 
  *
  * One right-hand side on a small circuit torn at branches runs resident: when
  * every sub-circuit has at most 512 ports, on at most 320 nodes (FP32: 64 ports,
- * symmetric A), and the device holds all of them at once, the port-to-port sweeps and checks of a solve (of an
- * inner solve when refining) are one cooperative launch.  Same sweeps, checks and
- * residual history.  opt.timing runs a launch per sweep.
+ * symmetric A), and the device holds all of them at once, the port-to-port sweeps
+ * and checks of a solve (of an inner solve when refining) are one cooperative
+ * launch.  Same sweeps, checks and residual history.  opt.timing runs a launch per
+ * sweep.
  *
  * A zero column converges at once with x = 0.  With a refining precision the
  * sweeps run in FP32/BF16 on A d = r and x += d, r = b - A x in FP64, until

@@ -259,7 +259,7 @@ using Clock = std::chrono::steady_clock;
 
 // FP64 residual of x against b (both [n][nrhs] renumbered): launches the
 // residual and the copy of its per-column sums into pinned host memory.  With
-// transpose set the residual is taken on A^T (the adjoint system).
+// transpose set the residual is taken on A^T (the adjoint system).  x null: of x = 0.
 template <typename TX>
 vtm_status residual_launch(vtm_handle h, const double* b, const TX* x, int nrhs, double* r_out, bool transpose,
                            float* r32 = nullptr, __bf16* r16 = nullptr) {
@@ -270,9 +270,10 @@ vtm_status residual_launch(vtm_handle h, const double* b, const TX* x, int nrhs,
         const int no = int(P.n_orig);
         const double* bo = b == h->bp.p ? h->bo.p : h->ro.p;
         const bool oT = transpose && !P.osymmetric;  // the adjoint's residual is on A^T
-        VTM_HIP(vtm::launch_restrict<TX>(no, nrhs, h->vr0.p, h->vr1.p, x, h->xo.p, false, h->stream));
+        if (x) VTM_HIP(vtm::launch_restrict<TX>(no, nrhs, h->vr0.p, h->vr1.p, x, h->xo.p, false, h->stream));
         VTM_HIP(vtm::launch_residual<double>(no, nrhs, oT ? h->orowT.p : h->orow.p, oT ? h->ocolT.p : h->ocol.p,
-                                             oT ? h->ovalT.p : h->oval.p, bo, h->xo.p, r_out ? h->ro.p : nullptr,
+                                             oT ? h->ovalT.p : h->oval.p, bo, x ? h->xo.p : nullptr,
+                                             r_out ? h->ro.p : nullptr,
                                              nullptr, nullptr, h->red_partial, h->red_norms, h->stream));
         if (r_out)
             VTM_HIP(vtm::launch_expand(int(P.n), nrhs, no, h->vx_src.p, h->vx_w.p, h->ro.p, false, r_out, h->stream));
@@ -288,14 +289,28 @@ vtm_status residual_launch(vtm_handle h, const double* b, const TX* x, int nrhs,
     return VTM_OK;
 }
 
-// waits for the stream, then relres per column from the copied sums
-vtm_status residual_finish(vtm_handle h, int nrhs, std::vector<double>& rel) {
-    VTM_HIP(hipStreamSynchronize(h->stream));
+// relres per column from the copied sums (the stream has been waited for)
+void residual_read(vtm_handle h, int nrhs, std::vector<double>& rel) {
     rel.resize(nrhs);
     for (int r = 0; r < nrhs; ++r) {
         const double rr = h->h_norms[2 * r], bb = h->h_norms[2 * r + 1];
         rel[r] = bb > 0.0 ? std::sqrt(rr / bb) : std::sqrt(rr);
     }
+}
+
+vtm_status residual_finish(vtm_handle h, int nrhs, std::vector<double>& rel) {
+    VTM_HIP(hipStreamSynchronize(h->stream));
+    residual_read(h, nrhs, rel);
+    return VTM_OK;
+}
+
+// x, permuted, to the caller's vector
+vtm_status write_x(vtm_handle h, int nrhs, double* x) {
+    const vtm::Plan& P = h->plan;
+    if (P.vertex)
+        VTM_HIP(vtm::launch_restrict<double>(int(P.n_orig), nrhs, h->vr0.p, h->vr1.p, h->xp.p, x, true, h->stream));
+    else
+        VTM_HIP(vtm::launch_scatter(int(P.n), nrhs, h->iperm.p, h->xp.p, x, h->stream));
     return VTM_OK;
 }
 
@@ -345,6 +360,7 @@ struct IterOut {
     int64_t launches = 0;
     double pp_ms = 0.0;      // port-to-port sweeps (opt.timing)
     int64_t pp_launches = 0;
+    bool written = false;    // the caller's x holds the final iterate
     std::vector<double> rel;
     vtm_status status = VTM_OK;
     // residual history: max over columns of the relative residual at each check of a
@@ -763,7 +779,8 @@ bool can_reside(vtm_handle h, int nrhs, bool iface) {
 // h->res_state and cur moved on; `lost` set (and the handle back to a launch per
 // sweep) when a wait ran out or the launch was refused: the waves are then gone.
 template <typename T>
-vtm_status run_resident(vtm_handle h, const vtm::ResidentControl& ctl, bool adjoint, int& cur, bool& lost) {
+vtm_status run_resident(vtm_handle h, const vtm::ResidentControl& ctl, bool adjoint, int& cur, bool& lost,
+                        const double* bb = nullptr) {
     const vtm::Plan& P = h->plan;
     const bool kt = adjoint && !P.symmetric;
     const int64_t words = int64_t(vtm::resident_slot_words<T>(P.nports));
@@ -775,6 +792,7 @@ vtm_status run_resident(vtm_handle h, const vtm::ResidentControl& ctl, bool adjo
     }
     vtm::ResidentArgs<T> a{};
     a.ctl = ctl;
+    a.bb = bb;
     a.S = int(P.S);
     a.nports = P.nports;
     a.packed = h->pps ? 1 : 0;
@@ -827,8 +845,9 @@ int64_t graph_length(vtm_handle h, int64_t k) {
     return h->opt.use_graph ? vtm::graph_length(h->opt.check_every, k) : k;
 }
 
-// Plain FP64 VTM on (bp -> xp).  Waves start at zero unless resume is set.
-vtm_status run_fp64(vtm_handle h, int nrhs, double tol, bool adjoint, bool resume, IterOut& out) {
+// Plain FP64 VTM on (bp -> xp, and the caller's x when out.written).  Waves start at
+// zero unless resume is set.
+vtm_status run_fp64(vtm_handle h, int nrhs, double tol, bool adjoint, bool resume, double* x, IterOut& out) {
     const vtm::Plan& P = h->plan;
     const int64_t np = P.nports * nrhs;
     vtm::Cadence cad;
@@ -836,30 +855,57 @@ vtm_status run_fp64(vtm_handle h, int nrhs, double tol, bool adjoint, bool resum
     cad.adaptive = h->opt.adaptive_checks != 0;
     int cur = 0;
     if (!resume) VTM_HIP(vtm::launch_fill<double>(np, 0.0, h->a64[0].p, h->stream));
-    VTM_HIP(vtm::launch_fill<double>(P.n * nrhs, 0.0, h->xp.p, h->stream));
-    // x^0 = 0: the check before any sweep (b = 0 converges at once)
-    vtm_status st = residual<double>(h, h->bp.p, h->xp.p, nrhs, nullptr, out.rel, adjoint);
-    if (st != VTM_OK) return st;
-    ++out.checks;
-    out.record();
     auto done = [&](const std::vector<double>& rel) {
         for (double v : rel)
             if (!(v <= tol)) return false;
         return true;
     };
-    if (done(out.rel)) return VTM_OK;
-    if (!resume) cad.record(0, max_of(out.rel));
-    std::vector<double> bb(nrhs);  // ||b||^2 per right-hand side, for the port-residual checks
-    for (int r = 0; r < nrhs; ++r) bb[r] = h->h_norms[2 * r + 1];
     const bool pp = has_pp(h, nrhs, adjoint) && !resume;
     // port-to-port sweeps check the residual from port quantities; once it passes
     // (and at the end), x^k is rebuilt by a full sweep from the same waves and
     // the residual on A decides
     const bool iface = pp && !P.vertex;  // the port identity holds for cut branches only
+    // x^0 = 0: the check before any sweep (b = 0 converges at once).  Its relative
+    // residual is 1 unless b is zero or not finite, so a solve that starts resident goes
+    // ahead without waiting for it (a round trip, 30 us): the run takes ||b||^2 from where
+    // the sums land, and what b is shows after it.  (b = 0: its waves are all zero.)
+    bool ahead = can_reside(h, nrhs, iface) && tol < 1.0 &&
+                 std::min<int64_t>(graph_length(h, cad.next(tol)), h->opt.max_sweeps) > 1;
+    vtm_status st = residual_launch<double>(h, h->bp.p, nullptr, nrhs, nullptr, adjoint);
+    if (st != VTM_OK) return st;
+    std::vector<double> bb(nrhs);  // ||b||^2 per right-hand side, for the port-residual checks
+    auto start_check = [&]() {
+        residual_read(h, nrhs, out.rel);
+        ++out.checks;
+        out.record();
+        for (int r = 0; r < nrhs; ++r) bb[r] = h->h_norms[2 * r + 1];
+    };
+    if (ahead) {
+        cad.record(0, 1.0);
+    } else {
+        VTM_HIP(hipStreamSynchronize(h->stream));
+        start_check();
+        if (done(out.rel)) {
+            VTM_HIP(vtm::launch_fill<double>(P.n * nrhs, 0.0, h->xp.p, h->stream));
+            return VTM_OK;
+        }
+        if (!resume) cad.record(0, max_of(out.rel));
+    }
+    // x is on its way to the caller, and the waves to buffer 0, while the host waits for
+    // the residual that nearly always ends the solve
+    bool moved = false;
     auto rebuild = [&]() -> vtm_status {
         vtm_status s2 = sweep_once(h, false, nrhs, h->bp.p, h->xp.p, cur ^ 1, adjoint, true, false);
         if (s2 != VTM_OK) return s2;
-        if ((s2 = residual<double>(h, h->bp.p, h->xp.p, nrhs, nullptr, out.rel, adjoint)) != VTM_OK) return s2;
+        if ((s2 = residual_launch<double>(h, h->bp.p, h->xp.p, nrhs, nullptr, adjoint)) != VTM_OK) return s2;
+        if ((s2 = write_x(h, nrhs, x)) != VTM_OK) return s2;
+        out.written = true;
+        // (at the sweep limit a second rebuild may follow, from buffer 0 as it is)
+        moved = cur == 1 && out.sweeps < h->opt.max_sweeps;
+        if (moved)
+            VTM_HIP(hipMemcpyAsync(h->a64[0].p, h->a64[1].p, sizeof(double) * np, hipMemcpyDeviceToDevice,
+                                   h->stream));
+        if ((s2 = residual_finish(h, nrhs, out.rel)) != VTM_OK) return s2;
         ++out.checks;
         out.record();
         return timing_collect(h, out);
@@ -886,9 +932,19 @@ vtm_status run_fp64(vtm_handle h, int nrhs, double tol, bool adjoint, bool resum
                 ctl.first = chunk - 1;
             }
             bool lost = false;
-            if ((st = run_resident<double>(h, ctl, adjoint, cur, lost)) != VTM_OK) return st;
-            if (lost) return run_fp64(h, nrhs, tol, adjoint, resume, out = IterOut{});
+            if ((st = run_resident<double>(h, ctl, adjoint, cur, lost, ahead ? h->red_norms + 1 : nullptr)) != VTM_OK)
+                return st;
+            if (lost) return run_fp64(h, nrhs, tol, adjoint, resume, x, out = IterOut{});
             const vtm::ResidentState& r = *h->res_state;
+            if (ahead) {
+                ahead = false;
+                start_check();
+                if (done(out.rel)) {
+                    VTM_HIP(vtm::launch_fill<double>(np, 0.0, h->a64[0].p, h->stream));
+                    VTM_HIP(vtm::launch_fill<double>(P.n, 0.0, h->xp.p, h->stream));
+                    return VTM_OK;
+                }
+            }
             for (int k = 0; k < r.hist_len; ++k) {
                 out.rel[0] = r.hist[k];
                 out.sweeps = r.hist_sweeps[k];
@@ -928,7 +984,7 @@ vtm_status run_fp64(vtm_handle h, int nrhs, double tol, bool adjoint, bool resum
         cad.record(out.sweeps, max_of(out.rel));
     }
     // leave the latest waves in buffer 0 for export / resume
-    if (cur == 1)
+    if (cur == 1 && !moved)
         VTM_HIP(hipMemcpyAsync(h->a64[0].p, h->a64[1].p, sizeof(double) * np, hipMemcpyDeviceToDevice,
                                h->stream));
     return VTM_OK;
@@ -977,13 +1033,15 @@ double inner_reach(const vtm_handle_s* h, int nrhs, bool pp) {
     return c > 1.0 ? 0.9 : 0.5;
 }
 
-vtm_status run_refine(vtm_handle h, int nrhs, double tol, bool adjoint, IterOut& out) {
+vtm_status run_refine(vtm_handle h, int nrhs, double tol, bool adjoint, double* x, IterOut& out) {
     const vtm::Plan& P = h->plan;
     const int64_t nv = P.n * nrhs, np = P.nports * nrhs;
     double drop = h->opt.inner_drop;
     if (!(drop > 0.0)) drop = h->opt.precision == VTM_BF16_REFINE ? 1e-2 : 1e-5;
-    VTM_HIP(vtm::launch_fill<double>(nv, 0.0, h->xp.p, h->stream));
     std::vector<double> rel, e, target(nrhs);
+    // x goes to the caller before the host waits for its residual where that costs less
+    // than the round trip (30 us) it hides when the residual ends the solve
+    const bool early = nv <= (int64_t(1) << 20);
     const bool pp = has_pp(h, nrhs, adjoint);
     auto all_le = [](const std::vector<double>& v, const std::vector<double>& t) {
         for (size_t i = 0; i < v.size(); ++i)
@@ -1000,22 +1058,31 @@ vtm_status run_refine(vtm_handle h, int nrhs, double tol, bool adjoint, IterOut&
     for (int outer = 0;; ++outer) {
         // r = b - A x (FP64) and its BF16 or FP32 copy (the inner right-hand side),
         // written by the same pass
-        vtm_status st = residual<double>(h, h->bp.p, h->xp.p, nrhs, iface ? nullptr : h->rp.p, rel, adjoint,
-                                         h->tiles ? nullptr : h->b32.p, h->tiles ? h->b16.p : nullptr);
+        vtm_status st =
+            residual_launch<double>(h, h->bp.p, outer ? h->xp.p : nullptr, nrhs, iface ? nullptr : h->rp.p, adjoint,
+                                    h->tiles ? nullptr : h->b32.p, h->tiles ? h->b16.p : nullptr);
         if (st != VTM_OK) return st;
+        if (outer && early) {
+            if ((st = write_x(h, nrhs, x)) != VTM_OK) return st;
+            out.written = true;
+        }
+        if ((st = residual_finish(h, nrhs, rel)) != VTM_OK) return st;
         ++out.checks;
         out.rel = rel;
         out.record();
+        bool ends = all_le(rel, std::vector<double>(nrhs, tol));
+        if (!ends && outer >= h->opt.max_outer) {
+            ends = true;
+            out.status = VTM_E_MAXITER;
+        }
         for (double v : rel)
             if (!std::isfinite(v) || v > h->opt.divergence) {
+                ends = true;
                 out.status = VTM_E_DIVERGED;
-                return VTM_OK;
             }
-        if (all_le(rel, std::vector<double>(nrhs, tol))) return VTM_OK;
-        if (outer >= h->opt.max_outer) {
-            out.status = VTM_E_MAXITER;
-            return VTM_OK;
-        }
+        // (x = 0 is written only when it is the result: the first correction replaces it)
+        if (outer == 0 && ends) VTM_HIP(vtm::launch_fill<double>(nv, 0.0, h->xp.p, h->stream));
+        if (ends) return VTM_OK;
         // inner target relative to ||r||: enough for the outer tolerance, at most drop
         for (int r = 0; r < nrhs; ++r) target[r] = rel[r] > 0.0 ? std::max(drop, 0.5 * tol / rel[r]) : 1.0;
         std::vector<double> rr(nrhs);  // ||r||^2 per right-hand side, for the port-residual inner checks
@@ -1059,7 +1126,7 @@ vtm_status run_refine(vtm_handle h, int nrhs, double tol, bool adjoint, IterOut&
             }
             bool lost = false;
             if ((st = run_resident<float>(h, ctl, adjoint, cur, lost)) != VTM_OK) return st;
-            if (lost) return run_refine(h, nrhs, tol, adjoint, out = IterOut{});
+            if (lost) return run_refine(h, nrhs, tol, adjoint, x, out = IterOut{});
             const vtm::ResidentState& r = *h->res_state;
             inner = r.ctl.sweeps;
             out.checks += r.checks;
@@ -1069,6 +1136,7 @@ vtm_status run_refine(vtm_handle h, int nrhs, double tol, bool adjoint, IterOut&
             if (r.stop == vtm::kBad) {
                 out.sweeps += inner;
                 out.status = VTM_E_DIVERGED;
+                if (outer == 0) VTM_HIP(vtm::launch_fill<double>(nv, 0.0, h->xp.p, h->stream));
                 return VTM_OK;
             }
             if (r.stop != vtm::kMore) {
@@ -1098,6 +1166,7 @@ vtm_status run_refine(vtm_handle h, int nrhs, double tol, bool adjoint, IterOut&
             if (bad) {
                 out.sweeps += inner;
                 out.status = VTM_E_DIVERGED;
+                if (outer == 0) VTM_HIP(vtm::launch_fill<double>(nv, 0.0, h->xp.p, h->stream));
                 return VTM_OK;
             }
             since = improved ? 0 : since + 1;
@@ -1111,7 +1180,7 @@ vtm_status run_refine(vtm_handle h, int nrhs, double tol, bool adjoint, IterOut&
                 return st;
             if ((st = timing_collect(h, out)) != VTM_OK) return st;
         }
-        VTM_HIP(vtm::launch_add<float>(nv, h->d32.p, h->xp.p, h->stream));
+        VTM_HIP(vtm::launch_add<float>(nv, h->d32.p, h->xp.p, outer == 0, h->stream));
         ++out.outer;
     }
 }
@@ -1137,16 +1206,13 @@ vtm_status solve_common(vtm_handle h, const double* b, double* x, int32_t nrhs, 
     IterOut out;
     vtm_status st;
     if (h->opt.precision == VTM_FP64) {
-        st = run_fp64(h, nrhs, tol, adjoint, h->waves_set, out);
+        st = run_fp64(h, nrhs, tol, adjoint, h->waves_set, x, out);
     } else {
-        st = run_refine(h, nrhs, tol, adjoint, out);
+        st = run_refine(h, nrhs, tol, adjoint, x, out);
     }
     h->waves_set = false;
     if (st != VTM_OK) return st;
-    if (P.vertex)
-        VTM_HIP(vtm::launch_restrict<double>(int(P.n_orig), nrhs, h->vr0.p, h->vr1.p, h->xp.p, x, true, h->stream));
-    else
-        VTM_HIP(vtm::launch_scatter(int(P.n), nrhs, h->iperm.p, h->xp.p, x, h->stream));
+    if (!out.written && (st = write_x(h, nrhs, x)) != VTM_OK) return st;
     VTM_HIP(hipStreamSynchronize(h->stream));
     if (rep) {
         rep->sweeps = out.sweeps;

@@ -230,7 +230,7 @@ inline int resid_blocks(int64_t rows, int nrhs) {
     const int64_t b = rows * nrhs / 4096;
     return int(b < 1024 ? 1024 : (b > kResidBlocks ? kResidBlocks : b));
 }
-// r_out (FP64), r32 (FP32) and r16 (BF16) are optional copies of r = b - A x
+// r_out (FP64), r32 (FP32) and r16 (BF16) are optional copies of r = b - A x; x null: x = 0
 template <typename TX>
 hipError_t launch_residual(int n, int nrhs, const int32_t* rowptr, const int32_t* col,
                            const double* val, const double* b, const TX* x, double* r_out, float* r32,
@@ -256,9 +256,9 @@ hipError_t launch_fill(int64_t count, T value, T* dst, hipStream_t st);
 // dst = (TD) src
 template <typename TS, typename TD>
 hipError_t launch_convert(int64_t count, const TS* src, TD* dst, hipStream_t st);
-// x += (double) d
+// x += (double) d; fresh: x = (double) d
 template <typename TD>
-hipError_t launch_add(int64_t count, const TD* d, double* x, hipStream_t st);
+hipError_t launch_add(int64_t count, const TD* d, double* x, bool fresh, hipStream_t st);
 // out[r][q] = a[abi2port[q]][r] (get) or a[abi2port[q]][r] = in[r][q] (set)
 template <typename TV>
 hipError_t launch_waves_io(int64_t np, int nrhs, const int32_t* abi2port, TV* a, double* abi,

@@ -176,6 +176,7 @@ __device__ __forceinline__ void control(const ResidentArgs<T>& A, unsigned n) {
     u64* const abort_word = decision + 1;
     ResidentState* const st = A.state;
     ResidentControl ctl = A.ctl;
+    if (A.bb) ctl.bb = *A.bb;
     int checks = 0, hist = 0;
     unsigned tag = A.epoch, run = unsigned(ctl.first);
     if (tid == 0) bad = 0;

@@ -61,7 +61,7 @@ struct ResidentControl {
     Cadence cad;
     double tol = 0.0;         // target of the relative residual
     double divergence = 0.0;  // above this (or not finite) the run ends as kBad
-    double bb = 0.0;          // the residual's denominator, squared
+    double bb = 0.0;          // the residual's denominator, squared (unless ResidentArgs::bb is set)
     int64_t sweeps = 0, max_sweeps = 0;
     int64_t first = 1;        // sweeps before the first check
     int32_t inner = 0;        // inner solve of a refinement: ends at the target or when two checks in a
@@ -87,6 +87,7 @@ struct ResidentState {
 template <typename T>
 struct ResidentArgs {
     ResidentControl ctl;
+    const double* bb;            // null, or where an earlier launch on the stream leaves ctl.bb
     int S;
     int64_t nports;
     const T* op;                 // packed triangles (packed) or column-group k x k blocks

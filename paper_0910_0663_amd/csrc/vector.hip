@@ -131,9 +131,9 @@ __global__ void k_convert<float, double>(int64_t count, const float* __restrict_
 }
 
 template <typename TD>
-__global__ void k_add(int64_t count, const TD* __restrict__ d, double* __restrict__ x) {
+__global__ void k_add(int64_t count, const TD* __restrict__ d, double* __restrict__ x, int fresh) {
     const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t < count) x[t] += double(d[t]);
+    if (t < count) x[t] = (fresh ? 0.0 : x[t]) + double(d[t]);
 }
 
 template <typename TV>
@@ -259,9 +259,9 @@ hipError_t launch_convert(int64_t count, const TS* src, TD* dst, hipStream_t st)
 }
 
 template <typename TD>
-hipError_t launch_add(int64_t count, const TD* d, double* x, hipStream_t st) {
+hipError_t launch_add(int64_t count, const TD* d, double* x, bool fresh, hipStream_t st) {
     if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_add<TD>, dim3(blocks_for(count)), dim3(kBlock), 0, st, count, d, x);
+    hipLaunchKernelGGL(k_add<TD>, dim3(blocks_for(count)), dim3(kBlock), 0, st, count, d, x, fresh ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -288,8 +288,8 @@ template hipError_t launch_convert<double, float>(int64_t, const double*, float*
 template hipError_t launch_convert<float, double>(int64_t, const float*, double*, hipStream_t);
 template hipError_t launch_convert<double, __bf16>(int64_t, const double*, __bf16*, hipStream_t);
 template hipError_t launch_fill<__bf16>(int64_t, __bf16, __bf16*, hipStream_t);
-template hipError_t launch_add<float>(int64_t, const float*, double*, hipStream_t);
-template hipError_t launch_add<double>(int64_t, const double*, double*, hipStream_t);
+template hipError_t launch_add<float>(int64_t, const float*, double*, bool, hipStream_t);
+template hipError_t launch_add<double>(int64_t, const double*, double*, bool, hipStream_t);
 template hipError_t launch_waves_io<double>(int64_t, int, const int32_t*, double*, double*, bool, hipStream_t);
 template hipError_t launch_waves_io<float>(int64_t, int, const int32_t*, float*, double*, bool, hipStream_t);
 
