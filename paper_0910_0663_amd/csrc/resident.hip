@@ -9,12 +9,12 @@
 // iteration is the same: sweep k + 1 of a sub-circuit reads the waves sweep k of its
 // neighbours sent).  Bound by the exchange's latency; alone it takes 1.3 us a sweep up to
 // 400 workgroups, 1.6 at 1,024, 3.1 at 4,096 (there the polls' traffic).  Measured, solve
-// before and after: 64x64 in 16x16 blocks to 1e-10 (296 sweeps) 1.3-1.5 -> 0.51 ms;
+// before and after: 64x64 in 16x16 blocks to 1e-10 (296 sweeps) 1.3-1.5 -> 0.50 ms;
 // 331x290 in random cuts (272 sweeps) 1.7 -> 0.69 ms; 768x640 in 8x8 blocks (7,680
-// sub-circuits, 832 sweeps) 6.9 -> 4.6 ms, 5.4 us a sweep.
+// sub-circuits, 832 sweeps) 6.9 -> 2.5 ms, 3.0 us a sweep.
 //
-// A circuit runs resident whenever it fits: at the largest that does, above, a sweep
-// still takes 5.4 us against 8.1 as a launch.
+// A circuit runs resident whenever it fits: at the largest of 32 ports that does, above, a
+// sweep takes 3.0 us against 8.1 as a launch.
 //
 // Exchange.  A wave travels as 8-byte words, each 32 bits of data and the 32-bit
 // number of its sweep (FP64: two words), written and read as relaxed agent-scope
@@ -120,8 +120,8 @@ __device__ inline bool wait_for(bool want, F ready, u64* abort_word, unsigned ta
 // Shapes by the largest port count QB (per_simd: wavefronts a SIMD should hold, which
 // bounds the registers; more sub-circuits then fit the chip) of a sub-circuit.  Row p of the operator
 // (lane) is port p's node against every port's node: z_n(p) = sum_p' S(n_p, n_p') c_p' a_p'.
-// Up to 32 ports, one wavefront takes two sub-circuits, all 32 columns of a row in a
-// lane (64 registers in FP64).  Above, a workgroup takes one: RG groups of 64 rows
+// Up to 32 ports, a wavefront takes two sub-circuits, all 32 columns of a row in a
+// lane (64 registers in FP64), and a workgroup one wavefront or eight (kManySubs).  Above, a workgroup takes one: RG groups of 64 rows
 // by CG groups of COLS columns, the partial sums meeting in LDS; 16-32 columns a lane
 // keep the chain of multiply-adds short and the registers low.
 //
@@ -134,28 +134,32 @@ template <int QB>
 struct Shape;
 template <>
 struct Shape<32> {
-    static constexpr int RG = 1, CG = 1, COLS = 32, SUBS = 2;
+    static constexpr int RG = 1, CG = 1, COLS = 32;
     template <typename T>
     static constexpr int per_simd() { return 4; }
 };
 template <>
 struct Shape<64> {
-    static constexpr int RG = 1, CG = 4, COLS = 16, SUBS = 1;
+    static constexpr int RG = 1, CG = 4, COLS = 16;
     template <typename T>
     static constexpr int per_simd() { return 5; }
 };
 template <>
 struct Shape<96> {
-    static constexpr int RG = 2, CG = 4, COLS = 24, SUBS = 1;
+    static constexpr int RG = 2, CG = 4, COLS = 24;
     template <typename T>
     static constexpr int per_simd() { return 4; }
 };
 template <>
 struct Shape<128> {
-    static constexpr int RG = 2, CG = 4, COLS = 32, SUBS = 1;
+    static constexpr int RG = 2, CG = 4, COLS = 32;
     template <typename T>
     static constexpr int per_simd() { return 4; }
 };
+
+// threads of a workgroup of SUBS sub-circuits (more than one: 32 lanes each)
+template <int QB, int SUBS>
+constexpr int kThreads = SUBS > 1 ? 32 * SUBS : 64 * Shape<QB>::RG * Shape<QB>::CG;
 
 // pair m of diagonals of a packed triangle (ports.hip)
 __device__ inline int packed_at(int k, int i, int j) {
@@ -324,8 +328,8 @@ __device__ __forceinline__ bool residual_check(const ResidentArgs<T>& A, unsigne
 template <int QB>
 constexpr int kSpan = 3 * (QB <= 32 ? 32 : 64);
 
-template <typename T, int QB>
-__global__ void __launch_bounds__(64 * Shape<QB>::RG * Shape<QB>::CG, Shape<QB>::template per_simd<T>())
+template <typename T, int QB, int SUBS>
+__global__ void __launch_bounds__((kThreads<QB, SUBS>), Shape<QB>::template per_simd<T>())
     k_resident(ResidentArgs<T> A) {
     const unsigned nb = gridDim.x - 1;         // workgroups that sweep
     if (blockIdx.x == nb) {
@@ -333,26 +337,29 @@ __global__ void __launch_bounds__(64 * Shape<QB>::RG * Shape<QB>::CG, Shape<QB>:
         return;
     }
     using Sh = Shape<QB>;
-    constexpr int RG = Sh::RG, CG = Sh::CG, COLS = Sh::COLS, SUBS = Sh::SUBS;
-    constexpr int L = 64 / SUBS;               // lanes of a sub-circuit's row group
-    constexpr int ROWS = L * RG;               // rows (ports) of a sub-circuit
+    constexpr int RG = Sh::RG, CG = Sh::CG, COLS = Sh::COLS;
+    constexpr bool MANY = SUBS > 1;            // 32 lanes a sub-circuit
+    constexpr int ROWS = MANY ? 32 : 64 * RG;  // rows (ports) of a sub-circuit
+    constexpr int ALL = ROWS * SUBS;           // of the workgroup's
+    constexpr int LOCAL = SUBS > 2 ? ALL : 0;  // waves between its sub-circuits go through LDS
     constexpr int STAGE = CG * COLS + 2;       // staged c a of a sub-circuit (the pad keeps two sub-circuits'
                                                // broadcast reads in different banks)
     constexpr int W = sizeof(T) / 4;           // words of a wave
     constexpr bool ORDERED = sizeof(T) == 4;   // the packed sweep's order (see above)
     constexpr int CHUNKS = ORDERED && CG > 1 ? 8 : CG;
     __shared__ alignas(16) T ca[SUBS][STAGE];
-    __shared__ T zp[CHUNKS][64 * RG];
+    __shared__ T zp[CHUNKS][ALL];
+    __shared__ T lex[2][LOCAL ? LOCAL : 1];
     __shared__ T ts[ORDERED ? SUBS : 1][ORDERED ? kSpan<QB> : 1];
-    __shared__ double xs[64 * RG], vs[64 * RG], red[8];
-    __shared__ int32_t node[64 * RG], first[64 * RG], cnt[64 * RG];
+    __shared__ double xs[ALL], vs[ALL], red[8];
+    __shared__ int32_t node[ALL], first[ALL], cnt[ALL];
     __shared__ int bad;
     __shared__ unsigned next_s;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int unit = xcd_block(blockIdx.x, nb);
-    const int sub = SUBS == 2 ? lane >> 5 : 0;
-    const int rg = wave % RG, cg = wave / RG;
-    const int row = SUBS == 2 ? (lane & 31) : rg * 64 + lane;
+    const int sub = MANY ? tid >> 5 : 0;
+    const int rg = MANY ? 0 : wave % RG, cg = MANY ? 0 : wave / RG;
+    const int row = MANY ? (lane & 31) : rg * 64 + lane;
     const int s = min(unit * SUBS + sub, A.S - 1);
     const bool real = unit * SUBS + sub < A.S;
     const int p0 = A.port_off[s], q = real ? A.port_off[s + 1] - p0 : 0;
@@ -415,8 +422,12 @@ __global__ void __launch_bounds__(64 * Shape<QB>::RG * Shape<QB>::CG, Shape<QB>:
     T a = T(0), o = T(0), o_prev = T(0), h = T(0), c = T(0), be = T(0), ga = T(0), an = T(0);
     int tw = 0;
     const int p = p0 + row;
+    // the workgroup's ports: a twin among them gets its wave through LDS
+    const int pw = LOCAL ? A.port_off[unit * SUBS] : 0, pe = LOCAL ? A.port_off[min(unit * SUBS + SUBS, A.S)] : 0;
+    bool near = false;
     if (owner) {
         tw = A.port_twin[p];
+        near = LOCAL && tw >= pw && tw < pe;
         a = A.a[A.cur][p];
         o_prev = A.a[A.cur][tw];
         h = A.h[p];
@@ -513,14 +524,21 @@ __global__ void __launch_bounds__(64 * Shape<QB>::RG * Shape<QB>::CG, Shape<QB>:
         }
         if (cg == 0) {
             if (owner) {
-                send(slots, set + unsigned(tw), o, tag);
+                if (near)
+                    lex[tag & 1][LOCAL ? tw - pw : 0] = o;
+                else
+                    send(slots, set + unsigned(tw), o, tag);
             }
-            if (!wait_for(owner, [&] { return receive(slots, set + unsigned(p), tag, an); }, abort_word, abort_tag,
-                             A.wait_ticks))
+            // (the set is written again after the next sweep's barrier, which every reader of it reaches)
+            if constexpr (LOCAL > 0) __syncthreads();
+            if (!wait_for(owner && !near, [&] { return receive(slots, set + unsigned(p), tag, an); }, abort_word,
+                          abort_tag, A.wait_ticks))
                 bad = st->timeout = 1;
+            if (near) an = lex[tag & 1][LOCAL ? p - pw : 0];
         }
         if (--left == 0) {
-            if (!residual_check(A, nb, owner, p, base, row, o, a, an, o_prev, xs, vs, red, RG, first, cnt, bad, next_s,
+            if (!residual_check(A, nb, owner, p, base, row, o, a, an, o_prev, xs, vs, red, MANY ? SUBS / 2 : RG, first,
+                                cnt, bad, next_s,
                                 tag, abort_tag))
                 return;
             left = next_s;
@@ -761,22 +779,28 @@ const void* wide_kernel(int max_npn) {
     }
 }
 
-template <typename T, int QB>
+template <typename T, int QB, int SUBS = 1>
 int blocks_of(int S) {
-    using Sh = Shape<QB>;
-    return fitting(reinterpret_cast<const void*>(&k_resident<T, QB>), 64 * Sh::RG * Sh::CG,
-                   (int64_t(S) + Sh::SUBS - 1) / Sh::SUBS);
+    return fitting(reinterpret_cast<const void*>(&k_resident<T, QB, SUBS>), kThreads<QB, SUBS>,
+                   (int64_t(S) + SUBS - 1) / SUBS);
 }
 
-template <typename T, int QB>
+template <typename T, int QB, int SUBS = 1>
 hipError_t launch_q(const ResidentArgs<T>& args, hipStream_t st) {
-    using Sh = Shape<QB>;
     ResidentArgs<T> a = args;
     void* params[] = {&a};
-    return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_resident<T, QB>),
-                                      dim3((unsigned(args.S) + Sh::SUBS - 1) / Sh::SUBS + 1), dim3(64 * Sh::RG * Sh::CG),
-                                      params, 0, st);
+    return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_resident<T, QB, SUBS>),
+                                      dim3((unsigned(args.S) + SUBS - 1) / SUBS + 1), dim3(kThreads<QB, SUBS>), params,
+                                      0, st);
 }
+
+// Up to 32 ports: sub-circuits of a workgroup.  Sixteen send nearly half of their waves
+// through LDS (neighbours in the block order), which relieves the exchange of many; few
+// are better off without the workgroup's barriers, each of their wavefronts on a compute
+// unit of its own (solves with 2 / 8 / 16: 7,680 sub-circuits 4.53 / 2.69 / 2.51 ms, 1,444
+// 0.99 / 0.91 / 0.95, 1,156 1.15 / 1.13 / 1.18, 437 in FP32 1.04 / 1.16 / 1.25, 64
+// 0.73 / 0.76 / 0.79).
+constexpr int kManySubs = 1280;
 
 }  // namespace
 
@@ -785,13 +809,13 @@ int resident_blocks(int S, int max_npn, int max_ports, bool packed) {
     if (S < 1) return 0;
     if constexpr (sizeof(T) == 4) {
         if (!packed || max_ports > 64) return 0;
-        return max_ports <= 32 ? blocks_of<T, 32>(S) : blocks_of<T, 64>(S);
+        return max_ports > 32 ? blocks_of<T, 64>(S) : S > kManySubs ? blocks_of<T, 32, 16>(S) : blocks_of<T, 32, 2>(S);
     } else {
         if (max_ports > 128) {
             if (packed || max_ports > kWidePorts || max_npn > 64 * kWideRows) return 0;
             return fitting(wide_kernel(max_npn), 512, S);
         }
-        return max_ports <= 32   ? blocks_of<T, 32>(S)
+        return max_ports <= 32   ? (S > kManySubs ? blocks_of<T, 32, 16>(S) : blocks_of<T, 32, 2>(S))
                : max_ports <= 64 ? blocks_of<T, 64>(S)
                : max_ports <= 96 ? blocks_of<T, 96>(S)
                                  : blocks_of<T, 128>(S);
@@ -803,7 +827,9 @@ hipError_t launch_resident(const ResidentArgs<T>& args, int max_npn, int max_por
     if (args.S < 1) return hipErrorInvalidValue;
     if constexpr (sizeof(T) == 4) {
         if (!args.packed || max_ports > 64) return hipErrorInvalidValue;
-        return max_ports <= 32 ? launch_q<T, 32>(args, st) : launch_q<T, 64>(args, st);
+        return max_ports > 32         ? launch_q<T, 64>(args, st)
+               : args.S > kManySubs ? launch_q<T, 32, 16>(args, st)
+                                    : launch_q<T, 32, 2>(args, st);
     } else {
         if (max_ports > 128) {
             if (args.packed || max_ports > kWidePorts || max_npn > 64 * kWideRows) return hipErrorInvalidValue;
@@ -812,7 +838,7 @@ hipError_t launch_resident(const ResidentArgs<T>& args, int max_npn, int max_por
             return hipLaunchCooperativeKernel(wide_kernel(max_npn), dim3(unsigned(args.S) + 1), dim3(512), params, 0,
                                               st);
         }
-        return max_ports <= 32   ? launch_q<T, 32>(args, st)
+        return max_ports <= 32   ? (args.S > kManySubs ? launch_q<T, 32, 16>(args, st) : launch_q<T, 32, 2>(args, st))
                : max_ports <= 64 ? launch_q<T, 64>(args, st)
                : max_ports <= 96 ? launch_q<T, 96>(args, st)
                                  : launch_q<T, 128>(args, st);
