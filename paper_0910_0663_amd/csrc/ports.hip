@@ -481,12 +481,17 @@ hipError_t launch_sweep_ppn(int S, int max_npn, int max_ports, int64_t op_bytes,
     // FP64: rows and columns of a sub-circuit spread out, where a column's wavefronts have
     // enough of it or the sub-circuits alone do not fill the chip (solves, one workgroup per
     // sub-circuit / spread: 105 of 296 port nodes 11.0 / 7.2 ms, 512 of 98 8.6 / 6.7, 1,728 of
-    // 98 21.4 / 23.9, 1,764 of 92 5.1 / 5.5, 961 of 124 5.37 / 5.18, 1,000 of 152 20.2 / 19.1).
+    // 98 21.4 / 23.9, 1,764 of 92 5.1 / 5.5, 961 of 124 5.37 / 5.18, 1,000 of 152 20.2 / 19.1,
+    // 576 of 296 30.5 / 27.8, 729 of 296 48.9 / 40.5).  Between one and two sub-circuits a
+    // compute unit a workgroup for each large one is better: all run at once, and spread out
+    // they make one and a half rounds of workgroups (300 of 296, uneven, 15.4 / 15.8; 360 16.9 /
+    // 17.7; 390 18.2 / 19.1; even ones of 294 to 405 gain 1 to 4%).
     // FP32 keeps the order of its sums: its inner solves stop near the rounding floor.
     if constexpr (sizeof(TO) == 8) {
         const int64_t ry = (max_npn + 63) / 64;
         const size_t need = (size_t(max_npn) + 64 * kPpnSplit) * 8 + size_t(max_ports) * 4;
-        if ((max_npn > 112 || (max_npn > 64 && S <= 512)) && S * ry <= INT32_MAX && need <= 65536) {
+        const bool one_round = max_npn > 192 && S > 256 && S < 512;
+        if ((max_npn > 112 || (max_npn > 64 && S <= 512)) && !one_round && S * ry <= INT32_MAX && need <= 65536) {
             hipLaunchKernelGGL((k_sweep_ppn_split<kPpnSplit, kPpnPairs>), dim3(unsigned(S * ry)), dim3(64 * kPpnSplit),
                                need, st, int(ry), Sn, nofs, pn_off, pn_pfirst, port_off, port_twin, pc, pbeta, pgamma,
                                h, a_cur, a_next, max_npn, reverse, keep);
