@@ -186,6 +186,7 @@ struct vtm_handle_s {
     DevBuf<int64_t> qmofs;
     DevBuf<__bf16> Mbt;
     DevBuf<double> M64t;
+    DevBuf<double> M64tT;  // unsymmetric A, FP64: of K^-T, for the adjoint (none: its sweeps are full)
     DevBuf<int64_t> sofs;
     DevBuf<double> S64, W64p;
     DevBuf<float> S32, W32p;
@@ -344,7 +345,7 @@ vtm_status port_residual_launch(vtm_handle h, bool low, int cur, int nrhs) {
 // unsymmetric A needs a form with a transposed operator.
 bool has_pp(vtm_handle h, int nrhs, bool adjoint) {
     const bool same = !adjoint || h->plan.symmetric;
-    if (h->ppb) return same;
+    if (h->ppb) return same || h->M64tT.p;
     if (!h->pp) return false;
     if (nrhs == 1) return same || h->ppn;
     if (h->pps || h->ppn) return h->ppt;
@@ -467,7 +468,8 @@ vtm_status sweep_once(vtm_handle h, bool low, int nrhs, const void* b, void* x, 
         const vtm::Plan& P = h->plan;
         if (!low)
             VTM_HIP(vtm::launch_sweep_mfma_pp<double>(int(P.S), P.max_ports, nrhs, h->pp_variant, h->pp_rc,
-                                                      h->lds_limit, h->M64t.p, h->qmofs.p, h->port_off.p,
+                                                      h->lds_limit, adjoint && !P.symmetric ? h->M64tT.p : h->M64t.p,
+                                                      h->qmofs.p, h->port_off.p,
                                                       h->port_twin.p, h->h64.p, h->a64[cur].p, h->a64[cur ^ 1].p,
                                                       cur, h->stream));
         else
@@ -1483,12 +1485,30 @@ static vtm_status build_values(vtm_handle_s* h) {
             VTM_HIP(h->M64t.alloc(nq));
             VTM_HIP(vtm::launch_port_matrix_tiles<double>(int(P.S), h->sub_off.p, h->kofs.p, h->port_off.p,
                                                           h->port_node.p, h->c64.p, h->beta64.p, h->gamma64.p,
-                                                          inv64.p, h->qmofs.p, h->M64t.p, s, h->coupling<double>()));
+                                                          inv64.p, h->qmofs.p, h->M64t.p, s, h->coupling<double>(),
+                                                          false));
+            // the adjoint of an unsymmetric A port to port too (16 columns, blocks of 8: 29x52x29 43.8 ->
+            // 25.3 ms, 54x30x55 60.6 -> 26.0).  BF16 keeps full sweeps: operators rounded otherwise move the
+            // refined x by as much as its tolerance.  No memory for them: full sweeps as well.
+            if (!P.symmetric && !P.coupled) {
+                const hipError_t e = h->M64tT.alloc(nq);
+                if (e == hipErrorOutOfMemory) {
+                    (void)hipGetLastError();
+                    h->M64tT.reset();
+                } else {
+                    VTM_HIP(e);
+                    VTM_HIP(vtm::launch_port_matrix_tiles<double>(int(P.S), h->sub_off.p, h->kofs.p, h->port_off.p,
+                                                                  h->port_node.p, h->c64.p, h->beta64.p, h->gamma64.p,
+                                                                  inv64.p, h->qmofs.p, h->M64tT.p, s,
+                                                                  h->coupling<double>(), true));
+                }
+            }
         } else {
             VTM_HIP(h->Mbt.alloc(nq));
             VTM_HIP(vtm::launch_port_matrix_tiles<__bf16>(int(P.S), h->sub_off.p, h->kofs.p, h->port_off.p,
                                                           h->port_node.p, h->c64.p, h->beta64.p, h->gamma64.p,
-                                                          inv64.p, h->qmofs.p, h->Mbt.p, s, h->coupling<double>()));
+                                                          inv64.p, h->qmofs.p, h->Mbt.p, s, h->coupling<double>(),
+                                                          false));
         }
         VTM_HIP(hipStreamSynchronize(s));
     }

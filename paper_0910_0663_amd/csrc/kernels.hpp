@@ -122,12 +122,13 @@ hipError_t launch_sweep_mfma_pp(int S, int max_ports, int nrhs, int variant, int
                                 const typename MfmaTypes<T>::TV* a_cur, typename MfmaTypes<T>::TV* a_next,
                                 int reverse, hipStream_t st);
 // M_s = diag(beta) Kinv[P, P] diag(c) + diag(gamma) in A-tile order from the FP64
-// column-major inverses at Kinv + kofs[s] (coefficients FP64, rounded to T once).
+// column-major inverses at Kinv + kofs[s] (coefficients FP64, rounded to T once);
+// transpose: with Kinv^T (no coupled lines).
 template <typename T>
 hipError_t launch_port_matrix_tiles(int S, const int32_t* sub_off, const int64_t* kofs, const int32_t* port_off,
                                     const int32_t* port_node, const double* pc, const double* pbeta,
                                     const double* pgamma, const double* Kinv, const int64_t* qmofs, T* out,
-                                    hipStream_t st, Coupling<double> B = {});
+                                    hipStream_t st, Coupling<double> B = {}, bool transpose = false);
 
 // ---- port-to-port form (ports.hip) -------------------------------------------
 // M_s = diag(beta) K^-1[i(P), i(P)] diag(c) + diag(gamma) for every sub-circuit,
