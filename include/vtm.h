@@ -117,7 +117,10 @@ typedef struct {
                                q x q; the adjoint of an unsymmetric A uses its
                                transpose); else M = diag(beta) K^-1[ports, ports]
                                diag(c) + diag(gamma).  Handles with MFMA tiles use M in
-                               tile order for all right-hand sides.  Residual checks
+                               tile order for all right-hand sides; on others several
+                               right-hand sides use K^-1 over the port nodes as tiles
+                               (a second copy, nrhs_max > 1; without memory for it the
+                               full form) or M.  Residual checks
                                use the port quantities alone (a local solve meets
                                every interior row, so b - A x lives on the port
                                nodes); once that residual passes, and at the end, x
@@ -334,8 +337,10 @@ vtm_status vtm_solve(vtm_handle h, const double *b, double *x, int32_t nrhs, dou
  * A^T, reusing the stored sub-circuit inverses read transposed (valid because
  * every cut coupling is symmetric, so the torn A^T is the transposed torn A).
  * Handles whose inverses are MFMA tiles (batched) use the same tiles when A is
- * symmetric and a transposed copy made at setup otherwise (then every sweep of
- * the adjoint is a full sweep).  Same conventions and errors as vtm_solve.
+ * symmetric and a transposed copy made at setup otherwise (then the adjoint
+ * sweeps port to port on FP64 handles, on a transposed M where there was memory
+ * for it and lines are not coupled; other sweeps of it are full sweeps).  Same
+ * conventions and errors as vtm_solve.
  */
 vtm_status vtm_solve_adjoint(vtm_handle h, const double *g, double *lambda, int32_t nrhs,
                              double tol, vtm_report *rep);
