@@ -315,8 +315,8 @@ vtm_status vtm_vertex_sca(const vtm_csr *A, const int32_t *label, const int32_t 
  *   rep     optional report.
  *
  * One right-hand side on a small circuit torn at branches runs resident: when
- * every sub-circuit has at most 512 ports, on at most 320 nodes (FP32: 64 ports,
- * symmetric A), and the device holds all of them at once, the port-to-port sweeps
+ * every sub-circuit has at most 512 ports, on at most 320 nodes, and the device
+ * holds all of them at once, the port-to-port sweeps
  * and checks of a solve (of an inner solve when refining) are one cooperative
  * launch.  Same sweeps, checks and residual history.  opt.timing runs a launch per
  * sweep.

@@ -125,7 +125,7 @@ __device__ inline bool wait_for(bool want, F ready, u64* abort_word, unsigned ta
 // by CG groups of COLS columns, the partial sums meeting in LDS; 16-32 columns a lane
 // keep the chain of multiply-adds short and the registers low.
 //
-// FP32 (packed operators, up to 64 ports) forms z in the order of the packed sweep of a
+// FP32 (packed operators, up to 64 ports; dense ones: k_resident_wide_f) forms z in the order of the packed sweep of a
 // launch per sweep (ports.hip), bit for bit: row r is port node r, and lane r holds for
 // each diagonal d both S(r, r + d) and S(r - d, r); t = c a summed per node is staged
 // between zeros.  An FP32 inner solve stops where rounding is a visible part of its
@@ -754,6 +754,180 @@ __global__ void __launch_bounds__(512, 2) k_resident_wide(ResidentArgs<double> A
     }
 }
 
+// The same in FP32, in the order of the port-node sweep of a launch per sweep (k_sweep_ppn,
+// ports.hip), bit for bit: a row's entries come in groups of four columns, and each of the
+// four has a running sum over the groups.  Wavefront w takes the sum w % 4 of every second
+// row group from w / 4 on: REG groups in registers, the rest in LDS, the k % 4 last columns
+// with the first sum.  Refined solves, a launch per sweep and resident: 168 sub-circuits of
+// 296 port nodes (29x44x53) 7.7 -> 4.2 ms, 125 of 152 (30x30x30 in blocks of 6) 4.9 -> 2.1,
+// 169 of 128 (400x400 in blocks of 33) 1.9 -> 1.0.
+template <int RG>
+struct WideF {
+    static constexpr int GROUPS = 16 * RG, ROWS = (RG + 1) / 2;  // ROWS: row groups of a wavefront
+    static constexpr int REG = RG >= 5 ? 54 : GROUPS, LDS = GROUPS - REG;
+};
+
+template <int RG>
+__global__ void __launch_bounds__(512, 2) k_resident_wide_f(ResidentArgs<float> A) {
+    const unsigned nb = gridDim.x - 1;
+    if (blockIdx.x == nb) {
+        control<float>(A, nb);
+        return;
+    }
+    using Wd = WideF<RG>;
+    constexpr int GROUPS = Wd::GROUPS, REG = Wd::REG, LG = Wd::LDS, NR = Wd::ROWS, ROWS = 64 * RG;
+    __shared__ float keep[LG > 0 ? LG * RG * 256 : 1];
+    __shared__ float part[4 * ROWS];
+    __shared__ double xs[kWidePorts], red[8];
+    __shared__ alignas(16) float tv[4 * GROUPS];
+    __shared__ float av[kWidePorts];
+    __shared__ int32_t node[kWidePorts], first[kWidePorts], cnt[kWidePorts];
+    __shared__ int bad;
+    __shared__ unsigned next_s;
+    __shared__ double vs[kWidePorts];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cls = wave & 3, half = wave >> 2;
+    const int s = xcd_block(blockIdx.x, nb);
+    const int p0 = A.port_off[s], q = A.port_off[s + 1] - p0;
+    const int k0 = A.pn_off[s], k = A.pn_off[s + 1] - k0;
+    const int ng = k >> 2, full = 4 * ng;
+    const bool owner = tid < q;
+    int p = p0 + tid;
+    u64* const abort_word = A.sums + 2 * size_t(nb) + 1;
+    const __amdgpu_buffer_rsrc_t slots =
+        __builtin_amdgcn_make_buffer_rsrc(A.slots, 0, int(unsigned(A.nports) * 16u), 0x00020000);
+    const __amdgpu_buffer_rsrc_t ops =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(A.op) + A.ofs[s], 0, k * k * 4, 0x00020000);
+
+    if (tid == 0) bad = 0;
+    for (int j = tid; j < 4 * GROUPS; j += 512) tv[j] = 0.0f;
+    int f0 = 0, f1 = 0;
+    if (tid < k) {
+        f0 = A.pn_pfirst[k0 + tid] - p0;
+        f1 = A.pn_pfirst[k0 + tid + 1] - p0;
+        for (int i = f0; i < f1; ++i) {
+            node[i] = tid;
+            first[i] = f0;
+            cnt[i] = f1 - f0;
+        }
+    }
+    auto load = [&](unsigned at) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ops, int(at), 0, 0));
+    };
+    // this wavefront's entry of group g in row group rg: zeros past the groups
+    auto entry = [&](int g, int rg) {
+        return load(g < ng ? unsigned((g * k + rg * 64 + lane) * 4 + cls) * 4u : 0x80000000u);
+    };
+    float op[REG][NR], last[3][NR];
+#pragma unroll
+    for (int i = 0; i < REG; ++i)
+#pragma unroll
+        for (int r = 0; r < NR; ++r) op[i][r] = entry(i, half + 2 * r);
+    if constexpr (LG > 0)
+        for (int i = 0; i < LG; ++i)
+            for (int r = 0; r < NR; ++r)
+                if (half + 2 * r < RG) keep[((i * RG + half + 2 * r) * 4 + cls) * 64 + lane] = entry(REG + i, half + 2 * r);
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+            last[e][r] = load(full + e < k ? unsigned((full + e) * k + (half + 2 * r) * 64 + lane) * 4u : 0x80000000u);
+    // (the port's coefficients are read anew every sweep: their registers would displace op's)
+    float a = 0.0f, o = 0.0f, o_prev = 0.0f, an = 0.0f;
+    int tw = 0;
+    if (owner) {
+        tw = A.port_twin[p];
+        a = A.a[A.cur][p];
+        o_prev = A.a[A.cur][tw];
+    }
+    unsigned left = unsigned(A.ctl.first);
+    unsigned tag = A.epoch;
+    const unsigned abort_tag = A.epoch + 1;
+
+    while (true) {
+        ++tag;
+        const unsigned set = (tag & 1) ? unsigned(A.nports) : 0u;
+        asm volatile("" : "+v"(p));  // or the addresses of all its coefficients are kept, too
+        if (owner) av[tid] = a;
+        __syncthreads();
+        if (bad) return;
+        if (tid < k) {
+            float t = 0.0f;
+            for (int i = f0; i < f1; ++i) t = __builtin_fmaf(A.c[p0 + i], av[i], t);
+            tv[tid] = t;
+        }
+        __syncthreads();
+        float acc[NR];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) acc[r] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < REG; ++i) {
+            const float t = tv[4 * i + cls];
+#pragma unroll
+            for (int r = 0; r < NR; ++r) acc[r] = __builtin_fmaf(op[i][r], t, acc[r]);
+            // bounds the staged values read ahead (their registers would displace op's)
+            if (i % 8 == 7) asm volatile("" : "+v"(acc[0]) : : "memory");
+        }
+        if constexpr (LG > 0) {
+#pragma unroll 4
+            for (int i = 0; i < LG; ++i) {
+                const float t = tv[4 * (REG + i) + cls];
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+                    if (half + 2 * r < RG)
+                        acc[r] = __builtin_fmaf(keep[((i * RG + half + 2 * r) * 4 + cls) * 64 + lane], t, acc[r]);
+            }
+        }
+        if (cls == 0) {  // wave-uniform
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                if (full + e < k) {
+                    const float t = tv[full + e];
+#pragma unroll
+                    for (int r = 0; r < NR; ++r) acc[r] = __builtin_fmaf(last[e][r], t, acc[r]);
+                }
+        }
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+            if (half + 2 * r < RG) part[cls * ROWS + (half + 2 * r) * 64 + lane] = acc[r];
+        float be = 0.0f, ga = 0.0f, h = 0.0f;
+        if (owner) {
+            be = A.beta[p];
+            ga = A.gamma[p];
+            h = A.h[p];
+        }
+        __syncthreads();
+        if (owner) {
+            const int n = node[tid];
+            float z = part[n];
+#pragma unroll
+            for (int j = 1; j < 4; ++j) z += part[j * ROWS + n];
+            o = __builtin_fmaf(be, z, ga * a) + h;  // rounded as in k_sweep_ppn
+            send(slots, set + unsigned(tw), o, tag);
+        }
+        if (!wait_for(owner, [&] { return receive(slots, set + unsigned(p), tag, an); }, abort_word, abort_tag,
+                      A.wait_ticks))
+            bad = A.state->timeout = 1;
+        if (--left == 0) {
+            if (!residual_check(A, nb, owner, p, 0, tid, o, a, an, o_prev, xs, vs, red, 8, first, cnt, bad, next_s, tag,
+                                abort_tag))
+                return;
+            left = next_s;
+            if (left == 0) {
+                if (owner) {
+                    // the last sweep read buffer cur when the run had an odd number of sweeps
+                    const int in = (A.cur + int((tag - A.epoch - 1) & 1)) & 1;
+                    A.a[in][p] = a;
+                    A.a[in ^ 1][p] = an;
+                }
+                return;
+            }
+        }
+        o_prev = o;
+        a = an;
+    }
+}
+
 // workgroups of `kernel` (threads each) that the current device holds at once, at most
 // `blocks` and the controlling one: blocks or 0
 int fitting(const void* kernel, int threads, int64_t blocks) {
@@ -768,7 +942,18 @@ int fitting(const void* kernel, int threads, int64_t blocks) {
     return blocks < int64_t(per) * cus ? int(blocks) : 0;
 }
 
+template <typename T>
 const void* wide_kernel(int max_npn) {
+    if constexpr (sizeof(T) == 4) {
+        switch ((max_npn + 63) / 64) {
+            case 0:
+            case 1:
+            case 2: return reinterpret_cast<const void*>(&k_resident_wide_f<2>);
+            case 3: return reinterpret_cast<const void*>(&k_resident_wide_f<3>);
+            case 4: return reinterpret_cast<const void*>(&k_resident_wide_f<4>);
+            default: return reinterpret_cast<const void*>(&k_resident_wide_f<5>);
+        }
+    }
     switch ((max_npn + 63) / 64) {
         case 0:
         case 1:
@@ -804,17 +989,21 @@ constexpr int kManySubs = 1280;
 
 }  // namespace
 
+// Whether sub-circuits take a compute unit each: dense operators beyond the shapes above
+template <typename T>
+bool wide(int max_npn, int max_ports, bool packed) {
+    return !packed && (sizeof(T) == 4 || max_ports > 128) && max_ports <= kWidePorts && max_npn <= 64 * kWideRows;
+}
+
 template <typename T>
 int resident_blocks(int S, int max_npn, int max_ports, bool packed) {
     if (S < 1) return 0;
+    if (wide<T>(max_npn, max_ports, packed)) return fitting(wide_kernel<T>(max_npn), 512, S);
     if constexpr (sizeof(T) == 4) {
         if (!packed || max_ports > 64) return 0;
         return max_ports > 32 ? blocks_of<T, 64>(S) : S > kManySubs ? blocks_of<T, 32, 16>(S) : blocks_of<T, 32, 2>(S);
     } else {
-        if (max_ports > 128) {
-            if (packed || max_ports > kWidePorts || max_npn > 64 * kWideRows) return 0;
-            return fitting(wide_kernel(max_npn), 512, S);
-        }
+        if (max_ports > 128) return 0;
         return max_ports <= 32   ? (S > kManySubs ? blocks_of<T, 32, 16>(S) : blocks_of<T, 32, 2>(S))
                : max_ports <= 64 ? blocks_of<T, 64>(S)
                : max_ports <= 96 ? blocks_of<T, 96>(S)
@@ -825,19 +1014,19 @@ int resident_blocks(int S, int max_npn, int max_ports, bool packed) {
 template <typename T>
 hipError_t launch_resident(const ResidentArgs<T>& args, int max_npn, int max_ports, hipStream_t st) {
     if (args.S < 1) return hipErrorInvalidValue;
+    if (wide<T>(max_npn, max_ports, args.packed)) {
+        ResidentArgs<T> a = args;
+        void* params[] = {&a};
+        return hipLaunchCooperativeKernel(wide_kernel<T>(max_npn), dim3(unsigned(args.S) + 1), dim3(512), params, 0,
+                                          st);
+    }
     if constexpr (sizeof(T) == 4) {
         if (!args.packed || max_ports > 64) return hipErrorInvalidValue;
         return max_ports > 32         ? launch_q<T, 64>(args, st)
                : args.S > kManySubs ? launch_q<T, 32, 16>(args, st)
                                     : launch_q<T, 32, 2>(args, st);
     } else {
-        if (max_ports > 128) {
-            if (args.packed || max_ports > kWidePorts || max_npn > 64 * kWideRows) return hipErrorInvalidValue;
-            ResidentArgs<T> a = args;
-            void* params[] = {&a};
-            return hipLaunchCooperativeKernel(wide_kernel(max_npn), dim3(unsigned(args.S) + 1), dim3(512), params, 0,
-                                              st);
-        }
+        if (max_ports > 128) return hipErrorInvalidValue;
         return max_ports <= 32   ? (args.S > kManySubs ? launch_q<T, 32, 16>(args, st) : launch_q<T, 32, 2>(args, st))
                : max_ports <= 64 ? launch_q<T, 64>(args, st)
                : max_ports <= 96 ? launch_q<T, 96>(args, st)

@@ -113,9 +113,8 @@ inline size_t resident_slot_words(int64_t nports) {
 }
 
 // Sweeping workgroups of a run, 0 when it cannot run resident: some sub-circuit has more
-// than 128 ports (FP64, dense operators: more than 512, or 320 port nodes; FP32: more than
-// 64, or the operators are not packed), or the current device cannot hold every workgroup
-// at once.
+// than 128 ports (dense operators: more than 512, or 320 port nodes; FP32, packed ones: more
+// than 64), or the current device cannot hold every workgroup at once.
 template <typename T>
 int resident_blocks(int S, int max_npn, int max_ports, bool packed);
 

@@ -62,20 +62,20 @@ def iterate(torch, w, k, resident, adjoint=False, **kw):
 # most ports of a sub-circuit: 16 and 32 (two to a wavefront, an odd number of them), 36
 # and 64, 51 and 96, 75 and 96 (four blocks of 32 a side), 132 and 3-D blocks with up to
 # three ports a node (unsymmetric: dense operators); random cuts of every size up to 96.
-# FP32 takes packed operators of up to 64 ports.
+# FP32 takes the dense ones a compute unit each.
 @pytest.mark.parametrize("cfg,kw,res64,res32", [
     (2, dict(dims=(12, 20), block=(4, 4)), True, True),
     (2, dict(dims=(40, 40)), True, True),
     (2, dict(dims=(36, 27), block=(9, 9)), True, True),
     (1, dict(dims=(33, 64)), True, True),
     (2, dict(dims=(51, 34), block=(17, 17)), True, True),
-    (2, dict(dims=(72, 72), block=(24, 24)), True, False),
-    (2, dict(dims=(75, 60), block=(25, 25)), True, False),
-    (2, dict(dims=(96, 96), block=(32, 32)), True, False),
-    (2, dict(dims=(99, 99), block=(33, 33)), True, False),
-    (3, dict(dims=(9, 10, 12), block=(3, 3, 3)), True, False),
-    (3, dict(dims=(12, 12, 13), block=(4, 4, 4)), True, False),
-    (4, dict(dims=(100, 90)), True, False),
+    (2, dict(dims=(72, 72), block=(24, 24)), True, True),
+    (2, dict(dims=(75, 60), block=(25, 25)), True, True),
+    (2, dict(dims=(96, 96), block=(32, 32)), True, True),
+    (2, dict(dims=(99, 99), block=(33, 33)), True, True),
+    (3, dict(dims=(9, 10, 12), block=(3, 3, 3)), True, True),
+    (3, dict(dims=(12, 12, 13), block=(4, 4, 4)), True, True),
+    (4, dict(dims=(100, 90)), True, True),
 ])
 @pytest.mark.parametrize("prec", ["fp64", "fp32_refine"])
 def test_iterates(torch, cfg, kw, res64, res32, prec):

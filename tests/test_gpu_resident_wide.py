@@ -1,4 +1,4 @@
-"""Resident runs of sub-circuits with more than 128 ports, FP64, one to a compute unit:
+"""Resident runs of sub-circuits one to a compute unit (FP64 of more than 128 ports, FP32):
 the oracle's iterates, and the sweeps, checks and result of a launch per sweep
 (timing = 1 takes that path).
 
@@ -86,6 +86,29 @@ def test_same_sweeps_and_checks_as_a_launch_per_sweep(torch, cfg, dims, block):
     assert (r0.sweeps, r0.checks) == (r1.sweeps, r1.checks)
     assert np.array_equal(r0.history_sweeps, r1.history_sweeps)
     assert np.abs(x0 - x1).max() <= 1e-11 * np.abs(x1).max()
+
+
+# FP32: the bits of a launch per sweep, on operators of two to five row groups, counts of
+# every remainder by four, symmetric and not
+@pytest.mark.parametrize("cfg,dims,block", [
+    (2, (72, 72), (24, 24)), (2, (130, 130), (65, 65)), (3, (9, 10, 12), (3, 3, 3)), (3, (18, 17, 19), (6, 6, 6)),
+    (3, (21, 22, 20), (7, 7, 7)), (3, (20, 20, 20), (10, 10, 10)), (3, (17, 16, 18), (8, 8, 8)),
+    (3, (24, 24, 24), (8, 8, 8)), (4, (180, 170), None),
+])
+def test_fp32_same_as_a_launch_per_sweep(torch, cfg, dims, block):
+    w = workloads.make(cfg, nrhs=1, dims=dims, **({} if block is None else dict(block=block)))
+    b = torch.as_tensor(w.b, device="cuda")
+    for adjoint in (False, True):
+        got = []
+        for timing in (0, 1):
+            s = vtm().Solver(w.A, w.part, w.Z, timing=timing, precision="fp32_refine")
+            x, rep = (s.solve_adjoint if adjoint else s.solve)(b, w.tol)
+            assert resident(s)
+            got.append((x.cpu().numpy(), rep))
+            s.close()
+        (x0, r0), (x1, r1) = got
+        assert (r0.sweeps, r0.outer, r0.checks) == (r1.sweeps, r1.outer, r1.checks)
+        assert np.array_equal(x0, x1)
 
 
 def test_a_wait_that_runs_out_falls_back(torch):
