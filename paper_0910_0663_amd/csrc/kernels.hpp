@@ -33,6 +33,19 @@ inline hipError_t raise_lds_limit(const void* kern, size_t lds) {
     return e;
 }
 
+// Compute units of the current device, asked once per device (0 when it cannot be asked).
+inline int compute_units() {
+    static std::mutex mu;
+    static std::map<int, int> known;
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    std::lock_guard<std::mutex> lock(mu);
+    const auto it = known.find(dev);
+    if (it != known.end()) return it->second;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    return known[dev] = cus;
+}
+
 // Largest sub-circuit whose local matrix is factored entirely in LDS.
 constexpr int kLdsSetupMax = 80;
 

@@ -94,17 +94,24 @@ typedef double pp_d2 __attribute__((ext_vector_type(2)));
 typedef unsigned long long u64p;
 typedef float pp_f4 __attribute__((ext_vector_type(4)));
 
-// 16 bytes of operator entries (NT: non-temporal)
+// 16 bytes of operator entries (NT: non-temporal).  Plain loads go through HIP's vector
+// types: through the compiler's own the same loops held 58 to 60 registers for 46 to 48
+// and swept up to 2.4% slower (150 sub-circuits of 296 port nodes in FP32: 10.9 -> 11.15 us).
 template <typename T, bool NT = false>
 __device__ inline void load16p(const T* p, T (&v)[Group<T>::G]) {
     if constexpr (sizeof(T) == 8) {
-        const pp_d2* q = reinterpret_cast<const pp_d2*>(p);
-        const pp_d2 w = NT ? __builtin_nontemporal_load(q) : *q;
-        v[0] = w.x;
-        v[1] = w.y;
+        if constexpr (NT) {
+            const pp_d2 w = __builtin_nontemporal_load(reinterpret_cast<const pp_d2*>(p));
+            v[0] = w.x, v[1] = w.y;
+        } else {
+            const double2 w = *reinterpret_cast<const double2*>(p);
+            v[0] = w.x, v[1] = w.y;
+        }
+    } else if constexpr (NT) {
+        const pp_f4 w = __builtin_nontemporal_load(reinterpret_cast<const pp_f4*>(p));
+        v[0] = w.x, v[1] = w.y, v[2] = w.z, v[3] = w.w;
     } else {
-        const pp_f4* q = reinterpret_cast<const pp_f4*>(p);
-        const pp_f4 w = NT ? __builtin_nontemporal_load(q) : *q;
+        const float4 w = *reinterpret_cast<const float4*>(p);
         v[0] = w.x;
         v[1] = w.y;
         v[2] = w.z;
@@ -297,7 +304,7 @@ __global__ void __launch_bounds__(kBlock)
     }
 }
 
-// One workgroup per sub-circuit, one port node (row of K^-1[N, N]) per thread.  Of
+// One workgroup per sub-circuit, one port node (row of K^-1[N, N]) per thread.  NT: of
 // every 16 sub-circuits the first `keep` read their operators as usual and the others
 // non-temporally (launch_sweep_ppn).  Bound by HBM: 4,096 sub-circuits of 296 port nodes
 // in FP32 (1.44 GB) 255 us a sweep, 5.6 TB/s, with every operator read as usual in one
@@ -305,7 +312,7 @@ __global__ void __launch_bounds__(kBlock)
 // Non-temporal loads take no room in the 256 MB memory-side cache, so a kept share
 // that fits it is found there by every sweep; read as usual, a stream several times
 // its size leaves nothing of itself behind.
-template <typename TO, typename TV>
+template <typename TO, typename TV, bool NT>
 __global__ void __launch_bounds__(512)
     k_sweep_ppn(const TO* __restrict__ Sn, const int64_t* __restrict__ nofs, const int32_t* __restrict__ pn_off,
                 const int32_t* __restrict__ pn_pfirst, const int32_t* __restrict__ port_off,
@@ -354,10 +361,14 @@ __global__ void __launch_bounds__(512)
             zv[row] = v;
         }
     };
-    if ((s & 15) < keep)
+    if constexpr (NT) {
+        if ((s & 15) < keep)
+            product(std::false_type{});
+        else
+            product(std::true_type{});
+    } else {
         product(std::false_type{});
-    else
-        product(std::true_type{});
+    }
     __syncthreads();
     for (int p = p0 + tid; p < p1; p += bs)
         a_next[port_twin[p]] = pbeta[p] * zv[pnode[p - p0]] + pgamma[p] * a_cur[p] + h[p];
@@ -372,7 +383,7 @@ __global__ void __launch_bounds__(512)
 // -> 94.0 ms).  Six column pairs in flight keep the kernel under 64 registers, so four
 // workgroups share a compute unit; four and eight: 11.0 and 11.1 ms where six make 10.8.
 constexpr int kPpnSplit = 8, kPpnPairs = 6;  // wavefronts, column pairs in flight in each
-template <int KS, int CH>
+template <int KS, int CH, bool NT>
 __global__ void __launch_bounds__(64 * KS)
     k_sweep_ppn_split(int ry, const double* __restrict__ Sn, const int64_t* __restrict__ nofs,
                       const int32_t* __restrict__ pn_off, const int32_t* __restrict__ pn_pfirst,
@@ -448,10 +459,14 @@ __global__ void __launch_bounds__(64 * KS)
         for (int p = pb + 64 * KS; p < b1; p += 64 * KS)
             a_next[port_twin[p]] = pbeta[p] * z(p) + (pgamma[p] * a_cur[p] + h[p]);
     };
-    if ((s & 15) < keep)
+    if constexpr (NT) {
+        if ((s & 15) < keep)
+            product(std::false_type{});
+        else
+            product(std::true_type{});
+    } else {
         product(std::false_type{});
-    else
-        product(std::true_type{});
+    }
 }
 
 }  // namespace
@@ -472,7 +487,11 @@ hipError_t launch_sweep_ppn(int S, int max_npn, int max_ports, int64_t op_bytes,
                             const TV* a_cur, TV* a_next, int reverse, hipStream_t st) {
     const size_t lds = 2 * size_t(max_npn) * sizeof(TV) + size_t(max_ports) * 4;
     if (lds > 65536) return hipErrorInvalidValue;
-    // Up to twice the memory-side cache, plain loads in alternating order reuse more of it
+    // Above the memory-side cache every other sweep walks backwards and finds in it what the
+    // sweep before read last (FP32, one order / alternating: 288 MB 55.0 / 54.2 us a sweep, 387
+    // MB 87.1 / 80.8); up to it one order does the same (90 MB 17.8 / 17.8, 210 MB 39.2 / 39.2),
+    // and one workgroup per sub-circuit keeps to it.
+    // Up to twice the cache, plain loads reuse more of it
     // (358 MB: 30.9 ms a solve, 31.4 with the share that fits kept, 29.8 with none kept; 192
     // MB: 17.2, and 21-23 with any non-temporal); above, the share that fits is kept (700 MB:
     // 65.0 -> 58.7 ms, 59.5 with none kept; 1.44 GB: 144 -> 128, 133).
@@ -482,26 +501,34 @@ hipError_t launch_sweep_ppn(int S, int max_npn, int max_ports, int64_t op_bytes,
     // enough of it or the sub-circuits alone do not fill the chip (solves, one workgroup per
     // sub-circuit / spread: 105 of 296 port nodes 11.0 / 7.2 ms, 512 of 98 8.6 / 6.7, 1,728 of
     // 98 21.4 / 23.9, 1,764 of 92 5.1 / 5.5, 961 of 124 5.37 / 5.18, 1,000 of 152 20.2 / 19.1,
-    // 576 of 296 30.5 / 27.8, 729 of 296 48.9 / 40.5).  Between one and two sub-circuits a
-    // compute unit a workgroup for each large one is better: all run at once, and spread out
-    // they make one and a half rounds of workgroups (300 of 296, uneven, 15.4 / 15.8; 360 16.9 /
-    // 17.7; 390 18.2 / 19.1; even ones of 294 to 405 gain 1 to 4%).
+    // 576 of 296 30.5 / 27.8, 729 of 296 48.9 / 40.5).  Large ones that are nearly as many as
+    // the compute units keep a workgroup each, where the operators fit the cache: their five
+    // or six wavefronts on every unit stream from it at 7.3 TB/s, and spread out they make
+    // more than one round (180 of 337 27.0 / 27.6 us a sweep, 210 uneven ones 26.8 / 28.4, 256
+    // 30.9 / 32.8; 150 23.9 / 22.8, of 296 17.6 / 14.6, 240 of 488, 435 MB, 65.1 / 58.9); so do
+    // those between one and two a unit (all run at once).
     // FP32 keeps the order of its sums: its inner solves stop near the rounding floor.
     if constexpr (sizeof(TO) == 8) {
         const int64_t ry = (max_npn + 63) / 64;
         const size_t need = (size_t(max_npn) + 64 * kPpnSplit) * 8 + size_t(max_ports) * 4;
-        const bool one_round = max_npn > 192 && S > 256 && S < 512;
-        if ((max_npn > 112 || (max_npn > 64 && S <= 512)) && !one_round && S * ry <= INT32_MAX && need <= 65536) {
-            hipLaunchKernelGGL((k_sweep_ppn_split<kPpnSplit, kPpnPairs>), dim3(unsigned(S * ry)), dim3(64 * kPpnSplit),
-                               need, st, int(ry), Sn, nofs, pn_off, pn_pfirst, port_off, port_twin, pc, pbeta, pgamma,
-                               h, a_cur, a_next, max_npn, reverse, keep);
+        const int cus = compute_units();
+        const bool one_round = (max_npn > 192 && S > cus && S < 2 * cus) ||
+                               (max_npn > 320 && 3 * S > 2 * cus && S <= cus && op_bytes <= kCache);
+        if ((max_npn > 112 || (max_npn > 64 && S <= 2 * cus)) && !one_round && S * ry <= INT32_MAX && need <= 65536) {
+            auto kern = keep == 16 ? k_sweep_ppn_split<kPpnSplit, kPpnPairs, false>
+                                   : k_sweep_ppn_split<kPpnSplit, kPpnPairs, true>;
+            hipLaunchKernelGGL(kern, dim3(unsigned(S * ry)), dim3(64 * kPpnSplit), need, st, int(ry), Sn, nofs, pn_off,
+                               pn_pfirst, port_off, port_twin, pc, pbeta, pgamma, h, a_cur, a_next, max_npn, reverse,
+                               keep);
             return hipGetLastError();
         }
     }
+    if (op_bytes <= kCache) reverse = 0;
     // one pass over the rows where possible
     const int bs = std::min(512, std::max(64, ((max_npn + 63) / 64) * 64));
-    hipLaunchKernelGGL((k_sweep_ppn<TO, TV>), dim3(S), dim3(bs), lds, st, Sn, nofs, pn_off, pn_pfirst, port_off,
-                       port_twin, pc, pbeta, pgamma, h, a_cur, a_next, max_npn, reverse, keep);
+    auto kern = keep == 16 ? k_sweep_ppn<TO, TV, false> : k_sweep_ppn<TO, TV, true>;
+    hipLaunchKernelGGL(kern, dim3(S), dim3(bs), lds, st, Sn, nofs, pn_off, pn_pfirst, port_off, port_twin, pc, pbeta,
+                       pgamma, h, a_cur, a_next, max_npn, reverse, keep);
     return hipGetLastError();
 }
 

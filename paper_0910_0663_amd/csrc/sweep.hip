@@ -373,7 +373,7 @@ hipError_t launch_sweep(int S, int max_ns, int nrhs, const TO* K, const int64_t*
         if constexpr (sizeof(TO) == 8) {
             constexpr int KS = 8;
             const size_t lds2 = (size_t(max_ns) + 64 * KS) * sizeof(TV);
-            if (split && int64_t(S) * ry <= 1024 && lds2 <= lds_limit) {
+            if (split && int64_t(S) * ry <= 4 * compute_units() && lds2 <= lds_limit) {
                 auto kern = k_sweep1_split<4, KS>;
                 if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds2); e != hipSuccess) return e;
                 hipLaunchKernelGGL(kern, dim3(S, ry), dim3(64 * KS), lds2, st, K, kofs, sub_off, ports.off, ports.node,
