@@ -119,7 +119,8 @@ typedef struct {
                                diag(c) + diag(gamma).  Handles with MFMA tiles use M in
                                tile order for all right-hand sides; on others several
                                right-hand sides use K^-1 over the port nodes as tiles
-                               (a second copy, nrhs_max > 1; without memory for it the
+                               (a second copy, nrhs_max > 1; without memory for it, at
+                               setup or for the temporary inverses of a refresh, the
                                full form) or M.  Residual checks
                                use the port quantities alone (a local solve meets
                                every interior row, so b - A x lives on the port

@@ -33,23 +33,56 @@ using vtm::fail;
                         std::string(#expr) + ": " + hipGetErrorString(e_));                        \
     } while (0)
 
+// Device memory the calling thread's handles may still take, for tests of what happens
+// without enough of it (vtm_testing_memory); negative: no bound but the device's.
+struct MemoryBound {
+    int64_t left = -1, lowest = -1;
+    bool take(int64_t bytes) {
+        if (left < 0) return true;
+        if (bytes > left) return false;
+        left -= bytes;
+        lowest = std::min(lowest, left);
+        return true;
+    }
+    void give(int64_t bytes) {
+        if (left >= 0) left += bytes;
+    }
+};
+thread_local MemoryBound t_memory;
+
 template <typename T>
 struct DevBuf {
     T* p = nullptr;
     size_t count = 0;
-    ~DevBuf() {
-        if (p) (void)hipFree(p);
-    }
+    DevBuf() = default;
+    DevBuf(const DevBuf&) = delete;
+    DevBuf& operator=(const DevBuf&) = delete;
+    ~DevBuf() { reset(); }
+    int64_t bytes() const { return int64_t((count ? count : 1) * sizeof(T)); }
     // a buffer of n elements; one of that size already held is kept (refresh
     // re-runs setup's uploads on buffers of unchanged sizes)
     hipError_t alloc(size_t n) {
         if (p && n == count) return hipSuccess;
         reset();
         count = n;
-        return hipMalloc(reinterpret_cast<void**>(&p), (n ? n : 1) * sizeof(T));
+        const int64_t size = bytes();
+        hipError_t e = t_memory.take(size) ? hipSuccess : hipErrorOutOfMemory;
+        if (e == hipSuccess && (e = hipMalloc(reinterpret_cast<void**>(&p), size_t(size))) != hipSuccess) {
+            p = nullptr;
+            t_memory.give(size);
+        }
+        if (e != hipSuccess) count = 0;
+        return e;
+    }
+    void swap(DevBuf& o) {
+        std::swap(p, o.p);
+        std::swap(count, o.count);
     }
     void reset() {
-        if (p) (void)hipFree(p);
+        if (p) {
+            (void)hipFree(p);
+            t_memory.give(bytes());
+        }
         p = nullptr;
         count = 0;
     }
@@ -161,9 +194,10 @@ struct vtm_handle_s {
     DevBuf<int64_t> nofs;
     DevBuf<double> N64, N64T;  // T: transposed, for the adjoint of an unsymmetric A
     DevBuf<float> N32, N32T;
-    // several right-hand sides (column-group handles): the same K^-1[N, N] as MFMA
-    // tiles (T: transposed, for the adjoint of an unsymmetric A)
-    bool ppt = false;
+    // several right-hand sides (column-group handles) sweep port to port: h for all of
+    // them, and on the port-node forms the same K^-1[N, N] as MFMA tiles (T: transposed,
+    // for the adjoint of an unsymmetric A); false where there was no memory for these
+    bool columns = false;
     std::vector<int64_t> ntofs_host;
     DevBuf<int64_t> ntofs;
     DevBuf<double> Nt64, Nt64T;
@@ -348,7 +382,8 @@ bool has_pp(vtm_handle h, int nrhs, bool adjoint) {
     if (h->ppb) return same || h->M64tT.p;
     if (!h->pp) return false;
     if (nrhs == 1) return same || h->ppn;
-    if (h->pps || h->ppn) return h->ppt;
+    if (!h->columns) return false;
+    if (h->pps || h->ppn) return true;
     const size_t tv = h->opt.precision == VTM_FP64 ? 8 : 4;
     return same && size_t(h->plan.max_ports) * 2 * tv <= 65536;  // M: two staged right-hand sides in LDS
 }
@@ -1512,39 +1547,6 @@ static vtm_status build_values(vtm_handle_s* h) {
         }
         VTM_HIP(hipStreamSynchronize(s));
     }
-    if (h->ppt) {
-        const int64_t nt = h->ntofs_host[P.S];
-        const bool fp64 = o.precision == VTM_FP64;
-        auto build = [&](bool transpose) -> hipError_t {
-            if (fp64)
-                return vtm::launch_port_node_tiles<double>(int(P.S), h->sub_off.p, h->kofs.p, h->pn_off.p, h->pn_node.p,
-                                                           h->K64.p, h->ntofs.p,
-                                                           transpose ? h->Nt64T.p : h->Nt64.p, transpose, s);
-            return vtm::launch_port_node_tiles<float>(int(P.S), h->sub_off.p, h->kofs.p, h->pn_off.p, h->pn_node.p,
-                                                      h->K32.p, h->ntofs.p, transpose ? h->Nt32T.p : h->Nt32.p,
-                                                      transpose, s);
-        };
-        auto room = [&]() -> hipError_t {
-            hipError_t e = fp64 ? h->Nt64.alloc(nt) : h->Nt32.alloc(nt);
-            if (e == hipSuccess && !P.symmetric) e = fp64 ? h->Nt64T.alloc(nt) : h->Nt32T.alloc(nt);
-            return e;
-        };
-        const hipError_t e = room();
-        if (e == hipErrorOutOfMemory) {
-            // no room for a second copy of the operators: several right-hand sides keep
-            // the full form
-            (void)hipGetLastError();
-            h->ppt = false;
-            h->Nt64.reset();
-            h->Nt64T.reset();
-            h->Nt32.reset();
-            h->Nt32T.reset();
-        } else {
-            VTM_HIP(e);
-            VTM_HIP(build(false));
-            if (!P.symmetric) VTM_HIP(build(true));
-        }
-    }
     if (h->ppn) {
         const int64_t nn = P.nofs[P.S];
         if (o.precision == VTM_FP64) {
@@ -1612,8 +1614,118 @@ static vtm_status build_values(vtm_handle_s* h) {
     return VTM_OK;
 }
 
-// The handle's structure (index arrays, work buffers, which local forms run),
-// then its values (build_values), then the batched kernels' launch shapes.
+// What a handle can do without, given up: whether that freed any memory.
+static bool give_up_copies(vtm_handle_s* h) {
+    bool freed = h->resident || h->M64tT.p || h->columns;
+    h->resident = false;
+    h->res_slots.reset();
+    h->res_sums.reset();
+    h->M64tT.reset();
+    h->columns = false;
+    h->ntofs.reset();
+    h->Nt64.reset();
+    h->Nt64T.reset();
+    h->Nt32.reset();
+    h->Nt32T.reset();
+    if (h->pp && h->h64.count > size_t(h->plan.nports)) h->h64.reset();
+    if (h->pp && h->h32.count > size_t(h->plan.nports)) h->h32.reset();
+    return freed;
+}
+
+// h of one right-hand side, or as much as the handle holds.
+static vtm_status alloc_h(vtm_handle_s* h) {
+    if (!h->pp) return VTM_OK;
+    const size_t np = size_t(h->plan.nports);
+    if (h->opt.precision == VTM_FP64) {
+        if (!h->h64.p) VTM_HIP(h->h64.alloc(np));
+    } else if (!h->h32.p) {
+        VTM_HIP(h->h32.alloc(np));
+    }
+    return VTM_OK;
+}
+
+// The second copies that several right-hand sides sweep on, after everything that the
+// handle cannot do without; no memory for them: those sweeps keep the full form.
+static vtm_status build_columns(vtm_handle_s* h) {
+    if (!h->columns) return VTM_OK;
+    const vtm::Plan& P = h->plan;
+    hipStream_t s = h->stream;
+    const bool fp64 = h->opt.precision == VTM_FP64, tiles = h->pps || h->ppn;
+    const size_t all = size_t(P.nports) * h->nrhs_max;
+    auto grow = [&](auto& buf) -> hipError_t {
+        if (buf.count == all) return hipSuccess;
+        std::decay_t<decltype(buf)> more;
+        const hipError_t e = more.alloc(all);
+        if (e == hipSuccess) buf.swap(more);
+        return e;
+    };
+    auto room = [&]() -> hipError_t {
+        hipError_t e = fp64 ? grow(h->h64) : grow(h->h32);
+        if (e != hipSuccess || !tiles) return e;
+        const int64_t nt = h->ntofs_host[P.S];
+        if ((e = h->ntofs.upload(h->ntofs_host, s)) != hipSuccess) return e;
+        e = fp64 ? h->Nt64.alloc(nt) : h->Nt32.alloc(nt);
+        if (e == hipSuccess && !P.symmetric) e = fp64 ? h->Nt64T.alloc(nt) : h->Nt32T.alloc(nt);
+        return e;
+    };
+    const hipError_t e = room();
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        h->columns = false;
+        h->Nt64.reset();
+        h->Nt64T.reset();
+        h->Nt32.reset();
+        h->Nt32T.reset();
+        return VTM_OK;
+    }
+    VTM_HIP(e);
+    for (int transpose = 0; tiles && transpose < (P.symmetric ? 1 : 2); ++transpose) {
+        if (fp64)
+            VTM_HIP(vtm::launch_port_node_tiles<double>(int(P.S), h->sub_off.p, h->kofs.p, h->pn_off.p, h->pn_node.p,
+                                                        h->K64.p, h->ntofs.p, transpose ? h->Nt64T.p : h->Nt64.p,
+                                                        transpose != 0, s));
+        else
+            VTM_HIP(vtm::launch_port_node_tiles<float>(int(P.S), h->sub_off.p, h->kofs.p, h->pn_off.p, h->pn_node.p,
+                                                       h->K32.p, h->ntofs.p, transpose ? h->Nt32T.p : h->Nt32.p,
+                                                       transpose != 0, s));
+    }
+    VTM_HIP(hipStreamSynchronize(s));
+    return VTM_OK;
+}
+
+// Resident runs: the port-node forms on cut branches, when every workgroup fits the
+// device at once and there is memory for what they exchange.
+static vtm_status make_resident(vtm_handle_s* h) {
+    const vtm::Plan& P = h->plan;
+    hipStream_t s = h->stream;
+    const bool fp64 = h->opt.precision == VTM_FP64;
+    if (!(h->pps || h->ppn) || P.vertex) return VTM_OK;
+    const int blocks = fp64 ? vtm::resident_blocks<double>(int(P.S), P.max_npn, P.max_ports, h->pps)
+                            : vtm::resident_blocks<float>(int(P.S), P.max_npn, P.max_ports, h->pps);
+    if (blocks == 0) return VTM_OK;
+    const size_t words = fp64 ? vtm::resident_slot_words<double>(P.nports) : vtm::resident_slot_words<float>(P.nports);
+    hipError_t e = h->res_slots.alloc(words);
+    if (e == hipSuccess) e = h->res_sums.alloc(2 * size_t(blocks) + 2);
+    if (e == hipSuccess)
+        e = hipHostMalloc(reinterpret_cast<void**>(&h->res_state), sizeof(vtm::ResidentState),
+                          hipHostMallocMapped | hipHostMallocCoherent);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        h->res_state = nullptr;
+        h->res_slots.reset();
+        h->res_sums.reset();
+        return VTM_OK;
+    }
+    VTM_HIP(e);
+    VTM_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&h->res_state_dev), h->res_state, 0));
+    VTM_HIP(vtm::launch_fill<double>(int64_t(words), 0.0, h->res_slots.p, s));
+    VTM_HIP(vtm::launch_fill<double>(int64_t(h->res_sums.count), 0.0, h->res_sums.p, s));
+    h->resident = true;
+    return VTM_OK;
+}
+
+// The handle's structure (index arrays, work buffers, which local forms run), then its
+// values (build_values), then the batched kernels' launch shapes and what it can do without.
 static vtm_status setup_from_plan(std::unique_ptr<vtm_handle_s> h, vtm_handle* out) {
     const vtm_options& o = h->opt;
     vtm_status st = VTM_OK;
@@ -1714,41 +1826,23 @@ static vtm_status setup_from_plan(std::unique_ptr<vtm_handle_s> h, vtm_handle* o
     } else if (h->pp) {
         VTM_HIP(h->pofs.upload(P.pofs, s));
     }
-    if (h->pp) VTM_HIP(fp64 ? h->h64.alloc(P.nports * nr) : h->h32.alloc(P.nports * nr));
-    // several right-hand sides: the port-node operators also as MFMA tiles
+    // several right-hand sides: on the port-node operators as MFMA tiles, or on M
     const int npt = vtm::node_tile_pad(P.max_npn);
-    h->ppt = (h->pps || h->ppn) && nr > 1 &&
-             (fp64 ? vtm::ppt_lds_bytes<double>(npt, P.max_ports, 1) : vtm::ppt_lds_bytes<float>(npt, P.max_ports, 1)) <=
-                 h->lds_limit;
-    if (h->ppt) {
+    h->columns = h->pp && nr > 1 &&
+                 (!(h->pps || h->ppn) || (fp64 ? vtm::ppt_lds_bytes<double>(npt, P.max_ports, 1)
+                                               : vtm::ppt_lds_bytes<float>(npt, P.max_ports, 1)) <= h->lds_limit);
+    if (h->columns && (h->pps || h->ppn)) {
         h->ntofs_host.resize(P.S + 1);
         h->ntofs_host[0] = 0;
         for (int64_t k = 0; k < P.S; ++k) {
             const int64_t np = vtm::node_tile_pad(P.pn_off[k + 1] - P.pn_off[k]);
             h->ntofs_host[k + 1] = h->ntofs_host[k] + np * np;
         }
-        VTM_HIP(h->ntofs.upload(h->ntofs_host, s));
     }
 
-    if ((st = build_values(h.get())) != VTM_OK) return st;
-    // resident runs: the port-node forms on cut branches, when every workgroup fits the
-    // device at once
-    if ((h->pps || h->ppn) && !P.vertex) {
-        const int blocks = fp64 ? vtm::resident_blocks<double>(int(P.S), P.max_npn, P.max_ports, h->pps)
-                                : vtm::resident_blocks<float>(int(P.S), P.max_npn, P.max_ports, h->pps);
-        if (blocks > 0) {
-            const size_t words =
-                fp64 ? vtm::resident_slot_words<double>(P.nports) : vtm::resident_slot_words<float>(P.nports);
-            VTM_HIP(h->res_slots.alloc(words));
-            VTM_HIP(h->res_sums.alloc(2 * size_t(blocks) + 2));
-            VTM_HIP(vtm::launch_fill<double>(int64_t(words), 0.0, h->res_slots.p, s));
-            VTM_HIP(vtm::launch_fill<double>(int64_t(h->res_sums.count), 0.0, h->res_sums.p, s));
-            VTM_HIP(hipHostMalloc(reinterpret_cast<void**>(&h->res_state), sizeof(vtm::ResidentState),
-                                  hipHostMallocMapped | hipHostMallocCoherent));
-            VTM_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&h->res_state_dev), h->res_state, 0));
-            h->resident = true;
-        }
-    }
+    if ((st = alloc_h(h.get())) != VTM_OK || (st = build_values(h.get())) != VTM_OK ||
+        (st = make_resident(h.get())) != VTM_OK || (st = build_columns(h.get())) != VTM_OK)
+        return st;
     if (h->tiles) {
         const TuneKey key{h->device, o.precision, nr, o.batch_row_tiles, o.batch_rhs_block, P.S, P.n, P.nports,
                           P.mofs[P.S], P.qmofs[P.S], P.max_ns, P.max_ports};
@@ -1842,7 +1936,10 @@ vtm_status vtm_refresh(vtm_handle h, const double* val, const double* Z, int64_t
         for (auto& kv : h->graphs) (void)hipGraphExecDestroy(kv.second);
         h->graphs.clear();
         h->waves_set = false;
-        return build_values(h);
+        st = build_values(h);
+        // the temporary inverses of a refresh come before copies that the handle can do without
+        if (st == VTM_E_OOM && give_up_copies(h) && (st = alloc_h(h)) == VTM_OK) st = build_values(h);
+        return st == VTM_OK ? build_columns(h) : st;
     });
 }
 
@@ -1900,6 +1997,15 @@ vtm_status vtm_info(vtm_handle h, int64_t* n, int64_t* n_sub, int64_t* n_wires, 
 int vtm_testing_wait_ticks(vtm_handle h, uint64_t ticks) {
     h->res_wait_ticks = ticks;
     return h->resident ? 1 : 0;
+}
+
+// For tests, not part of the interface: bounds the device memory that handles set up or
+// refreshed on the calling thread may take from now on (negative: no bound).  Returns the
+// least that was left under the bound before, or -1 without one.
+int64_t vtm_testing_memory(int64_t bytes) {
+    const int64_t low = t_memory.left < 0 ? -1 : t_memory.lowest;
+    t_memory.left = t_memory.lowest = bytes < 0 ? -1 : bytes;
+    return low;
 }
 
 void vtm_destroy(vtm_handle h) {
