@@ -54,7 +54,7 @@ class Circuit:
         self.precision = precision
         self.vccs = vccs
         self.solver_kw = solver_kw
-        self._g = None        # the conductances of the handle: a copy of its own, where they came from
+        self._g = None        # the conductances of the handle: an FP64 copy of its own, where they came from
         self._solver = None
         self._ij = None
         self.last_forward = None
@@ -67,24 +67,25 @@ class Circuit:
         gd = g.detach().contiguous()
         if not self._same(gd):
             self._g = None    # until the handle holds the new ones
-            gh = gd.to("cpu", torch.float64).numpy()
-            A = nodal_matrix(self.n, self.edges, gh, self.ground, self.vccs)
+            # the copy first, and the handle from the copy: g may change meanwhile.  Fetching
+            # it waits for it, so that a comparison on another stream finds it there.
+            kept = gd.to(torch.float64, copy=True)
+            A = nodal_matrix(self.n, self.edges, kept.cpu().numpy(), self.ground, self.vccs)
             if self._solver is None:
                 self._solver = Solver(A, self.part, self.Z, precision=self.precision, **self.solver_kw)
             else:
                 self._solver.refresh(A)
-            self._g = gd.clone()
+            self._g = kept
         return self._solver
 
     def _same(self, gd: torch.Tensor) -> bool:
-        """Whether gd holds the handle's conductances, bit for bit, compared where they
-        are (fetching 0.5 M of them to the host and comparing there took 1 ms of a 3 ms
+        """Whether gd holds the handle's conductances, bit for bit in FP64, compared where
+        they are (fetching 0.5 M of them to the host and comparing there took 1 ms of a 3 ms
         training step)."""
         old = self._g
-        if old is None or (old.shape, old.dtype, old.device) != (gd.shape, gd.dtype, gd.device):
+        if old is None or old.shape != gd.shape:
             return False
-        bits = {8: torch.int64, 4: torch.int32, 2: torch.int16, 1: torch.int8}[gd.element_size()]
-        return torch.equal(old.view(bits), gd.view(bits))
+        return torch.equal(old.to(gd.device).view(torch.int64), gd.to(torch.float64).view(torch.int64))
 
     def branch_ij(self, device) -> torch.Tensor:
         if self._ij is None or self._ij.device != device:
