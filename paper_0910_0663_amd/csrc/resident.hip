@@ -117,6 +117,10 @@ __device__ inline bool wait_for(bool want, F ready, u64* abort_word, unsigned ta
     }
 }
 
+// Bound of a wait that lasts as long as the run of n sweeps before it: 50 us more a sweep,
+// seven times what the slowest takes.
+__device__ inline u64 run_ticks(u64 ticks, unsigned n) { return ticks ? ticks + u64(n) * 5000 : 0; }
+
 // Shapes by the largest port count QB (per_simd: wavefronts a SIMD should hold, which
 // bounds the registers; more sub-circuits then fit the chip) of a sub-circuit.  Row p of the operator
 // (lane) is port p's node against every port's node: z_n(p) = sum_p' S(n_p, n_p') c_p' a_p'.
@@ -192,7 +196,8 @@ __device__ __forceinline__ void control(const ResidentArgs<T>& A, unsigned n) {
             double v = 0.0;
             const unsigned b = b0 + tid;
             const u64* const slot = A.sums + 2 * size_t(b < n ? b : 0);
-            if (!wait_for(b < n, [&] { return receive(slot, tag, v); }, abort_word, A.epoch + 1, A.wait_ticks)) {
+            if (!wait_for(b < n, [&] { return receive(slot, tag, v); }, abort_word, A.epoch + 1,
+                          run_ticks(A.wait_ticks, run))) {
                 bad = st->timeout = 1;
                 break;
             }
@@ -264,7 +269,7 @@ __device__ __forceinline__ void control(const ResidentArgs<T>& A, unsigned n) {
 }
 
 // One check of a sweeping workgroup: its sum of squares of the port residual is sent,
-// and next_s becomes the sweeps until the next check.  A thread of the first `waves`
+// and next_s, the sweeps since the check before, becomes those until the next one.  A thread of the first `waves`
 // wavefronts that is an owner holds port p, the entry base + row of first, cnt, xs and
 // vs.  False: a wait ran out.
 //
@@ -316,7 +321,7 @@ __device__ __forceinline__ bool residual_check(const ResidentArgs<T>& A, unsigne
                 nx = unsigned(v);
                 return unsigned(v >> 32) == tag;
             },
-            decision + 1, abort_tag, A.wait_ticks);
+            decision + 1, abort_tag, run_ticks(A.wait_ticks, next_s));  // (next_s: the sweeps before this check)
         if (!ok) bad = A.state->timeout = 1;
         next_s = nx;
     }
@@ -372,7 +377,7 @@ __global__ void __launch_bounds__((kThreads<QB, SUBS>), Shape<QB>::template per_
     ResidentState* const st = A.state;
 
     // ports of each node: node, first and count per port
-    if (tid == 0) bad = 0;
+    if (tid == 0) bad = 0, next_s = unsigned(A.ctl.first);
     if (cg == 0) {
         for (int j = row; j < (real ? k : 0); j += ROWS) {
             const int f0 = A.pn_pfirst[k0 + j] - p0, f1 = A.pn_pfirst[k0 + j + 1] - p0;
@@ -606,7 +611,7 @@ __global__ void __launch_bounds__(512, 2) k_resident_wide(ResidentArgs<double> A
     const __amdgpu_buffer_rsrc_t ops =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(A.op) + A.ofs[s], 0, k * k * 8, 0x00020000);
 
-    if (tid == 0) bad = 0;
+    if (tid == 0) bad = 0, next_s = unsigned(A.ctl.first);
     for (int j = tid; j < 16 * PAIRS; j += 512) tv[j] = 0.0;
     // this thread's port node, and the ports of each node
     int f0 = 0, f1 = 0;
@@ -799,7 +804,7 @@ __global__ void __launch_bounds__(512, 2) k_resident_wide_f(ResidentArgs<float> 
     const __amdgpu_buffer_rsrc_t ops =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(A.op) + A.ofs[s], 0, k * k * 4, 0x00020000);
 
-    if (tid == 0) bad = 0;
+    if (tid == 0) bad = 0, next_s = unsigned(A.ctl.first);
     for (int j = tid; j < 4 * GROUPS; j += 512) tv[j] = 0.0f;
     int f0 = 0, f1 = 0;
     if (tid < k) {
