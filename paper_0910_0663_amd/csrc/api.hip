@@ -1721,7 +1721,20 @@ static vtm_status make_resident(vtm_handle_s* h) {
     VTM_HIP(vtm::launch_fill<double>(int64_t(words), 0.0, h->res_slots.p, s));
     VTM_HIP(vtm::launch_fill<double>(int64_t(h->res_sums.count), 0.0, h->res_sums.p, s));
     h->resident = true;
-    return VTM_OK;
+    // one run of zeros: the queue that a process's first cooperative launch creates (3 ms) and
+    // the kernel's scratch memory then belong to the setup, not to a solve that may not
+    // allocate; a device that cannot run it shows here
+    vtm::ResidentControl ctl;
+    ctl.tol = ctl.bb = ctl.divergence = 1.0;
+    ctl.max_sweeps = ctl.first = 1;
+    int cur = 0;
+    bool lost = false;
+    if (fp64) {
+        VTM_HIP(vtm::launch_fill<double>(P.nports, 0.0, h->h64.p, s));
+        return run_resident<double>(h, ctl, false, cur, lost);
+    }
+    VTM_HIP(vtm::launch_fill<float>(P.nports, 0.0f, h->h32.p, s));
+    return run_resident<float>(h, ctl, false, cur, lost);
 }
 
 // The handle's structure (index arrays, work buffers, which local forms run), then its
