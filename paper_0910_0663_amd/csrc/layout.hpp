@@ -90,6 +90,18 @@ __device__ inline T packed_wave_out(T w2c, T c, T z, T a, T h) {
         return h + __builtin_fmaf(a, g, v);
 }
 
+// a b + c, rounded once
+__device__ inline double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ inline float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
+// The outgoing wave in the dense port-node form, beta z + gamma a + h, in one stated way too.
+template <typename T>
+__device__ inline T dense_wave_out(T beta, T z, T gamma, T a, T h) {
+#pragma clang fp contract(off)
+    const T g = gamma * a;
+    return fused(beta, z, g) + h;
+}
+
 // elements reserved for an n x n block (rounded up to a multiple of 4)
 __host__ __device__ inline int64_t inv_block_elems(int n) { return (int64_t(n) * n + 3) & ~int64_t(3); }
 

@@ -334,7 +334,7 @@ __global__ void __launch_bounds__(512)
         const int f0 = pn_pfirst[k0 + j], f1 = pn_pfirst[k0 + j + 1];
         TV acc = TV(0);
         for (int p = f0; p < f1; ++p) {
-            acc += pc[p] * a_cur[p];
+            acc = fused(pc[p], a_cur[p], acc);
             pnode[p - p0] = j;
         }
         tv[j] = acc;
@@ -352,9 +352,10 @@ __global__ void __launch_bounds__(512)
                 TO v[G];
                 load16p<TO, decltype(nt)::value>(Ss + (int64_t(g) * k + row) * G, v);
 #pragma unroll
-                for (int j = 0; j < G; ++j) acc[j] += TV(v[j]) * tv[g * G + j];
+                for (int j = 0; j < G; ++j) acc[j] = fused(TV(v[j]), tv[g * G + j], acc[j]);
             }
-            for (int c = full; c < k; ++c) acc[0] += TV(Ss[int64_t(full) * k + int64_t(c - full) * k + row]) * tv[c];
+            for (int c = full; c < k; ++c)
+                acc[0] = fused(TV(Ss[int64_t(full) * k + int64_t(c - full) * k + row]), tv[c], acc[0]);
             TV v = acc[0];
 #pragma unroll
             for (int j = 1; j < G; ++j) v += acc[j];
@@ -371,7 +372,7 @@ __global__ void __launch_bounds__(512)
     }
     __syncthreads();
     for (int p = p0 + tid; p < p1; p += bs)
-        a_next[port_twin[p]] = pbeta[p] * zv[pnode[p - p0]] + pgamma[p] * a_cur[p] + h[p];
+        a_next[port_twin[p]] = dense_wave_out<TV>(pbeta[p], zv[pnode[p - p0]], pgamma[p], a_cur[p], h[p]);
 }
 
 // The same in FP64, 64 rows per workgroup: their columns spread over KS wavefronts, whose

@@ -124,6 +124,8 @@ __device__ inline u64 run_ticks(u64 ticks, unsigned n) { return ticks ? ticks + 
 // Shapes by the largest port count QB (per_simd: wavefronts a SIMD should hold, which
 // bounds the registers; more sub-circuits then fit the chip) of a sub-circuit.  Row p of the operator
 // (lane) is port p's node against every port's node: z_n(p) = sum_p' S(n_p, n_p') c_p' a_p'.
+// As compiled, FP64 of up to 32, 64 and 128 ports spills 6 to 9 registers and FP32 in sixteens
+// one, all written once before the sweeps.
 // Up to 32 ports, a wavefront takes two sub-circuits, all 32 columns of a row in a
 // lane (64 registers in FP64), and a workgroup one wavefront or eight (kManySubs).  Above, a workgroup takes one: RG groups of 64 rows
 // by CG groups of COLS columns, the partial sums meeting in LDS; 16-32 columns a lane
@@ -570,7 +572,8 @@ __global__ void __launch_bounds__((kThreads<QB, SUBS>), Shape<QB>::template per_
 // launch a sweep reads every operator from the memory-side cache.  Solves, a launch per
 // sweep and resident: 210 sub-circuits of 296 port nodes (44x40x52) 10.8 -> 4.7 ms, 7.2 us
 // a sweep for 18; 105 of them 7.2 -> 3.6; 216 of 218 (42x42x42 in blocks of 7) 9.9 -> 2.8;
-// 64 of 196 (400x400 in blocks of 50) 1.95 -> 1.28.  Eight pairs in registers: nine spill.
+// 64 of 196 (400x400 in blocks of 50) 1.95 -> 1.28.  RG = 5 spills 11 registers with
+// eight pairs in registers, written once and read in the sweeps; with nine pairs 37.
 template <int RG>
 struct Wide {
     static constexpr int PAIRS = 4 * RG;  // 32 RG column pairs over eight wavefronts
@@ -907,7 +910,7 @@ __global__ void __launch_bounds__(512, 2) k_resident_wide_f(ResidentArgs<float> 
             float z = part[n];
 #pragma unroll
             for (int j = 1; j < 4; ++j) z += part[j * ROWS + n];
-            o = __builtin_fmaf(be, z, ga * a) + h;  // rounded as in k_sweep_ppn
+            o = dense_wave_out<float>(be, z, ga, a, h);
             send(slots, set + unsigned(tw), o, tag);
         }
         if (!wait_for(owner, [&] { return receive(slots, set + unsigned(p), tag, an); }, abort_word, abort_tag,
