@@ -488,10 +488,11 @@ hipError_t launch_sweep_ppn(int S, int max_npn, int max_ports, int64_t op_bytes,
                             const TV* a_cur, TV* a_next, int reverse, hipStream_t st) {
     const size_t lds = 2 * size_t(max_npn) * sizeof(TV) + size_t(max_ports) * 4;
     if (lds > 65536) return hipErrorInvalidValue;
-    // Above the memory-side cache every other sweep walks backwards and finds in it what the
-    // sweep before read last (FP32, one order / alternating: 288 MB 55.0 / 54.2 us a sweep, 387
-    // MB 87.1 / 80.8); up to it one order does the same (90 MB 17.8 / 17.8, 210 MB 39.2 / 39.2),
-    // and one workgroup per sub-circuit keeps to it.
+    // Every other sweep walks backwards and finds in the caches what the sweep before read
+    // last (FP32, one order / alternating: 3,720 sub-circuits of random cuts, 75 MB, 11.5 / 11.1
+    // us a sweep, 5,852 of them 17.6 / 16.0, 288 MB in blocks of 8 55.0 / 54.2, 387 MB 87.1 /
+    // 80.8; 28 more circuits of 56 to 225 MB, even and ragged, FP32 and FP64, the same within
+    // 1%, as two runs of one kernel differ).
     // Up to twice the cache, plain loads reuse more of it
     // (358 MB: 30.9 ms a solve, 31.4 with the share that fits kept, 29.8 with none kept; 192
     // MB: 17.2, and 21-23 with any non-temporal); above, the share that fits is kept (700 MB:
@@ -524,7 +525,6 @@ hipError_t launch_sweep_ppn(int S, int max_npn, int max_ports, int64_t op_bytes,
             return hipGetLastError();
         }
     }
-    if (op_bytes <= kCache) reverse = 0;
     // one pass over the rows where possible
     const int bs = std::min(512, std::max(64, ((max_npn + 63) / 64) * 64));
     auto kern = keep == 16 ? k_sweep_ppn<TO, TV, false> : k_sweep_ppn<TO, TV, true>;
