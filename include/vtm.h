@@ -319,8 +319,9 @@ vtm_status vtm_vertex_sca(const vtm_csr *A, const int32_t *label, const int32_t 
  * every sub-circuit has at most 512 ports, on at most 320 nodes, and the device
  * holds all of them at once, the port-to-port sweeps
  * and checks of a solve (of an inner solve when refining) are one cooperative
- * launch.  Same sweeps, checks and residual history.  opt.timing runs a launch per
- * sweep.  vtm_setup tries such a launch once: a process's first takes 4 to 5 ms, for the
+ * launch.  Sweeps, checks and history are those of a launch per sweep (opt.timing runs
+ * one), in FP32 to the bit, in FP64 to the rounding of sums in another order, which could
+ * move a residual that equals tol to another check.  vtm_setup tries such a launch once: a process's first takes 4 to 5 ms, for the
  * queue that the runtime creates for it (four solves of a 64 x 64 grid bring them in).  A run that waits 4 s for a sweep (other work holds compute units) ends; its
  * solve starts over, and the handle then launches per sweep.
  *

@@ -19,6 +19,7 @@
 #include "plan.hpp"
 #include "resident.hpp"
 #include "status.hpp"
+#include "testing.hpp"
 #include "vtm.h"
 
 namespace {
@@ -2004,17 +2005,19 @@ vtm_status vtm_info(vtm_handle h, int64_t* n, int64_t* n_sub, int64_t* n_wires, 
     });
 }
 
-// For tests, not part of the interface: bounds every wait of h's resident runs to
-// `ticks` of 10 ns (0: one try), to exercise the way back to a launch per sweep.
-// Returns whether h runs resident.
 int vtm_testing_wait_ticks(vtm_handle h, uint64_t ticks) {
+    if (!h) return 0;
     h->res_wait_ticks = ticks;
     return h->resident ? 1 : 0;
 }
 
-// For tests, not part of the interface: bounds the device memory that handles set up or
-// refreshed on the calling thread may take from now on (negative: no bound).  Returns the
-// least that was left under the bound before, or -1 without one.
+uint32_t vtm_testing_epoch(vtm_handle h, uint32_t epoch) {
+    if (!h) return 0;
+    const uint32_t was = h->res_epoch;
+    h->res_epoch = epoch;
+    return was;
+}
+
 int64_t vtm_testing_memory(int64_t bytes) {
     const int64_t low = t_memory.left < 0 ? -1 : t_memory.lowest;
     t_memory.left = t_memory.lowest = bytes < 0 ? -1 : bytes;
