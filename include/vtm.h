@@ -317,13 +317,15 @@ vtm_status vtm_vertex_sca(const vtm_csr *A, const int32_t *label, const int32_t 
  *
  * One right-hand side on a small circuit torn at branches runs resident: when
  * every sub-circuit has at most 512 ports, on at most 320 nodes, and the device
- * holds all of them at once, the port-to-port sweeps
- * and checks of a solve (of an inner solve when refining) are one cooperative
- * launch.  Sweeps, checks and history are those of a launch per sweep (opt.timing runs
- * one), in FP32 to the bit, in FP64 to the rounding of sums in another order, which could
- * move a residual that equals tol to another check.  vtm_setup tries such a launch once: a process's first takes 4 to 5 ms, for the
- * queue that the runtime creates for it (four solves of a 64 x 64 grid bring them in).  A run that waits 4 s for a sweep (other work holds compute units) ends; its
- * solve starts over, and the handle then launches per sweep.
+ * holds all of them at once, the port-to-port sweeps and checks of a solve (of an
+ * inner solve when refining) are one cooperative launch.  Sweeps, checks and
+ * history are those of a launch per sweep (opt.timing runs one), in FP32 to the
+ * bit, in FP64 to the rounding of sums in another order, which could move a
+ * residual that equals tol to another check.  vtm_setup tries such a launch once:
+ * a process's first takes 4 to 5 ms, for the queue that the runtime creates for it
+ * (four solves of a 64 x 64 grid bring them in).  A run that waits 4 s for a sweep
+ * (other work holds compute units) ends; its solve starts over, and the handle then
+ * launches per sweep.
  *
  * A zero column converges at once with x = 0.  With a refining precision the
  * sweeps run in FP32/BF16 on A d = r and x += d, r = b - A x in FP64, until

@@ -664,9 +664,12 @@ __global__ void __launch_bounds__(512, 2) k_resident_wide(ResidentArgs<double> A
     unsigned left = unsigned(A.ctl.first);
     unsigned tag = A.epoch;
     const unsigned abort_tag = A.epoch + 1;
+    // whether the streamed pairs go backwards in a sweep: by its number in the solve, not by
+    // its tag, whose parity earlier solves leave either way (the order shows in the sums' bits)
+    auto backwards = [&](unsigned t) { return ((t ^ A.epoch ^ unsigned(A.ctl.sweeps)) & 1u) != 0; };
     if constexpr (ST > 0) {
 #pragma unroll
-        for (int e = 0; e < AHEAD; ++e) stream(e, (tag + 1) & 1, sv[e]);
+        for (int e = 0; e < AHEAD; ++e) stream(e, backwards(tag + 1), sv[e]);
     }
 
     while (true) {
@@ -705,7 +708,7 @@ __global__ void __launch_bounds__(512, 2) k_resident_wide(ResidentArgs<double> A
             asm volatile("" : "+v"(acc[0]) : : "memory");
         }
         if constexpr (ST > 0) {
-            const bool back = tag & 1;
+            const bool back = backwards(tag);
             for (int e0 = 0; e0 < count; e0 += AHEAD) {
 #pragma unroll
                 for (int e = 0; e < AHEAD; ++e) {
@@ -736,7 +739,7 @@ __global__ void __launch_bounds__(512, 2) k_resident_wide(ResidentArgs<double> A
         // the next sweep's first streamed pairs are on their way while the waves are
         if constexpr (ST > 0) {
 #pragma unroll
-            for (int e = 0; e < AHEAD; ++e) stream(e, (tag + 1) & 1, sv[e]);
+            for (int e = 0; e < AHEAD; ++e) stream(e, backwards(tag + 1), sv[e]);
         }
         if (!wait_for(owner, [&] { return receive(slots, set + unsigned(p), tag, an); }, abort_word, abort_tag,
                       A.wait_ticks))
