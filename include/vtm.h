@@ -323,9 +323,10 @@ vtm_status vtm_vertex_sca(const vtm_csr *A, const int32_t *label, const int32_t 
  * bit, in FP64 to the rounding of sums in another order, which could move a
  * residual that equals tol to another check.  vtm_setup tries such a launch once:
  * a process's first takes 4 to 5 ms, for the queue that the runtime creates for it
- * (four solves of a 64 x 64 grid bring them in).  A run that waits 4 s for a sweep
- * (other work holds compute units) ends; its solve starts over, and the handle then
- * launches per sweep.
+ * (four solves of a 64 x 64 grid bring them in).  A device runs cooperative launches
+ * of one process at a time: where it refuses one (0.1 s), handles set up within the
+ * next minute launch per sweep.  A run that waits 4 s for a sweep (other work holds
+ * compute units) ends; its solve starts over, and the handle then launches per sweep.
  *
  * A zero column converges at once with x = 0.  With a refining precision the
  * sweeps run in FP32/BF16 on A d = r and x += d, r = b - A x in FP64, until

@@ -152,6 +152,22 @@ struct TuneKey {
 std::mutex g_tune_mu;
 std::map<TuneKey, std::array<int, 4>> g_tune;  // mfma variant, mfma rc, pp variant, pp rc
 
+// When a device last refused this process a cooperative launch (it gives them to one process
+// at a time, and a refusal takes 45 ms): new handles do not try again within a minute.
+std::mutex g_refused_mu;
+std::map<int, std::chrono::steady_clock::time_point> g_refused;
+
+void note_refusal(int device) {
+    std::lock_guard<std::mutex> lock(g_refused_mu);
+    g_refused[device] = std::chrono::steady_clock::now();
+}
+
+bool refused_lately(int device) {
+    std::lock_guard<std::mutex> lock(g_refused_mu);
+    const auto it = g_refused.find(device);
+    return it != g_refused.end() && std::chrono::steady_clock::now() - it->second < std::chrono::minutes(1);
+}
+
 }  // namespace
 
 struct vtm_handle_s {
@@ -861,6 +877,7 @@ vtm_status run_resident(vtm_handle h, const vtm::ResidentControl& ctl, bool adjo
     const hipError_t e = vtm::launch_resident<T>(a, P.max_npn, P.max_ports, h->stream);
     if (e != hipSuccess) {
         (void)hipGetLastError();
+        note_refusal(h->device);
         h->resident = false;
         lost = true;
         return VTM_OK;
@@ -1703,7 +1720,7 @@ static vtm_status make_resident(vtm_handle_s* h) {
     if (!(h->pps || h->ppn) || P.vertex) return VTM_OK;
     const int blocks = fp64 ? vtm::resident_blocks<double>(int(P.S), P.max_npn, P.max_ports, h->pps)
                             : vtm::resident_blocks<float>(int(P.S), P.max_npn, P.max_ports, h->pps);
-    if (blocks == 0) return VTM_OK;
+    if (blocks == 0 || refused_lately(h->device)) return VTM_OK;
     const size_t words = fp64 ? vtm::resident_slot_words<double>(P.nports) : vtm::resident_slot_words<float>(P.nports);
     hipError_t e = h->res_slots.alloc(words);
     if (e == hipSuccess) e = h->res_sums.alloc(2 * size_t(blocks) + 2);

@@ -37,3 +37,43 @@ def taken(timing):
 
 def test_first_solve_takes_no_memory_for_a_cooperative_launch():
     assert taken(0) <= taken(1)
+
+
+SECOND = """
+import ctypes as C
+import time
+import torch
+import paper_0910_0663_amd as vtm
+import workloads
+w = workloads.make(1)
+b = torch.as_tensor(w.b, device="cuda")
+f = vtm.lib().vtm_testing_wait_ticks
+f.argtypes, f.restype = [C.c_void_p, C.c_uint64], C.c_int
+took, kept = [], []
+for k in range(4):
+    torch.cuda.synchronize()
+    t = time.perf_counter()
+    kept.append(vtm.Solver(w.A, w.part, w.Z))
+    kept[-1].solve(b, 1e-10)
+    took.append(time.perf_counter() - t)
+print("resident", f(kept[0]._h, 400_000_000), *took)
+"""
+
+
+def test_a_process_that_is_refused_asks_once():
+    """A device gives cooperative launches to one process.  Another one's handles work, and
+    only the first waits for the refusal (0.12 s; 0.045 s again for each that asks again,
+    where a setup and a solve take 0.006 s)."""
+    import torch
+    import paper_0910_0663_amd as vtm
+    import workloads
+    w = workloads.make(1)
+    s = vtm.Solver(w.A, w.part, w.Z)
+    s.solve(torch.as_tensor(w.b, device="cuda"), 1e-10)
+    out = subprocess.run([sys.executable, "-c", SECOND], cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert out.returncode == 0, out.stderr[-2000:]
+    words = out.stdout.split()
+    resident, took = int(words[words.index("resident") + 1]), [float(v) for v in words[words.index("resident") + 2:]]
+    if not resident:
+        assert min(took[1:]) < 0.025, took
+    s.close()
