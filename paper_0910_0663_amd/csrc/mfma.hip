@@ -131,27 +131,26 @@ __device__ inline void tile_gemm(const T* Ablk, int mt_n, int kt_n, const T* sb,
 #pragma unroll
             for (int j = 0; j < RT; ++j)
                 if (j < nmy && d < KT) abuf[d][j] = A0[(int64_t(mts[j]) * KT + d) * 64];
+        auto step = [&](int k, int h) {  // k tile k, in ring slot h (compile-time)
+            if (k + PD - 1 < KT) {
+#pragma unroll
+                for (int j = 0; j < RT; ++j)
+                    if (j < nmy) abuf[(h + PD - 1) % PD][j] = A0[(int64_t(mts[j]) * KT + k + PD - 1) * 64];
+            }
+            typename M::BFrag bf[NT];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) bf[nt] = M::bfrag(sb, bsel, k, nt);
+#pragma unroll
+            for (int j = 0; j < RT; ++j)
+                if (j < nmy)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+                        if (nt * 16 < w) acc[j][nt] = M::mma(abuf[h][j], bf[nt], acc[j][nt]);
+        };
         for (int kt = 0; kt < KT; kt += PD) {
 #pragma unroll
-            for (int h = 0; h < PD; ++h) {
-                const int k = kt + h;
-                if (k < KT) {
-                    if (k + PD - 1 < KT) {
-#pragma unroll
-                        for (int j = 0; j < RT; ++j)
-                            if (j < nmy) abuf[(h + PD - 1) % PD][j] = A0[(int64_t(mts[j]) * KT + k + PD - 1) * 64];
-                    }
-                    typename M::BFrag bf[NT];
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) bf[nt] = M::bfrag(sb, bsel, k, nt);
-#pragma unroll
-                    for (int j = 0; j < RT; ++j)
-                        if (j < nmy)
-#pragma unroll
-                            for (int nt = 0; nt < NT; ++nt)
-                                if (nt * 16 < w) acc[j][nt] = M::mma(abuf[h][j], bf[nt], acc[j][nt]);
-                }
-            }
+            for (int h = 0; h < PD; ++h)
+                if (kt + h < KT) step(kt + h, h);
         }
 #pragma unroll
         for (int j = 0; j < RT; ++j) {
@@ -366,6 +365,16 @@ __global__ void __launch_bounds__(kBlock)
     }
 }
 
+// Wavefronts a SIMD that an instance of the sweep below has to leave room for (0: as it comes
+// out).  Without it these take one or a few registers more than that many may hold, and a
+// workgroup less fits a compute unit: 150 sub-circuits of 384 ports, FP64, 20 right-hand
+// sides 53.6 us a sweep, with it 43.2; 5,625 of 32, BF16, 64 right-hand sides 25.0 and 22.3.
+template <typename T, int NT, int RT, int WAVES, bool HL>
+constexpr int pp_waves() {
+    if (sizeof(T) == 8) return NT == 1 && RT == 3 && WAVES == 8 ? 4 : 0;
+    return RT == 1 && WAVES == 4 && (NT <= 2 || (NT == 3 && !HL)) ? 8 : 0;
+}
+
 // Batched port-to-port sweep (the Appendix's interface-only iteration, eqs.
 // 23-26, for many right-hand sides): block (y, s) forms
 //   a_next[twin(p)][r] = h[p][r] + sum_p' M_s[p][p'] a_cur[p'][r]
@@ -375,7 +384,7 @@ __global__ void __launch_bounds__(kBlock)
 // path, FP32 accumulate).  WAVES wavefronts per workgroup (the operators are
 // small: 64 ports make four 16-row tiles).
 template <typename T, int NT, int RT, int WAVES, bool HL>
-__global__ void __launch_bounds__(WAVES * 64)
+__global__ void __launch_bounds__(WAVES * 64, (pp_waves<T, NT, RT, WAVES, HL>()))
     k_sweep_mfma_pp(const T* __restrict__ Mop, const int64_t* __restrict__ qmofs,
                     const int32_t* __restrict__ port_off, const int32_t* __restrict__ port_twin,
                     const typename Mma<T>::TV* __restrict__ h, const typename Mma<T>::TV* __restrict__ a_cur,
@@ -409,40 +418,54 @@ __global__ void __launch_bounds__(WAVES * 64)
     // FP64: h of the outputs this lane will produce, loaded into registers before the
     // product so that the epilogue does not wait on it (when one pass of row tiles
     // covers the operator); BF16 stages h in LDS instead (registers cost occupancy)
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
+    // one row tile a wavefront: those without one skip the loads by a scalar branch
+    const int wave = RT == 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
     constexpr bool kPre = sizeof(T) == 8;
     const bool one = mt_n <= WAVES * RT;   // one pass of row tiles covers the operator
     const bool pre = kPre && one;
-    // (wavefronts without a row tile skip it: a scalar branch)
     TV hreg[kPre ? RT * NT * 4 : 1];
+    int twr[RT * 4];  // twin port of each output row, loaded before the product too
+    if constexpr (RT == 1) {
+        const bool tile = one && wave < mt_n;
 #pragma unroll
-    for (int j = 0; j < (kPre ? RT : 0); ++j) {
-        const bool tile = pre && wave + j * WAVES < mt_n;
+        for (int i = 0; i < (kPre ? NT * 4 : 0); ++i) hreg[i] = TV(0);
 #pragma unroll
-        for (int i = 0; i < NT * 4; ++i) hreg[j * NT * 4 + i] = TV(0);
+        for (int v = 0; v < 4; ++v) twr[v] = 0;
+        if (kPre && tile) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int row = wave * 16 + M::out_row(lane, v), n = nt * 16 + (lane & 15);
+                    if (row < q && n < w) hreg[kPre ? nt * 4 + v : 0] = h[int64_t(p0 + row) * nrhs + r0 + n];
+                }
+        }
         if (tile) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = wave * 16 + M::out_row(lane, v);
+                if (row < q) twr[v] = port_twin[p0 + row];
+            }
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < (kPre ? RT : 0); ++j)
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int row = (wave + j * WAVES) * 16 + M::out_row(lane, v), n = nt * 16 + (lane & 15);
-                    if (row < q && n < w) hreg[(j * NT + nt) * 4 + v] = h[int64_t(p0 + row) * nrhs + r0 + n];
+                    hreg[(j * NT + nt) * 4 + v] =
+                        pre && row < q && n < w ? h[int64_t(p0 + row) * nrhs + r0 + n] : TV(0);
                 }
-        }
-    }
-    // twin port of each output row, loaded before the product (one pass of row tiles)
-    int twr[RT * 4];
 #pragma unroll
-    for (int j = 0; j < RT; ++j) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) twr[j * 4 + v] = 0;
-        if (one && wave + j * WAVES < mt_n) {
+        for (int j = 0; j < RT; ++j)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int row = (wave + j * WAVES) * 16 + M::out_row(lane, v);
-                if (row < q) twr[j * 4 + v] = port_twin[p0 + row];
+                twr[j * 4 + v] = one && row < q ? port_twin[p0 + row] : 0;
             }
-        }
     }
     // BF16 (HL): h of this block staged in LDS beside the waves (its loads overlap
     // theirs); the launch drops HL when there is no room for it (very large operators)
