@@ -820,14 +820,19 @@ __device__ inline double shift_up(double v) {
 // end of a pair reads zeros, so that nothing of one sub-circuit is shifted into the other.
 // FP32 keeps the shuffles, and with them the order of its sums: its inner solves stop near
 // the rounding floor, where another order moves the sweep at which they stop.
+// NCH: chunks of diagonals held, all that the largest sub-circuit has.  With four a wavefront
+// takes 94 registers; operators of up to 8 port nodes need one, and their sweeps as many
+// wavefronts as fit (111,556 sub-circuits of 8, 1000 x 1000 in 3x3 blocks: shuffled 25.6 us a
+// sweep, four chunks 26.3, one 19.7; 250,000 of 4: 52.3, 54.7, 39.1).
+template <int NCH>
 __device__ inline void pps_pair64(int unit, int S, const double* __restrict__ Sp, const int64_t* __restrict__ sofs,
                                   const int32_t* __restrict__ pn_off, const int32_t* __restrict__ pn_pfirst,
                                   const int32_t* __restrict__ port_off, const int32_t* __restrict__ port_twin,
                                   const double* __restrict__ pc, const double* __restrict__ pW, double W,
                                   const double* __restrict__ h, const double* __restrict__ a_cur,
                                   double* __restrict__ a_next, double* ca, double* tv, double* zv, int32_t* pnode) {
-    constexpr int L = 32, CH = kPpsChunk, NCH = L / CH, PRE = kPpsPre64;
-    static_assert(L % CH == 0 && CH % 2 == 0 && PRE >= 1 && PRE <= NCH, "whole pairs in chunks that tile the lanes");
+    constexpr int L = 32, CH = kPpsChunk, PRE = kPpsPre64 < NCH ? kPpsPre64 : NCH;
+    static_assert(L % CH == 0 && NCH * CH <= L && CH % 2 == 0 && PRE >= 1 && PRE <= NCH, "whole pairs in chunks that tile the lanes");
     const int tid = threadIdx.x, r = tid % L, hb = tid - r, half = tid / L;
     const int tb = half * 64;  // this sub-circuit's t region
     // wave-uniform offsets of the two sub-circuits, indices clamped to S
@@ -861,7 +866,7 @@ __device__ inline void pps_pair64(int unit, int S, const double* __restrict__ Sp
         const int nx = __shfl(f0, tid + 1);  // lane r + 1's first port (the last lane: q)
         f1 = r + 1 < k ? nx : q;
     }
-    double buf[L];  // diagonal d of this lane's row (compile-time indices only)
+    double buf[NCH * CH];  // diagonal d of this lane's row (compile-time indices only)
     auto load = [&](int ci) {
 #pragma unroll
         for (int j = 0; j < CH / 2; ++j) {
@@ -912,8 +917,8 @@ __device__ inline void pps_pair64(int unit, int S, const double* __restrict__ Sp
 }
 
 // One workgroup (one wavefront) per unit: a pair of sub-circuits when HALF (then FP64
-// takes pps_pair64).
-template <typename TO, typename TV, bool HALF>
+// takes pps_pair64, of NCH chunks).
+template <typename TO, typename TV, bool HALF, int NCH>
 __global__ void __launch_bounds__(64)
     k_sweep_pps(int S, const TO* __restrict__ Sp, const int64_t* __restrict__ sofs,
                 const int32_t* __restrict__ pn_off, const int32_t* __restrict__ pn_pfirst,
@@ -927,8 +932,8 @@ __global__ void __launch_bounds__(64)
     // memory-side cache), while each XCD keeps the same units (and its L2)
     const int unit = reverse ? xcd_block_reversed(blockIdx.x, gridDim.x) : xcd_block(blockIdx.x, gridDim.x);
     if constexpr (HALF && sizeof(TO) == 8)
-        pps_pair64(unit, S, Sp, sofs, pn_off, pn_pfirst, port_off, port_twin, pc, pW, W, h, a_cur, a_next, ca, tv, zv,
-                   pnode);
+        pps_pair64<NCH>(unit, S, Sp, sofs, pn_off, pn_pfirst, port_off, port_twin, pc, pW, W, h, a_cur, a_next, ca, tv,
+                        zv, pnode);
     else
         pps_unit<TO, TV, HALF>(unit, S, Sp, sofs, pn_off, pn_pfirst, port_off, port_twin, pc, pW, W, h, a_cur, a_next,
                                ca, tv, zv, pnode);
@@ -1042,12 +1047,12 @@ hipError_t launch_port_node_matrix(int S, const int32_t* sub_off, const int64_t*
     return hipGetLastError();
 }
 
-template <typename TO, typename TV, bool HALF>
+template <typename TO, typename TV, bool HALF, int NCH>
 hipError_t launch_pps(int S, const TO* Sp, const int64_t* sofs, const int32_t* pn_off, const int32_t* pn_pfirst,
                       const int32_t* port_off, const int32_t* port_twin, const TV* pc, const TV* pW, TV W,
                       const TV* h, const TV* a_cur, TV* a_next, int reverse, hipStream_t st) {
     const int units = HALF ? (S + 1) / 2 : S;
-    hipLaunchKernelGGL((k_sweep_pps<TO, TV, HALF>), dim3(units), dim3(64), 0, st, S, Sp, sofs, pn_off, pn_pfirst,
+    hipLaunchKernelGGL((k_sweep_pps<TO, TV, HALF, NCH>), dim3(units), dim3(64), 0, st, S, Sp, sofs, pn_off, pn_pfirst,
                        port_off, port_twin, pc, pW, W, h, a_cur, a_next, reverse);
     return hipGetLastError();
 }
@@ -1059,8 +1064,12 @@ hipError_t launch_sweep_pps(int S, int max_npn, int max_ports, const TO* Sp, con
                             const TV* a_cur, TV* a_next, int reverse, hipStream_t st) {
     if (max_npn > 64 || max_ports > 64) return hipErrorInvalidValue;
     if (S == 0) return hipSuccess;
+    if constexpr (sizeof(TO) == 8)
+        if (max_npn <= kPpsChunk && max_ports <= 32)
+            return launch_pps<TO, TV, true, 1>(S, Sp, sofs, pn_off, pn_pfirst, port_off, port_twin, pc, pW, W, h, a_cur,
+                                               a_next, reverse, st);
     if (max_npn <= 32 && max_ports <= 32)
-        return launch_pps<TO, TV, true>(S, Sp, sofs, pn_off, pn_pfirst, port_off, port_twin, pc, pW, W, h, a_cur,
+        return launch_pps<TO, TV, true, 32 / kPpsChunk>(S, Sp, sofs, pn_off, pn_pfirst, port_off, port_twin, pc, pW, W, h, a_cur,
                                         a_next, reverse, st);
     hipLaunchKernelGGL((k_sweep_pps_split<TO, TV, kPpsSplit>), dim3(S), dim3(64 * kPpsSplit), 0, st, Sp, sofs, pn_off,
                        pn_pfirst, port_off, port_twin, pc, pW, W, h, a_cur, a_next, reverse);
