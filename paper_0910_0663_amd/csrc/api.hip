@@ -1681,7 +1681,7 @@ static vtm_status build_columns(vtm_handle_s* h) {
         hipError_t e = fp64 ? grow(h->h64) : grow(h->h32);
         if (e != hipSuccess || !tiles) return e;
         const int64_t nt = h->ntofs_host[P.S];
-        if ((e = h->ntofs.upload(h->ntofs_host, s)) != hipSuccess) return e;
+        if (!h->ntofs.p && (e = h->ntofs.upload(h->ntofs_host, s)) != hipSuccess) return e;
         e = fp64 ? h->Nt64.alloc(nt) : h->Nt32.alloc(nt);
         if (e == hipSuccess && !P.symmetric) e = fp64 ? h->Nt64T.alloc(nt) : h->Nt32T.alloc(nt);
         return e;

@@ -1131,19 +1131,25 @@ __global__ void __launch_bounds__(256)
     const int s = blockIdx.x;
     const int ns = sub_off[s + 1] - sub_off[s];
     const int k0 = pn_off[s], k = pn_off[s + 1] - k0;
-    const int np = node_tile_pad(k);
+    constexpr int KT = 64 / int(sizeof(T)), E = KT / 4;
+    const int np = node_tile_pad(k), kt_n = np / KT, units = np / 16 * kt_n * 64;
     const T* Ks = K + kofs[s];
     T* out = Nt + ntofs[s];
-    const int64_t cnt = int64_t(np) * np;
-    for (int64_t d = threadIdx.x; d < cnt; d += blockDim.x) {
-        int r, c;
-        node_tile_rc<T>(np, d, r, c);
-        T v = T(0);
-        if (r < k && c < k) {
-            const int i = pn_node[k0 + (transpose ? c : r)], j = pn_node[k0 + (transpose ? r : c)];
-            v = Ks[inv_offset<T>(ns, i, j)];
+    // a thread the 16 bytes of one lane in one tile (node_tile_rc)
+    for (int u = blockIdx.y * blockDim.x + threadIdx.x; u < units; u += blockDim.x * gridDim.y) {
+        const int tile = u >> 6, lane = u & 63, mt = tile / kt_n, kt = tile - mt * kt_n;
+        const int r = mt * 16 + (lane & 15), c0 = kt * KT + (lane >> 4);
+        const int nr = r < k ? pn_node[k0 + r] : 0;
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            const int c = c0 + 4 * j;
+            T v = T(0);
+            if (r < k && c < k) {
+                const int nc = pn_node[k0 + c];
+                v = Ks[transpose ? inv_offset<T>(ns, nc, nr) : inv_offset<T>(ns, nr, nc)];
+            }
+            out[int64_t(u) * E + j] = v;
         }
-        out[d] = v;
     }
 }
 
@@ -1309,7 +1315,10 @@ template <typename T>
 hipError_t launch_port_node_tiles(int S, const int32_t* sub_off, const int64_t* kofs, const int32_t* pn_off,
                                   const int32_t* pn_node, const T* K, const int64_t* ntofs, T* Nt, bool transpose,
                                   hipStream_t st) {
-    hipLaunchKernelGGL(k_port_node_tiles<T>, dim3(S), dim3(256), 0, st, sub_off, kofs, pn_off, pn_node, K, ntofs, Nt,
+    if (S == 0) return hipSuccess;
+    // few sub-circuits: up to 32 workgroups each
+    const int y = std::max(1, std::min(32, 4 * compute_units() / S));
+    hipLaunchKernelGGL(k_port_node_tiles<T>, dim3(S, y), dim3(256), 0, st, sub_off, kofs, pn_off, pn_node, K, ntofs, Nt,
                        transpose ? 1 : 0);
     return hipGetLastError();
 }
