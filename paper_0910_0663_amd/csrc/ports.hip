@@ -503,18 +503,21 @@ hipError_t launch_sweep_ppn(int S, int max_npn, int max_ports, int64_t op_bytes,
     // enough of it or the sub-circuits alone do not fill the chip (solves, one workgroup per
     // sub-circuit / spread: 105 of 296 port nodes 11.0 / 7.2 ms, 512 of 98 8.6 / 6.7, 1,728 of
     // 98 21.4 / 23.9, 1,764 of 92 5.1 / 5.5, 961 of 124 5.37 / 5.18, 1,000 of 152 20.2 / 19.1,
-    // 576 of 296 30.5 / 27.8, 729 of 296 48.9 / 40.5).  Large ones that are nearly as many as
-    // the compute units keep a workgroup each, where the operators fit the cache: their five
-    // or six wavefronts on every unit stream from it at 7.3 TB/s, and spread out they make
+    // 576 of 296 30.5 / 27.8, 729 of 296 48.9 / 40.5).  Of more than 320 port nodes, nearly as
+    // many as the compute units keep a workgroup each where the operators fit the cache: their
+    // six or more wavefronts on every unit stream from it at 7.3 TB/s, and spread out they make
     // more than one round (180 of 337 27.0 / 27.6 us a sweep, 210 uneven ones 26.8 / 28.4, 256
-    // 30.9 / 32.8; 150 23.9 / 22.8, of 296 17.6 / 14.6, 240 of 488, 435 MB, 65.1 / 58.9); so do
-    // those between one and two a unit (all run at once).
+    // 30.9 / 32.8; 150 23.9 / 22.8, of 296 17.6 / 14.6, 240 of 488, 435 MB, 65.1 / 58.9).  So do
+    // those of 193 to 320 between one and two a unit, which all run at once: within 6% either
+    // way (300 of 296 28.2 / 27.4, 360 33.4 / 32.4, 420 37.8 / 37.8, 420 uneven ones 33.6 /
+    // 34.8); of more nodes the spread form wins there, too (300 of 337 56.9 / 46.9, 490 91.8 /
+    // 81.9, 300 of 488 108 / 78).
     // FP32 keeps the order of its sums: its inner solves stop near the rounding floor.
     if constexpr (sizeof(TO) == 8) {
         const int64_t ry = (max_npn + 63) / 64;
         const size_t need = (size_t(max_npn) + 64 * kPpnSplit) * 8 + size_t(max_ports) * 4;
         const int cus = compute_units();
-        const bool one_round = (max_npn > 192 && S > cus && S < 2 * cus) ||
+        const bool one_round = (max_npn > 192 && max_npn <= 320 && S > cus && S < 2 * cus) ||
                                (max_npn > 320 && 3 * S > 2 * cus && S <= cus && op_bytes <= kCache);
         if ((max_npn > 112 || (max_npn > 64 && S <= 2 * cus)) && !one_round && S * ry <= INT32_MAX && need <= 65536) {
             auto kern = keep == 16 ? k_sweep_ppn_split<kPpnSplit, kPpnPairs, false>

@@ -13,8 +13,11 @@
 // 331x290 in random cuts (272 sweeps) 1.7 -> 0.69 ms; 768x640 in 8x8 blocks (7,680
 // sub-circuits, 832 sweeps) 6.9 -> 2.5 ms, 3.0 us a sweep.
 //
-// A circuit runs resident whenever it fits: at the largest of 32 ports that does, above, a
-// sweep takes 3.0 us against 8.1 as a launch.
+// A circuit runs resident whenever it fits.  At the largest that do, solves, a launch per
+// sweep and resident, FP64 and FP32: 8,100 sub-circuits of 32 ports 4.2 -> 1.7 and 3.8 -> 2.0
+// ms, 1,260 of 64 2.2 -> 1.0 and 2.2 -> 1.1; FP64 506 of 96 2.1 -> 0.8, 506 of 128 3.1 -> 1.4,
+// 448 dense ones of 96 6.1 -> 2.8; a compute unit each, 255 of 384 ports 12.4 -> 4.8 and
+// 8.7 -> 4.2.
 //
 // Exchange.  A wave travels as 8-byte words, each 32 bits of data and the 32-bit
 // number of its sweep (FP64: two words), written and read as relaxed agent-scope

@@ -30,7 +30,7 @@ def torch():
 # rows over workgroups, alternating and non-temporal.  FP32: the same sizes of operators.
 @pytest.mark.parametrize("prec,dims,block,S,mb", [
     ("fp64", (54, 54, 45), 9, 180, (100, 256)), ("fp64", (45, 54, 45), 9, 150, (0, 256)),
-    ("fp64", (40, 48, 80), 8, 300, (0, 256)), ("fp64", (54, 54, 90), 9, 360, (256, 512)),
+    ("fp64", (40, 48, 80), 8, 300, (0, 256)), ("fp64", (54, 54, 90), 9, 360, (256, 512)), ("fp64", (56, 56, 80), 8, 490, (256, 512)),
     ("fp64", (60, 60, 100), 10, 360, (512, 2048)), ("fp64", (64, 64, 64), 8, 512, (256, 512)),
     ("fp64", (80, 80, 80), 8, 1000, (512, 2048)),
     ("fp32_refine", (48, 48, 40), 8, 180, (0, 256)), ("fp32_refine", (80, 80, 80), 8, 1000, (256, 512)),
